@@ -487,6 +487,9 @@ static dawn_status msssp_impl(const int32_t* rowptr, const int32_t* colidx, cons
                               bool unweighted = false) {
   unweighted = unweighted || wt == DAWN_W_UNIT;  // unit weights: the hop-count tiles
   const bool f32 = wt == DAWN_W_F32;
+  if (ss_multi_fits(n, m, k))
+    return ss_multi_run(rowptr, colidx, weights, unweighted ? kWUNIT : f32 ? kWF32 : kWU32, n, m,
+                        sources, k, dist_out, info, stream);
   const int32_t kt = std::min(k, g_tuning.tile_k);
   const TileLayout L = tile_layout(n, m, kt, unweighted);
   TileArgs A = tile_args(rowptr, colidx, weights, n, m, L, ws);
@@ -628,9 +631,10 @@ extern "C" dawn_status dawn_msssp(const int32_t* rowptr, const int32_t* colidx,
   if (st != DAWN_OK) return st;
   if (k < 1) return set_error(DAWN_E_INVALID, "k must be >= 1");
   if (!sources || !dist_out) return set_error(DAWN_E_INVALID, "null pointer");
-  const size_t need = tile_layout(n, m, std::min(k, g_tuning.tile_k)).total;
+  const size_t need =
+      ss_multi_fits(n, m, k) ? 0 : tile_layout(n, m, std::min(k, g_tuning.tile_k)).total;
   StreamScratch ws(stream);
-  if ((st = ws.alloc(need)) != DAWN_OK) return st;
+  if (need && (st = ws.alloc(need)) != DAWN_OK) return st;
   return msssp_impl(rowptr, colidx, weights, wt, n, m, sources, k, dist_out, ws.p, nullptr, stream);
 }
 

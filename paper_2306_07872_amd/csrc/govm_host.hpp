@@ -127,6 +127,14 @@ dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, 
                    void* ws, dawn_run_info* info, hipStream_t stream, bool capture,
                    const void* tgraph = nullptr);
 
+// Multi-source calls on graphs whose run state fits one workgroup's LDS: one
+// workgroup per source, dist[j * n + v].  Takes no workspace.  wt: kWU32,
+// kWF32 or kWUNIT.
+bool ss_multi_fits(int64_t n, int64_t m, int32_t k);
+dawn_status ss_multi_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
+                         int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
+                         dawn_run_info* info, hipStream_t stream);
+
 // ----- distance tile ---------------------------------------------------------
 struct TileLayout {
   size_t ctl, info, D, mk[3], qgrp[3], qwave[3], qwg[3], fbm[2], vis, planes, total;

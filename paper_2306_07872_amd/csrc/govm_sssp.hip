@@ -172,9 +172,56 @@ constexpr int kLdsQWave = 512;
 constexpr int kUnroll = 4;      // edges in flight per lane (wave and workgroup tiers)
 constexpr int kUnrollLane = 4;  // edges in flight per lane (lane tier)
 
+// Position of the set bit of x that has r set bits below it (x has more than
+// r set bits): a binary search on the population counts of its low halves.
+__device__ __forceinline__ int nth_set_bit(uint32_t x, int r) {
+  int pos = 0;
+#pragma unroll
+  for (int s = 16; s >= 1; s >>= 1) {
+    const int lo = __popc(x & ((1u << s) - 1u));
+    if (r >= lo) {
+      r -= lo;
+      x >>= s;
+      pos += s;
+    }
+  }
+  return pos;
+}
+
+// Rows of a block of bitmap words, 64 at a time: lane l holds a word; the set
+// bits of the words, in order, are dealt to the lanes as the rows' edges are.
+struct ScanRows {
+  uint2 word[kWave];  // by rank among the non-empty words: {bits, bits before | lane << 16}
+  DealMarks<kWave * 32> mk;
+};
+
+// f(has, o, bit): this lane's row is bit `bit` of the word lane o holds.
+// Reached by the whole wavefront; f is called once per 64 rows.
+template <typename F>
+__device__ __forceinline__ void scan_rows(ScanRows& st, uint32_t bits, F&& f) {
+  const int lane = lane_id();
+  const int cnt = __popc(bits);
+  const int incl = wave_incl_scan(cnt);
+  const int nrows = __builtin_amdgcn_readlane(incl, kWave - 1);
+  if (nrows == 0) return;
+  const int excl = incl - cnt;
+  const unsigned long long nz = __ballot(cnt > 0);
+  if (cnt > 0)
+    st.word[lanes_below(nz)] = make_uint2(bits, (uint32_t)excl | ((uint32_t)lane << 16));
+  deal_mark(st.mk, excl, cnt, 0);
+  int before = 0;
+  for (int r0 = 0; r0 < nrows; r0 += kWave) {
+    const uint2 w = st.word[deal_rank(st.mk, r0, before)];
+    const bool has = r0 + lane < nrows;
+    const int bit = has ? nth_set_bit(w.x, r0 + lane - (int)(w.y & 0xFFFFu)) : 0;
+    f(has, (int)(w.y >> 16), bit);
+  }
+  wave_lds_sync();
+}
+
 struct SsShared {
-  int stage[kMaxWavesPerBlock * 3 * kWave];      // lane-tier batch: prefix, row base, distance
-  uint32_t scan[kMaxWavesPerBlock * 2 * kWave];  // bitmap block: short-row bits, their prefix
+  DealRows<4096> rows[kMaxWavesPerBlock];  // lane-tier batch
+  ScanRows scan[kMaxWavesPerBlock];        // bitmap block
   int32_t qw[kLdsQWave];
   uint32_t nqw, upd, gbase_w;
 };
@@ -381,22 +428,6 @@ __device__ __forceinline__ void ss_pull(const SsArgs& A, int cur, int nxt, int r
 // lowered again during this step is already marked for the next step, where
 // it is expanded with a value at least as low; expanding it now as well would
 // only repeat that work.  Its current-bitmap word is still cleared.
-// Position of the set bit of x that has r set bits below it (x has more than
-// r set bits): a binary search on the population counts of its low halves.
-__device__ __forceinline__ int nth_set_bit(uint32_t x, int r) {
-  int pos = 0;
-#pragma unroll
-  for (int s = 16; s >= 1; s >>= 1) {
-    const int lo = __popc(x & ((1u << s) - 1u));
-    if (r >= lo) {
-      r -= lo;
-      x >>= s;
-      pos += s;
-    }
-  }
-  return pos;
-}
-
 __device__ __forceinline__ bool ss_skip_row(const SsArgs& A, int nxt, int32_t u) {
   return A.skip && ((ld_agent(&A.bm[nxt][u >> 5]) >> (u & 31)) & 1u);
 }
@@ -502,11 +533,6 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
     // edges are dealt out to the lanes through an LDS prefix sum of the row
     // lengths.  The scan clears every word, heavy rows' bits included: nothing
     // else reads this bitmap during a push step.
-    int* l_incl = sh.stage + wave * 3 * kWave;
-    int* l_base = l_incl + kWave;
-    int* l_du = l_base + kWave;
-    uint32_t* s_bits = sh.scan + wave * 2 * kWave;
-    uint32_t* s_pre = s_bits + kWave;
     const int64_t nwords = ((int64_t)A.n + 31) / 32;
     int bw = kWave;
     while (bw > 1 && (nwords + bw - 1) / bw < (int64_t)nwv) bw >>= 1;
@@ -521,25 +547,11 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
           bits = word & ~A.hv[wi];
         }
       }
-      const int cnt = __popc(bits);
-      const int incl = wave_incl_scan(cnt);
-      const int nrows = __shfl(incl, kWave - 1, kWave);
-      if (nrows == 0) continue;
-      s_bits[lane] = bits;
-      s_pre[lane] = (uint32_t)(incl - cnt);
-      wave_lds_sync();
-      for (int r0 = 0; r0 < nrows; r0 += kWave) {
-        const int j = r0 + lane;
-        const bool has = j < nrows;
+      scan_rows(sh.scan[wave], bits, [&](bool has, int o, int bit) {
         int32_t start = 0, deg = 0;
         uint32_t du = 0;
         if (has) {
-          int o = 0;  // the last word whose exclusive prefix is <= j (o + s <= 63 throughout)
-  #pragma unroll
-          for (int s = 32; s >= 1; s >>= 1)
-            if (s_pre[o + s] <= (uint32_t)j) o += s;
-          const int pos = nth_set_bit(s_bits[o], j - (int)s_pre[o]);
-          const int32_t u = (int32_t)(((int64_t)blk * bw + o) * 32 + pos);
+          const int32_t u = (int32_t)(((int64_t)blk * bw + o) * 32 + bit);
           start = A.rowptr[u];
           deg = A.rowptr[u + 1] - start;
           du = ld_agent(&A.dist[u]);
@@ -548,32 +560,16 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
           if (skipped) deg = 0;
           acc.es += (unsigned long long)deg;
         }
-        const int dincl = wave_incl_scan(deg);
-        const int total = __shfl(dincl, kWave - 1, kWave);
-        l_incl[lane] = dincl;
-        l_base[lane] = start - (dincl - deg);
-        l_du[lane] = (int)du;
-        wave_lds_sync();
-        for (int base = 0; base < total; base += kWave * kUnrollLane) {
-          int32_t e[kUnrollLane], v[kUnrollLane];
-          bool ok[kUnrollLane], imp[kUnrollLane];
-          uint32_t d[kUnrollLane], cand[kUnrollLane];
-  #pragma unroll
-          for (int jj = 0; jj < kUnrollLane; jj++) {
-            const int k = base + jj * kWave + lane;
-            int owner = 0;  // first lane whose inclusive prefix exceeds k
-  #pragma unroll
-            for (int s = 32; s >= 1; s >>= 1)
-              if (l_incl[owner + s - 1] <= k) owner += s;
-            ok[jj] = k < total;
-            e[jj] = l_base[owner] + k;
-            d[jj] = (uint32_t)l_du[owner];
-          }
+        deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, [&](const int32_t (&e)[kUnrollLane],
+                                                                  const bool (&ok)[kUnrollLane],
+                                                                  const uint32_t (&d)[kUnrollLane]) {
+          int32_t v[kUnrollLane];
+          bool imp[kUnrollLane];
+          uint32_t cand[kUnrollLane];
           ss_relax_pre<WT, kUnrollLane>(A, e, ok, d, imp, v, cand);
           ss_enqueue<WT, kUnrollLane, PULL>(A, imp, v, cand, nxt, rn, acc, sh);
-        }
-        wave_lds_sync();
-      }
+        });
+      });
     }
 
   }
@@ -690,7 +686,7 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
 // kernels; the queue length and the ptr flag live in LDS.
 // ---------------------------------------------------------------------------
 struct SsSmallShared {
-  int stage[kMaxWavesPerBlock * 3 * kWave];  // per wavefront: prefix, row base, distance
+  DealRows<4096> rows[kMaxWavesPerBlock];
   uint32_t cnt_next, upd;
 };
 
@@ -740,9 +736,6 @@ __global__ void __launch_bounds__(1024) ss_small_kernel(SsArgs A, const int32_t*
     __syncthreads();
     if (threadIdx.x == 0) sh.cnt_next = 0u;
     __syncthreads();
-    int* l_incl = sh.stage + wave * 3 * kWave;
-    int* l_base = l_incl + kWave;
-    int* l_du = l_base + kWave;
     for (;;) {
       const int cur = step & 1, nxt = cur ^ 1;
       for (uint32_t bi = wave; (uint64_t)bi * kWave < cnt; bi += W) {
@@ -760,27 +753,11 @@ __global__ void __launch_bounds__(1024) ss_small_kernel(SsArgs A, const int32_t*
             acc.es += (unsigned long long)deg;
           }
         }
-        const int incl = wave_incl_scan(deg);
-        const int total = __shfl(incl, kWave - 1, kWave);
-        l_incl[lane] = incl;
-        l_base[lane] = start - (incl - deg);
-        l_du[lane] = (int)du;
-        wave_lds_sync();
-        for (int base = 0; base < total; base += kWave * kUnrollLane) {
-          int32_t e[kUnrollLane], v[kUnrollLane];
-          bool ok[kUnrollLane], imp[kUnrollLane];
-          uint32_t d[kUnrollLane];
-#pragma unroll
-          for (int j = 0; j < kUnrollLane; j++) {
-            const int k = base + j * kWave + lane;
-            int owner = 0;  // first lane whose inclusive prefix exceeds k
-#pragma unroll
-            for (int s = 32; s >= 1; s >>= 1)
-              if (l_incl[owner + s - 1] <= k) owner += s;
-            ok[j] = k < total;
-            e[j] = l_base[owner] + k;
-            d[j] = (uint32_t)l_du[owner];
-          }
+        deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, [&](const int32_t (&e)[kUnrollLane],
+                                                                  const bool (&ok)[kUnrollLane],
+                                                                  const uint32_t (&d)[kUnrollLane]) {
+          int32_t v[kUnrollLane];
+          bool imp[kUnrollLane];
           ss_relax_n<WT, kUnrollLane>(A, e, ok, d, imp, v);
 #pragma unroll
           for (int j = 0; j < kUnrollLane; j++) {
@@ -803,8 +780,7 @@ __global__ void __launch_bounds__(1024) ss_small_kernel(SsArgs A, const int32_t*
               }
             }
           }
-        }
-        wave_lds_sync();
+        });
       }
       __syncthreads();
       const uint32_t upd = sh.upd, cn = min(sh.cnt_next, A.cap_v);
@@ -841,171 +817,261 @@ __global__ void __launch_bounds__(1024) ss_small_kernel(SsArgs A, const int32_t*
 }
 
 // ---------------------------------------------------------------------------
-// tiny graphs: the whole state in LDS
+// one workgroup per source: the run's state in LDS
 //
-// With n <= kTinyN the distances, both beta bitmaps and both frontier queues
-// fit in one workgroup's LDS, so every step runs on LDS atomics (a few
-// hundred cycles) instead of device-scope atomics; only the CSR is read from
-// global memory.  The final distances are copied out once.
+// With n <= kCuMaxN the distances and both beta bitmaps of a run fit in one
+// workgroup's LDS, so every step runs on LDS atomics and a workgroup barrier;
+// only the CSR is read from global memory (it stays in the L2), and the final
+// distances are copied out once.  A step is bound by one compute unit's
+// instruction rate and a chain of about ten dependent loads.  Measured, fp32
+// ER graphs, call times: n = 15,013, m = 120,104: 1165 us with the frontier
+// queue, distances and bitmaps in global memory, 214 us here (347 us with the
+// persistent grid); n = 10,000 grid: 387 us against 2046 us.
+// MULTI: workgroup j runs source j of a multi-source call, so k sources keep k
+// compute units busy with no grid barrier and no tile (all pairs of an ER
+// graph with 1531 vertices and 12,248 edges: 5.5 ms with tiles of 256
+// columns, 0.39 ms here).
 // ---------------------------------------------------------------------------
 constexpr int kTinyN = 6144;
 
-struct SsTinyShared {
-  int stage[kMaxWavesPerBlock * 3 * kWave];
-  uint32_t dist[kTinyN];
-  uint16_t q[2][kTinyN];
-  uint32_t bm[2][kTinyN / 32];
-  uint32_t cnt_next, upd;
-};
+// End of a one-workgroup run, reached by every thread: the counters are summed
+// over the workgroup (`part`: LDS scratch).  A single run stores them and its
+// state in the control words and reports as ss_report does; a run of a
+// multi-source call adds them to `info` (zeroed by an earlier launch).
+template <int WT, bool MULTI>
+__device__ void ss_wg_report(const SsArgs& A, dawn_run_info* info, int32_t status, uint32_t step,
+                             const Acc& acc, unsigned long long (*part)[3]) {
+  SsCtl* C = A.ctl;
+  const unsigned long long v0 = wave_sum64(acc.fe), v1 = wave_sum64(acc.es),
+                           v2 = wave_sum64(acc.im);
+  const int w = threadIdx.x / kWave;
+  if (lane_id() == 0) {
+    part[w][0] = v0;
+    part[w][1] = v1;
+    part[w][2] = v2;
+  }
+  // the int32 range flag is set by any thread's atomic
+  if (!MULTI && (WT == kWI32 || status == -1)) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  unsigned long long fe = 0, es = 0, im = 0;
+  for (int i = 0; i < (int)(blockDim.x / kWave); i++) {
+    fe += part[i][0];
+    es += part[i][1];
+    im += part[i][2];
+  }
+  if constexpr (MULTI) {
+    if (!info) {
+      latch_status(A.latch, status);
+      return;
+    }
+    atomicMax(&info->steps, (int32_t)step);
+    atomicMin(&info->converged, status);
+    auto add = [](int64_t* p, unsigned long long x) {
+      atomicAdd(reinterpret_cast<unsigned long long*>(p), x);
+    };
+    add(&info->frontier_entries, fe);
+    add(&info->edges_scanned, es);
+    add(&info->improvements, im);
+    add(&info->union_rows, fe);
+    add(&info->union_edges, es);
+    return;
+  }
+  SsCounters& S = C->ctr;
+  st_agent64(&S.fe, fe);
+  st_agent64(&S.es, es);
+  st_agent64(&S.im, im);
+  if (status == -1) {
+    // failed validation: report what the control words record
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    ss_report<WT>(C, info, A.latch);
+    return;
+  }
+  if (WT == kWI32) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  const uint32_t ab = ld_agent(&C->abort), ov = ld_agent(&C->overflow);
+  const uint32_t nf = WT == kWI32 ? ld_agent(&C->negfloor) : 0u;
+  st_agent(&C->step, step);
+  st_agent_i(&C->converged, status);
+  st_agent(&C->done, 1u);
+  int32_t conv = run_status(status, ab, ov);
+  if (WT == kWI32 && conv == 1 && nf) conv = 0;
+  if (!info) {
+    latch_status(A.latch, conv);
+  } else {
+    info->steps = (int32_t)step;
+    info->converged = conv;
+    info->frontier_entries = (int64_t)fe;
+    info->edges_scanned = (int64_t)es;
+    info->improvements = (int64_t)im;
+    info->union_rows = (int64_t)fe;
+    info->union_edges = (int64_t)es;
+  }
+}
 
+// A distance key as the caller sees it (int32: the sign bit flipped back).
 template <int WT>
-__global__ void __launch_bounds__(1024) ss_tiny_kernel(SsArgs A, const int32_t* sources,
-                                                       const int64_t* voff, int32_t count,
-                                                       int32_t single, int32_t check_valid,
-                                                       dawn_run_info* info) {
-  __shared__ SsTinyShared sh;
+__device__ __forceinline__ uint32_t key_value(uint32_t key) {
+  return WT == kWI32 ? key ^ 0x80000000u : key;
+}
+
+// Sizes of the kernel's instances: the state of a smaller graph leaves room
+// for a copy of the row pointers (one L2 round trip less per step), and for a
+// second workgroup per compute unit.
+constexpr int kCuMidN = 16384, kCuMaxN = 32768;
+constexpr int kUnrollCu = 4;  // edges in flight per lane
+constexpr int kCuWin = 1024;  // edges marked at a time (sized so that kCuMaxN fits)
+
+template <int N>
+struct SsCuShared {
+  static constexpr bool kRows = N <= kCuMidN;  // row pointers in LDS
+  uint32_t dist[N];
+  uint32_t bm[2][N / 32];
+  int32_t rp[kRows ? N + 1 : 1];
+  union {
+    struct {
+      DealRows<kCuWin> rows;
+      ScanRows scan;
+    } st[kMaxWavesPerBlock];
+    unsigned long long part[kMaxWavesPerBlock][3];  // the report's sums, after the last step
+  };
+  uint32_t upd[3];
+};
+static_assert(sizeof(SsCuShared<kCuMaxN>) <= 160 * 1024, "LDS of a compute unit");
+static_assert(sizeof(SsCuShared<kCuMidN>) <= 160 * 1024, "LDS of a compute unit");
+
+template <int WT, int N, bool MULTI>
+__global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* sources,
+                                                     const int64_t* voff, int32_t count,
+                                                     int32_t single, int32_t check_valid,
+                                                     dawn_run_info* info) {
+  __shared__ SsCuShared<N> sh;
+  constexpr bool kRows = SsCuShared<N>::kRows;
   SsCtl* C = A.ctl;
   const int lane = lane_id(), wave = threadIdx.x >> 6, W = blockDim.x >> 6;
   const int n = A.n, nwords = (n + 31) / 32;
+  uint32_t* out = A.dist;
+  int32_t src = A.src;
   uint32_t step = 0;
   int32_t status = 1;
   Acc acc;
-  if (check_valid && ld_agent(&C->done)) {
-    status = -1;
+  if constexpr (MULTI) {
+    out += (size_t)blockIdx.x * n;
+    src = sources[blockIdx.x];
+    if (src < 0 || src >= n) status = -1;
+  } else {
+    if (check_valid && ld_agent(&C->done)) status = -1;
+  }
+  if (status == -1) {
+    // nothing is run: every distance INF
+    for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = key_value<WT>(inf_key<WT>());
   } else {
     for (int i = threadIdx.x; i < n; i += blockDim.x) sh.dist[i] = inf_key<WT>();
     for (int i = threadIdx.x; i < nwords; i += blockDim.x) {
       sh.bm[0][i] = 0u;
       sh.bm[1][i] = 0u;
     }
-    if (threadIdx.x == 0) {
-      sh.cnt_next = 0u;
-      sh.upd = 0u;
+    if constexpr (kRows)
+      for (int i = threadIdx.x; i <= n; i += blockDim.x) sh.rp[i] = A.rowptr[i];
+    if (threadIdx.x < 3) sh.upd[threadIdx.x] = 0u;
+    if (!MULTI && threadIdx.x == 0) {
       // the status words the report reads: the workspace may hold an earlier
       // run's (atomics, as the later reports are)
       atomicExch(&C->negfloor, 0u);
       atomicExch(&C->abort, 0u);
       atomicExch(&C->overflow, 0u);
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < count; j += blockDim.x) {
-      int64_t s = sources ? (int64_t)sources[j] : (int64_t)single;
-      if (voff) s += voff[j];
-      sh.dist[s] = zero_key<WT>();
-      const uint32_t bit = 1u << (s & 31);
-      if (atomicOr(&sh.bm[0][s >> 5], bit) & bit) continue;
-      sh.q[0][atomicAdd(&sh.cnt_next, 1u)] = (uint16_t)s;
+    if constexpr (MULTI) {
+      if (threadIdx.x == 0) {
+        sh.dist[src] = zero_key<WT>();
+        sh.bm[0][src >> 5] = 1u << (src & 31);
+      }
+    } else {
+      for (int j = threadIdx.x; j < count; j += blockDim.x) {
+        int64_t s = sources ? (int64_t)sources[j] : (int64_t)single;
+        if (voff) s += voff[j];
+        sh.dist[s] = zero_key<WT>();
+        atomicOr(&sh.bm[0][s >> 5], 1u << (s & 31));
+      }
     }
     __syncthreads();
-    uint32_t cnt = sh.cnt_next;
-    __syncthreads();
-    if (threadIdx.x == 0) sh.cnt_next = 0u;
-    __syncthreads();
-    int* l_incl = sh.stage + wave * 3 * kWave;
-    int* l_base = l_incl + kWave;
-    int* l_du = l_base + kWave;
+    auto& st = sh.st[wave];
     for (;;) {
-      const int cur = step & 1, nxt = cur ^ 1;
-      for (uint32_t bi = wave; (uint64_t)bi * kWave < cnt; bi += W) {
-        const uint32_t i = bi * kWave + lane;
-        int32_t u = 0, start = 0, deg = 0;
-        uint32_t du = 0;
-        if (i < cnt) {
-          u = sh.q[cur][i];
-          start = A.rowptr[u];
-          deg = A.rowptr[u + 1] - start;
-          du = sh.dist[u];
-          sh.bm[cur][u >> 5] = 0u;
-          if (deg > 0) {
-            acc.fe += 1;
+      uint32_t* bc = sh.bm[step & 1];
+      uint32_t* bn = sh.bm[(step & 1) ^ 1];
+      bool upd = false;
+      // wavefront w scans words w, w + W, ..., up to 64 of them at a time (one
+      // pass at 1024 threads): a frontier band is shared by all wavefronts, and
+      // a wavefront's rows wait for one chain of loads per 64 of them
+      for (int w0 = wave; w0 < nwords; w0 += kWave * W) {
+        const int wi = w0 + lane * W;
+        uint32_t bits = 0u;
+        if (wi < nwords) {
+          bits = bc[wi];
+          if (bits) bc[wi] = 0u;
+        }
+        scan_rows(st.scan, bits, [&](bool has, int o, int bit) {
+          int32_t start = 0, deg = 0;
+          uint32_t du = 0;
+          if (has) {
+            const int u = (w0 + o * W) * 32 + bit;
+            if constexpr (kRows) {
+              start = sh.rp[u];
+              deg = sh.rp[u + 1] - start;
+            } else {
+              start = A.rowptr[u];
+              deg = A.rowptr[u + 1] - start;
+            }
+            du = sh.dist[u];
+            if (deg > 0) acc.fe += 1;  // a frontier row (rows without edges are not counted)
+            // lowered again in this step: expanded in the next, with the lower value
+            if (A.skip && ((bn[u >> 5] >> (u & 31)) & 1u)) deg = 0;
             acc.es += (unsigned long long)deg;
           }
-        }
-        const int incl = wave_incl_scan(deg);
-        const int total = __shfl(incl, kWave - 1, kWave);
-        l_incl[lane] = incl;
-        l_base[lane] = start - (incl - deg);
-        l_du[lane] = (int)du;
-        wave_lds_sync();
-        for (int base = 0; base < total; base += kWave * kUnrollLane) {
-          int32_t v[kUnrollLane];
-          uint32_t cand[kUnrollLane];
-          bool ok[kUnrollLane];
+          deal_rows<kUnrollCu>(st.rows, start, deg, du, [&](const int32_t (&e)[kUnrollCu],
+                                                            const bool (&ok)[kUnrollCu],
+                                                            const uint32_t (&d)[kUnrollCu]) {
+            int32_t v[kUnrollCu];
+            uint32_t cand[kUnrollCu], dv[kUnrollCu];
 #pragma unroll
-          for (int j = 0; j < kUnrollLane; j++) {
-            const int k = base + j * kWave + lane;
-            int owner = 0;  // first lane whose inclusive prefix exceeds k
+            for (int j = 0; j < kUnrollCu; j++) {
+              v[j] = 0;
+              cand[j] = 0u;
+              if (ok[j]) {
+                v[j] = A.colidx[e[j]];
+                cand[j] = relax_key<WT>(d[j], WT == kWUNIT ? 1u : A.w[e[j]]);
+                if constexpr (WT == kWI32)
+                  if (cand[j] == 0u) atomicOr(&C->negfloor, 1u);  // sum left the int32 range
+              }
+            }
 #pragma unroll
-            for (int s = 32; s >= 1; s >>= 1)
-              if (l_incl[owner + s - 1] <= k) owner += s;
-            ok[j] = k < total;
-            v[j] = 0;
-            cand[j] = 0u;
-            if (ok[j]) {
-              const int32_t e = l_base[owner] + k;
-              uint32_t we = 1u;
-              v[j] = A.colidx[e];
-              if constexpr (WT != kWUNIT) we = A.w[e];
-              cand[j] = relax_key<WT>((uint32_t)l_du[owner], we);
-              if constexpr (WT == kWI32)
-                if (cand[j] == 0u) atomicOr(&A.ctl->negfloor, 1u);  // sum left the int32 range
-            }
-          }
+            for (int j = 0; j < kUnrollCu; j++) dv[j] = sh.dist[v[j]];
 #pragma unroll
-          for (int j = 0; j < kUnrollLane; j++) {
-            bool newv = false;
-            if (ok[j] && v[j] != A.src && cand[j] < sh.dist[v[j]] &&
-                cand[j] < atomicMin(&sh.dist[v[j]], cand[j])) {
-              acc.im += 1;
-              sh.upd = 1u;
-              const uint32_t bit = 1u << (v[j] & 31);
-              newv = (atomicOr(&sh.bm[nxt][v[j] >> 5], bit) & bit) == 0u;
+            for (int j = 0; j < kUnrollCu; j++) {
+              if (ok[j] && cand[j] < dv[j] && v[j] != src &&
+                  cand[j] < atomicMin(&sh.dist[v[j]], cand[j])) {
+                acc.im += 1;
+                upd = true;
+                __hip_atomic_fetch_or(&bn[v[j] >> 5], 1u << (v[j] & 31), __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+              }
             }
-            const unsigned long long b = __ballot(newv);
-            if (b != 0ull) {
-              const int leader = __ffsll((long long)b) - 1;
-              uint32_t pos = 0;
-              if (lane == leader) pos = atomicAdd(&sh.cnt_next, (uint32_t)__popcll(b));
-              pos = __shfl(pos, leader, kWave) + lanes_below(b);
-              if (newv) sh.q[nxt][pos] = (uint16_t)v[j];
-            }
-          }
-        }
-        wave_lds_sync();
+          });
+        });
       }
+      // three flags rotate: step t sets (t+1) mod 3, read after the barrier,
+      // and clears (t+2) mod 3, which nothing else touches before step t+1 ends
+      if (threadIdx.x == 0) sh.upd[(step + 2) % 3] = 0u;
+      if (upd) sh.upd[(step + 1) % 3] = 1u;
       __syncthreads();
-      const uint32_t upd = sh.upd, cn = sh.cnt_next;
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        sh.upd = 0u;
-        sh.cnt_next = 0u;
-      }
-      __syncthreads();
+      const uint32_t more = sh.upd[(step + 1) % 3];
       step++;
-      cnt = cn;
-      if (!upd) { status = 1; break; }
-      if (step >= (uint32_t)A.n) { status = 0; break; }
+      if (!more) { status = 1; break; }
+      if (step >= (uint32_t)n) { status = 0; break; }
     }
-    for (int i = threadIdx.x; i < n; i += blockDim.x) A.dist[i] = sh.dist[i];
+    for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = key_value<WT>(sh.dist[i]);
   }
-  // thread i zeroes the counter that it then adds to (flush_acc: fe, es, im)
-  SsCounters& S = C->ctr;
-  if (threadIdx.x == 0) st_agent64(&S.fe, 0ull);
-  if (threadIdx.x == 1) st_agent64(&S.es, 0ull);
-  if (threadIdx.x == 2) st_agent64(&S.im, 0ull);
-  flush_acc(acc, &S.fe, &S.es, &S.im, nullptr, nullptr);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (status != -1) {
-      st_agent(&C->step, step);
-      st_agent_i(&C->converged, status);
-      st_agent(&C->done, 1u);
-    }
-    ss_report<WT>(C, info, A.latch);
-  }
+  ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part);  // (after the last step's barrier)
 }
 
 // ---------------------------------------------------------------------------
@@ -1013,8 +1079,8 @@ __global__ void __launch_bounds__(1024) ss_tiny_kernel(SsArgs A, const int32_t* 
 //
 // With n <= kTinyN and m <= kLdsM a workgroup of kLdsThreads threads holds the
 // whole run: the distances, the frontier bitmaps and the weights in LDS, and
-// each thread's edges t, t + kLdsThreads, ... (at most kLdsEdges) in
-// registers, as packed (source, target) ids.  A step then needs no queue: a thread
+// each thread's edges t, t + kLdsThreads, ... (at most E, the instance's edges
+// per thread) in registers, as packed (source, target) ids.  A step then needs no queue: a thread
 // relaxes each of its edges whose source's bit is set in the step's frontier
 // bitmap.  Those are exactly the out-edges of the frontier, the relaxations
 // Algorithm 2 makes, and every thread gets the same number of edges whatever
@@ -1024,35 +1090,45 @@ __global__ void __launch_bounds__(1024) ss_tiny_kernel(SsArgs A, const int32_t* 
 // (t+2) mod 3, which step t-1 read and step t+1 fills.
 // ---------------------------------------------------------------------------
 constexpr int kLdsThreads = 1024;
-constexpr int kLdsEdges = 16;  // edges per thread
-constexpr int kLdsM = kLdsThreads * kLdsEdges;
+constexpr int kLdsM = kLdsThreads * 16;  // the largest instance: 16 edges per thread
 constexpr int kLdsRows = kTinyN / kLdsThreads;  // vertices per thread
-constexpr int kLdsHalf = kLdsEdges / 2;
 
+template <int E>
 struct SsLdsShared {
   uint32_t dist[kTinyN];
   uint32_t bm[3][kTinyN / 32];
   uint32_t upd[3];
-  uint16_t src[kLdsM];  // each edge's source, read once to fill the registers
-  uint32_t w[kLdsM];
+  uint16_t src[kLdsThreads * E];  // each edge's source, read once to fill the registers
+  uint32_t w[kLdsThreads * E];
   unsigned long long part[kLdsThreads / kWave][3];
 };
 
-template <int WT>
+template <int WT, int E, bool MULTI>
 __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int32_t* sources,
                                                              const int64_t* voff, int32_t count,
                                                              int32_t single, int32_t check_valid,
                                                              dawn_run_info* info) {
-  __shared__ SsLdsShared sh;
+  constexpr int kLdsEdges = E, kLdsHalf = E < 8 ? E : 8;
+  __shared__ SsLdsShared<E> sh;
   SsCtl* C = A.ctl;
   const int n = A.n, m = A.m, nwords = (n + 31) / 32, t = threadIdx.x;
+  uint32_t* out = A.dist;
+  int32_t src = A.src;
   uint32_t step = 0;
   int32_t status = 1;
   Acc acc;
-  if (check_valid && ld_agent(&C->done)) {
-    status = -1;
+  if constexpr (MULTI) {
+    out += (size_t)blockIdx.x * n;
+    src = sources[blockIdx.x];
+    if (src < 0 || src >= n) status = -1;
   } else {
-    if (t == 0) {
+    if (check_valid && ld_agent(&C->done)) status = -1;
+  }
+  if (status == -1) {
+    // nothing is run: every distance INF
+    for (int i = t; i < n; i += kLdsThreads) out[i] = key_value<WT>(inf_key<WT>());
+  } else {
+    if (!MULTI && t == 0) {
       // the status words the report reads: the workspace may hold an earlier
       // run's
       atomicExch(&C->negfloor, 0u);
@@ -1106,11 +1182,18 @@ __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int
         if (e == 0 || sh.src[e - 1] != u) first |= 1u << j;
       }
     }
-    for (int j = t; j < count; j += kLdsThreads) {
-      int64_t s = sources ? (int64_t)sources[j] : (int64_t)single;
-      if (voff) s += voff[j];
-      sh.dist[s] = zero_key<WT>();
-      atomicOr(&sh.bm[0][s >> 5], 1u << (s & 31));
+    if constexpr (MULTI) {
+      if (t == 0) {
+        sh.dist[src] = zero_key<WT>();
+        sh.bm[0][src >> 5] = 1u << (src & 31);
+      }
+    } else {
+      for (int j = t; j < count; j += kLdsThreads) {
+        int64_t s = sources ? (int64_t)sources[j] : (int64_t)single;
+        if (voff) s += voff[j];
+        sh.dist[s] = zero_key<WT>();
+        atomicOr(&sh.bm[0][s >> 5], 1u << (s & 31));
+      }
     }
     __syncthreads();
     for (;;) {
@@ -1157,7 +1240,7 @@ __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int
             acc.fe += (first >> j) & 1u;
             if constexpr (WT == kWI32)
               if (cand[i] == 0u) atomicOr(&A.ctl->negfloor, 1u);  // sum left the int32 range
-            if ((int32_t)v != A.src && cand[i] < dv[i]) need |= 1u << i;
+            if ((int32_t)v != src && cand[i] < dv[i]) need |= 1u << i;
           }
         }
         // returning atomics, all issued before any result is used
@@ -1187,59 +1270,9 @@ __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int
       if (!more) { status = 1; break; }
       if (step >= (uint32_t)n) { status = 0; break; }
     }
-    for (int i = t; i < n; i += kLdsThreads) A.dist[i] = sh.dist[i];
+    for (int i = t; i < n; i += kLdsThreads) out[i] = key_value<WT>(sh.dist[i]);
   }
-  // One workgroup owns the counters: they are summed in LDS and stored, not
-  // added to, and the report is made from the values this workgroup holds.
-  {
-    const unsigned long long v0 = wave_sum64(acc.fe), v1 = wave_sum64(acc.es),
-                             v2 = wave_sum64(acc.im);
-    if (lane_id() == 0) {
-      sh.part[t / kWave][0] = v0;
-      sh.part[t / kWave][1] = v1;
-      sh.part[t / kWave][2] = v2;
-    }
-  }
-  // the int32 range flag is set by any thread's atomic
-  if (WT == kWI32 || status == -1) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  __syncthreads();
-  if (t == 0) {
-    unsigned long long fe = 0, es = 0, im = 0;
-    for (int i = 0; i < kLdsThreads / kWave; i++) {
-      fe += sh.part[i][0];
-      es += sh.part[i][1];
-      im += sh.part[i][2];
-    }
-    SsCounters& S = C->ctr;
-    st_agent64(&S.fe, fe);
-    st_agent64(&S.es, es);
-    st_agent64(&S.im, im);
-    if (status == -1) {
-      // failed validation: report what the control words record
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      ss_report<WT>(C, info, A.latch);
-    } else {
-      if (WT == kWI32) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      const uint32_t ab = ld_agent(&C->abort), ov = ld_agent(&C->overflow);
-      const uint32_t nf = WT == kWI32 ? ld_agent(&C->negfloor) : 0u;
-      st_agent(&C->step, step);
-      st_agent_i(&C->converged, status);
-      st_agent(&C->done, 1u);
-      int32_t conv = run_status(status, ab, ov);
-      if (WT == kWI32 && conv == 1 && nf) conv = 0;
-      if (!info) {
-        latch_status(A.latch, conv);
-      } else {
-        info->steps = (int32_t)step;
-        info->converged = conv;
-        info->frontier_entries = (int64_t)fe;
-        info->edges_scanned = (int64_t)es;
-        info->improvements = (int64_t)im;
-        info->union_rows = (int64_t)fe;
-        info->union_edges = (int64_t)es;
-      }
-    }
-  }
+  ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part);
 }
 
 // ---------------------------------------------------------------------------
@@ -1263,6 +1296,67 @@ SsLayout ss_layout(int64_t n, int64_t m) {
   L.hv = c.take((size_t)L.nwords * 4);
   L.total = c.off;
   return L;
+}
+
+// Whether a graph takes the edge-parallel kernel, which holds it whole.
+static bool ss_wg_whole(int64_t n, int64_t m) { return n <= kTinyN && m <= kLdsM; }
+
+// The one-workgroup kernel whose LDS state fits the graph (n <= kCuMaxN).
+using SsWgKernel = void (*)(SsArgs, const int32_t*, const int64_t*, int32_t, int32_t, int32_t,
+                            dawn_run_info*);
+template <int WT, bool MULTI>
+static SsWgKernel ss_wg_kernel(int64_t n, int64_t m) {
+  if (ss_wg_whole(n, m))
+    return m <= 4 * kLdsThreads   ? ss_lds_kernel<WT, 4, MULTI>
+           : m <= 8 * kLdsThreads ? ss_lds_kernel<WT, 8, MULTI>
+                                  : ss_lds_kernel<WT, 16, MULTI>;
+  return n <= kTinyN    ? ss_cu_kernel<WT, kTinyN, MULTI>
+         : n <= kCuMidN ? ss_cu_kernel<WT, kCuMidN, MULTI>
+                        : ss_cu_kernel<WT, kCuMaxN, MULTI>;
+}
+
+// Multi-source calls on small graphs: one workgroup per source, which costs
+// the same for 1 to 256 sources (one per compute unit) and grows with m; a
+// tile costs less per edge the fewer its columns.  Measured (us, tile against
+// workgroups), ER n = 32,768: m = 131,072, k = 2 656 / 284, k = 256 2279 /
+// 354; m = 262,144, k = 2 528 / 371; m = 524,288, k = 2 542 / 656, k = 64 1296
+// / 744; m = 1,048,576, k = 64 1284 / 1314, k = 256 4044 / 1260.  R-MAT scale
+// 15: m = 524,288, k = 16 628 / 657, k = 64 741 / 679; m = 1,048,576, k = 256
+// 2305 / 1561.
+bool ss_multi_fits(int64_t n, int64_t m, int32_t k) {
+  const Tuning& T = tuning();
+  const int64_t most = (int64_t)T.small_m * (k >= 128 ? 8 : k >= 32 ? 4 : k >= 2 ? 2 : 1);
+  return T.mode == 0 && T.tile_step_launches > 0 && T.validate == 0 && n <= kCuMaxN && m <= most;
+}
+
+__global__ void ss_multi_info_kernel(dawn_run_info* info) {
+  if (threadIdx.x == 0) {
+    *info = dawn_run_info{};
+    info->converged = 1;
+  }
+}
+
+dawn_status ss_multi_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
+                         int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
+                         dawn_run_info* info, hipStream_t stream) {
+  SsArgs A{};
+  A.rowptr = rowptr;
+  A.colidx = colidx;
+  A.w = static_cast<const uint32_t*>(w);
+  A.dist = static_cast<uint32_t*>(dist);
+  A.n = n;
+  A.m = m;
+  A.skip = tuning().ss_skip;
+  A.latch = dev_info().latch;
+  const SsWgKernel kern = wt == kWF32    ? ss_wg_kernel<kWF32, true>(n, m)
+                          : wt == kWUNIT ? ss_wg_kernel<kWUNIT, true>(n, m)
+                                         : ss_wg_kernel<kWU32, true>(n, m);
+  if (info) hipLaunchKernelGGL(ss_multi_info_kernel, dim3(1), dim3(64), 0, stream, info);
+  void* tk = ktimer_begin(stream);
+  hipLaunchKernelGGL(kern, dim3((unsigned)k), dim3(1024), 0, stream, A, sources, nullptr, k, 0, 0,
+                     info);
+  ktimer_end(tk, stream, 1);
+  return hip_check(hipGetLastError(), "one workgroup per source");
 }
 
 Residency ss_persistent_residency(int threads) {
@@ -1298,12 +1392,10 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
                          A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
     }
     void* tk = capture ? nullptr : ktimer_begin(stream);
-    if (A.n <= kTinyN && A.m <= kLdsM)  // its own workgroup size (the whole graph in registers)
-      hipLaunchKernelGGL(ss_lds_kernel<WT>, dim3(1), dim3(kLdsThreads), 0, stream, A,
-                         seeds.sources_dev, seeds.voff_dev, seeds.count, seeds.source,
-                         (int32_t)(T.validate != 0), info);
-    else if (A.n <= kTinyN)
-      hipLaunchKernelGGL(ss_tiny_kernel<WT>, dim3(1), dim3(threads), 0, stream, A,
+    const bool in_lds = A.n <= kCuMaxN;
+    if (in_lds)
+      hipLaunchKernelGGL((ss_wg_kernel<WT, false>(A.n, A.m)), dim3(1),
+                         dim3(ss_wg_whole(A.n, A.m) ? kLdsThreads : threads), 0, stream, A,
                          seeds.sources_dev, seeds.voff_dev, seeds.count, seeds.source,
                          (int32_t)(T.validate != 0), info);
     else
@@ -1311,7 +1403,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
                          seeds.sources_dev, seeds.voff_dev, seeds.count, seeds.source,
                          (int32_t)(T.validate != 0), info);
     ktimer_end(tk, stream, 1);
-    if constexpr (WT == kWI32)
+    if (WT == kWI32 && !in_lds)
       hipLaunchKernelGGL(ss_decode_i32_kernel, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                          (int64_t)A.n);
     return hip_check(hipGetLastError(), "small-graph launch");
