@@ -52,7 +52,9 @@ __device__ __align__(256) uint32_t g_run_latch[64];
 // object until the process ends.  Host code never names the array in a launch
 // or copy; it uses the device address that hipGetSymbolAddress returned with
 // that device current (DevInfo::noalloc).
-static __device__ __align__(256) unsigned char g_noalloc_scratch[DAWN_NOALLOC_SCRATCH_BYTES];
+// The grid barrier's slots come on top of the documented bytes.
+constexpr size_t kNoallocBytes = DAWN_NOALLOC_SCRATCH_BYTES + sizeof(GridBar::slot);
+static __device__ __align__(256) unsigned char g_noalloc_scratch[kNoallocBytes];
 
 const DevInfo& dev_info() {
   int d = 0;
@@ -433,7 +435,7 @@ extern "C" dawn_status dawn_sssp_noalloc(const int32_t* rowptr, const int32_t* c
   if (source < 0 || source >= n) return set_error(DAWN_E_INVALID, "source %d out of range", source);
   if (!dist_out) return set_error(DAWN_E_INVALID, "dist_out is null");
   const size_t bytes = ss_layout(n, m).total;
-  if (bytes > (size_t)DAWN_NOALLOC_SCRATCH_BYTES)
+  if (bytes > kNoallocBytes)
     return set_error(DAWN_E_WORKSPACE,
                      "graph needs %zu bytes of scratch; dawn_sssp_noalloc holds %zu (use dawn_sssp_ws)",
                      bytes, (size_t)DAWN_NOALLOC_SCRATCH_BYTES);

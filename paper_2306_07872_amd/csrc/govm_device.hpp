@@ -34,6 +34,14 @@ struct alignas(128) LineU32 {
   uint32_t v;
 };
 
+// Grid barrier of persistent launches (grid_sync): a slot per workgroup and the
+// release word, each run's epochs counting up from the control block's bar_base.
+constexpr int kMaxGrid = 2048;  // workgroups of a persistent launch
+struct alignas(128) GridBar {
+  LineU32 release;
+  uint32_t slot[kMaxGrid];
+};
+
 // Counters of a single-source run.  Every workgroup of a step adds to them
 // (memory-side atomics): on one line of their own they measured faster than
 // striped over 32 lines, and faster than beside the queue and step words.
@@ -53,13 +61,13 @@ struct alignas(256) SsCtl {
   int32_t converged;          // see dawn_run_info
   uint32_t abort;             // set when a barrier wait gives up
   uint32_t overflow;          // a queue capacity was exceeded (cannot happen on valid input)
-  uint32_t bar_base;          // value of `bar` when the next persistent launch starts
+  uint32_t bar_base;          // the last barrier epoch of earlier persistent launches
   uint32_t negfloor;          // int32 weights: a path sum fell to or below INT32_MIN
   alignas(128) uint32_t upd[kRot];  // [step % 4]: any improvement during the previous step
-  LineU32 bar;                // grid barrier arrivals (monotone within a launch)
   LineU32 arrive;             // last-block detection of step launches
   LineU32 cnt[kRot][4];       // [step % 4][tier]: lane, wave, workgroup-chunk records
   SsCounters ctr;
+  GridBar bar;
 };
 
 // Counters of a tile run.
@@ -77,7 +85,7 @@ struct alignas(256) TileCtl {
   int32_t converged;
   uint32_t abort, overflow, bar_base;
   uint32_t cstep;                      // the step whose compaction ran last
-  LineU32 bar;                         // grid barrier arrivals (monotone within a launch)
+  GridBar bar;
   LineU32 arrive;                      // last-block detection of step launches
   LineU32 cnt[kRot][4];                // [step % 4][tier]: group, wave, workgroup-chunk
   CtrStripe ctr[kCtrStripes];           // statistics, summed over the stripes
@@ -177,6 +185,14 @@ __device__ __forceinline__ int32_t ld_queue(const int32_t* p) { return ld_agent_
 __device__ __forceinline__ int4 ld_queue4(const int4* p) {
   const int32_t* q = reinterpret_cast<const int32_t*>(p);
   return make_int4(ld_agent_i(q), ld_agent_i(q + 1), ld_agent_i(q + 2), ld_agent_i(q + 3));
+}
+
+__device__ __forceinline__ void st_queue4(int4* p, int32_t x, int32_t y, int32_t z, int32_t w) {
+  int32_t* q = reinterpret_cast<int32_t*>(p);
+  st_agent_i(q, x);
+  st_agent_i(q + 1, y);
+  st_agent_i(q + 2, z);
+  st_agent_i(q + 3, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -313,7 +329,7 @@ __device__ __forceinline__ void wave_push(bool pred, int32_t val, int32_t* q, ui
   base = __shfl(base, leader, kWave);
   if (pred) {
     const uint32_t pos = base + lanes_below(b);
-    if (pos < cap) q[pos] = val;
+    if (pos < cap) st_agent_i(&q[pos], val);
     else atomicOr(overflow, 1u);
   }
 }
@@ -321,63 +337,94 @@ __device__ __forceinline__ void wave_push(bool pred, int32_t val, int32_t* q, ui
 // ---------------------------------------------------------------------------
 // grid barrier for persistent launches
 //
-// Arrivals increment one monotone counter; a block waits until the counter
-// reaches base + epoch * nblocks (`base` = the counter's value when the launch
-// started, so the counter is never reset while a block may still be waiting).  Release/acquire fences at agent scope make every
-// write before the barrier visible to every read after it, across the L2s of
-// all XCDs.  The wait is bounded by wall-clock time (s_memrealtime runs at
-// 100 MHz): past the bound the block raises `abort` and every block leaves, so
-// the kernel always terminates.  The bound (`ticks`, tuning field barrier_ms)
-// is a kernel argument; 0 gives up at the first wait that is not already
-// satisfied, which lets a test force the failure path from the host.
+// Everything that one workgroup writes and another reads across the barrier is
+// written through to memory: with agent-scope stores and atomics, never with a
+// plain store.  So a workgroup's arrival only has to wait until its own memory
+// operations have completed; the agent-scope release that plain stores would
+// need writes back the XCD's whole L2 for every workgroup of the grid.  After
+// the barrier one invalidation per workgroup (the agent-scope acquire) drops
+// stale lines, so plain loads then see every write from before it.
+//
+// Arrivals go to a slot per workgroup (plain traffic, no serialised adds on one
+// address); workgroup 0 polls the slots, a lane each, and releases the others
+// through one word.  Measured alone, 256 workgroups of 1024 threads: 3.3 us per
+// barrier, 3.5 with a line written by each thread in between; with arrivals
+// added up in one word and a release fence 7.6 and 10.4 us, and 5.5 and 5.7
+// without the fence.
+//
+// Epochs count up from `base` (never reset while a workgroup may wait).  The
+// wait is bounded by wall-clock time (s_memrealtime runs at 100 MHz): past the
+// bound the workgroup raises `abort` and every workgroup leaves, so the kernel
+// always terminates.  The bound (`ticks`, tuning field barrier_ms) is a kernel
+// argument; 0 gives up at the first wait that is not already satisfied, which
+// lets a test force the failure path from the host.
 // ---------------------------------------------------------------------------
 constexpr unsigned long long kTicksPerMs = 100000ull;  // s_memrealtime: 100 MHz
 
-__device__ __forceinline__ bool grid_sync(uint32_t* bar, uint32_t* abort_flag, uint32_t nblocks,
+// This wavefront's memory operations have completed (write-through stores and
+// atomics are then visible to the whole device).
+__device__ __forceinline__ void wait_own_stores() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+}
+
+__device__ __forceinline__ bool grid_wait(const uint32_t* word, uint32_t target,
+                                          uint32_t* abort_flag, unsigned long long t0,
+                                          unsigned long long ticks) {
+  for (uint32_t it = 0;; it++) {
+    if ((int32_t)(ld_agent(word) - target) >= 0) return true;
+    if ((it & 7u) == 7u && ld_agent(abort_flag)) return false;
+    if (__builtin_amdgcn_s_memrealtime() - t0 > ticks) {
+      st_agent(abort_flag, 1u);
+      return false;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
+__device__ __forceinline__ bool grid_sync(GridBar* bar, uint32_t* abort_flag, uint32_t nblocks,
                                           uint32_t base, uint32_t& epoch,
                                           unsigned long long ticks) {
   __shared__ int s_ok;
+  wait_own_stores();
+  if (threadIdx.x == 0) s_ok = 1;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    epoch += 1;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t target = base + epoch * nblocks;
-    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    int ok = 1;
-    // every poll of the barrier word is a memory-side load that queues with
-    // the arrivals on that address: poll every few hundred cycles and check
-    // the abort flag only every 8th time (measured: a barrier of 256
-    // workgroups takes 7.7 us instead of 19)
-    for (uint32_t it = 0;; it++) {
-      const uint32_t cur = ld_agent(bar);
-      if ((int32_t)(cur - target) >= 0) break;
-      if ((it & 7u) == 7u && ld_agent(abort_flag)) { ok = 0; break; }
-      if (__builtin_amdgcn_s_memrealtime() - t0 > ticks) {
-        st_agent(abort_flag, 1u);
-        ok = 0;
+  epoch += 1;
+  const uint32_t target = base + epoch;
+  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+  if (blockIdx.x == 0) {
+    for (uint32_t b = 1 + threadIdx.x; b < nblocks; b += blockDim.x)
+      if (!grid_wait(&bar->slot[b], target, abort_flag, t0, ticks)) {
+        s_ok = 0;
         break;
       }
-      __builtin_amdgcn_s_sleep(4);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      if (s_ok) st_agent(&bar->release.v, target);
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
+  } else if (threadIdx.x == 0) {
+    st_agent(&bar->slot[blockIdx.x], target);
+    if (!grid_wait(&bar->release.v, target, abort_flag, t0, ticks)) s_ok = 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    s_ok = ok;
   }
   __syncthreads();
   return s_ok != 0;
 }
 
 // Last-block detection for step launches: returns true in every thread of
-// the workgroup that arrives last, once all other workgroups' writes are
-// visible to it, and leaves the arrival word at zero for the next launch.
-// Every thread must call it.  (Arrivals in two levels, over striped words,
-// measured no faster: a step's workgroups do not finish all at once.)
+// the workgroup that arrives last, once all other workgroups' write-through
+// stores and atomics are visible to it, and leaves the arrival word at zero
+// for the next launch.  (Plain stores are not: the kernel's end writes those
+// back for the next launch.)  Every thread must call it.  (Arrivals in two
+// levels, over striped words, measured no faster: a step's workgroups do not
+// finish all at once.)
 __device__ __forceinline__ bool last_block_arrive(LineU32* arrive) {
   __shared__ int s_last;
+  wait_own_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     int last = 0;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     if (__hip_atomic_fetch_add(&arrive->v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
         gridDim.x - 1) {
       st_agent(&arrive->v, 0u);

@@ -277,7 +277,7 @@ __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U]
       // unit weights: every candidate of a step is the same level (the
       // frontier holds exactly the vertices of the previous level), so the
       // writers agree and a plain store will do
-      if constexpr (WT == kWUNIT) A.dist[v[i]] = cand[i];
+      if constexpr (WT == kWUNIT) st_agent(&A.dist[v[i]], cand[i]);
       else atomicMin(&A.dist[v[i]], cand[i]);  // result unused: not waited for
     }
   }
@@ -309,7 +309,8 @@ __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U]
       for (uint32_t c = 0; c < nch; c++) {
         const int32_t off = (int32_t)c * A.t_chunk;
         if (base + c < A.cap_wg)
-          A.qwg[nxt][base + c] = make_int4(v[i], start[i] + off, min(A.t_chunk, deg[i] - off), c == 0);
+          st_queue4(&A.qwg[nxt][base + c], v[i], start[i] + off, min(A.t_chunk, deg[i] - off),
+                    c == 0);
         else
           atomicOr(&C->overflow, 1u);
       }
@@ -543,7 +544,7 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
       if (lane < bw && wi < nwords) {
         const uint32_t word = ld_agent(&A.bm[cur][wi]);
         if (word) {
-          A.bm[cur][wi] = 0u;
+          st_agent(&A.bm[cur][wi], 0u);
           bits = word & ~A.hv[wi];
         }
       }
@@ -584,7 +585,7 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
   __syncthreads();
   for (uint32_t j = threadIdx.x; j < n_w; j += blockDim.x) {
     const uint32_t p = sh.gbase_w + j;
-    if (p < A.cap_v) A.qwave[nxt][p] = sh.qw[j];
+    if (p < A.cap_v) st_agent_i(&A.qwave[nxt][p], sh.qw[j]);
     else atomicOr(&C->overflow, 1u);
   }
   return pull;
@@ -616,7 +617,7 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A) {
   for (;;) {
     if (blockIdx.x == 0 && threadIdx.x == 0) ss_zero_rotation(C, step);
     ss_step<WT, false>(A, step, blockIdx.x, gridDim.x, acc, sh, counts);
-    if (!grid_sync(&C->bar.v, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
+    if (!grid_sync(&C->bar, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
       status = -2;
       break;
     }
@@ -635,7 +636,7 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A) {
     st_agent(&C->step, step);
     st_agent_i(&C->converged, status);
     st_agent(&C->done, 1u);
-    st_agent(&C->bar_base, bar_base + epoch * gridDim.x);
+    st_agent(&C->bar_base, bar_base + epoch);
   }
 }
 
@@ -1435,7 +1436,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   }
   {
     const Residency r = residency_of(ss_persistent_kernel<WT>, threads);
-    int grid = r.grid;
+    int grid = std::min(r.grid, kMaxGrid);
     if (T.grid > 0 && T.grid < grid) grid = T.grid;
     if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
     SsArgs a = A;

@@ -183,7 +183,7 @@ __device__ __forceinline__ void compact_flush(const TileArgs& A, int q, int rc,
     int32_t* gq = t == 0 ? A.qgrp[q] : A.qwave[q];
     const uint32_t c = sh.cnt[t], b = sh.base[t];
     for (uint32_t j = threadIdx.x; j < c; j += blockDim.x) {
-      if (b + j < A.cap_v) gq[b + j] = sh.q[t][j];
+      if (b + j < A.cap_v) st_agent_i(&gq[b + j], sh.q[t][j]);
       else atomicOr(&C->overflow, 1u);
     }
   }
@@ -241,7 +241,7 @@ __device__ __forceinline__ void tile_compact(const TileArgs& A, uint32_t step, u
         unsigned long long* vp = A.vis + v * nseg;
 #pragma unroll
         for (int s = 0; s < kSegMax; s++)
-          if (s < nseg && xs[s]) vp[s] |= xs[s];
+          if (s < nseg && xs[s]) st_agent64(&vp[s], vp[s] | xs[s]);
         if (!first) {
           for (uint32_t bits = step; bits; bits &= bits - 1u) {
             unsigned long long* pp = A.planes + (size_t)(__ffs(bits) - 1) * pn + v * nseg;
@@ -257,7 +257,7 @@ __device__ __forceinline__ void tile_compact(const TileArgs& A, uint32_t step, u
       start = A.rowptr[v];
       deg = A.rowptr[v + 1] - start;
       if (deg == 0)  // nothing to expand: the row never enters a queue
-        for (int s = 0; s < nseg; s++) mp[s] = 0ull;
+        for (int s = 0; s < nseg; s++) st_agent64(&mp[s], 0ull);
       else {
         acc.fe += 1;        // frontier rows
         acc.sa += pairs;    // frontier (row, source) pairs
@@ -297,7 +297,7 @@ __device__ __forceinline__ void tile_compact(const TileArgs& A, uint32_t step, u
       const int32_t off = (int32_t)c * A.t_chunk;
       const uint32_t p = chbase + loc + c;
       if (p < A.cap_wg)
-        A.qwg[q][p] = make_int4((int32_t)v, start + off, min(A.t_chunk, deg - off), c == 0);
+        st_queue4(&A.qwg[q][p], (int32_t)v, start + off, min(A.t_chunk, deg - off), c == 0);
       else
         atomicOr(&C->overflow, 1u);
     }
@@ -637,11 +637,10 @@ __device__ __forceinline__ void tile_clear_prev(const TileArgs& A, uint32_t step
       }
       if (first) {
         unsigned long long* mp = A.mk[qp] + (size_t)u * nseg;
-        for (int s = 0; s < nseg; s++) mp[s] = 0ull;
+        for (int s = 0; s < nseg; s++) st_agent64(&mp[s], 0ull);
       }
     }
   }
-
 }
 
 template <bool F32>
@@ -791,13 +790,13 @@ __global__ void __launch_bounds__(1024) tile_persistent_kernel(TileArgs A, int32
   for (;;) {
     if (blockIdx.x == 0) tile_prologue(C, step, A.K);
     tile_compact<false>(A, step, blockIdx.x, gridDim.x, acc, csh);
-    if (!grid_sync(&C->bar.v, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
+    if (!grid_sync(&C->bar, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
       status = -2;
       finished = true;
       break;
     }
     tile_relax<F32>(A, step, blockIdx.x, gridDim.x, sh_colact);
-    if (!grid_sync(&C->bar.v, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
+    if (!grid_sync(&C->bar, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
       status = -2;
       finished = true;
       break;
@@ -813,7 +812,7 @@ __global__ void __launch_bounds__(1024) tile_persistent_kernel(TileArgs A, int32
   flush_acc(acc, &S.fe, &S.es, &S.im, &S.sa, &S.se);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st_agent(&C->step, step);
-    st_agent(&C->bar_base, bar_base + epoch * gridDim.x);
+    st_agent(&C->bar_base, bar_base + epoch);
     if (finished) {
       st_agent_i(&C->converged, status);
       st_agent(&C->done, 1u);
@@ -1238,12 +1237,12 @@ __global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A) {
   for (;;) {
     if (blockIdx.x == 0) tile_prologue(C, step, A.K);
     tile_compact<true>(A, step, blockIdx.x, gridDim.x, acc, csh);
-    if (!grid_sync(&C->bar.v, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
+    if (!grid_sync(&C->bar, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
       status = -2;
       break;
     }
     utile_push_step<S>(A, step, blockIdx.x, gridDim.x, sh_colact);
-    if (!grid_sync(&C->bar.v, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
+    if (!grid_sync(&C->bar, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
       status = -2;
       break;
     }
@@ -1256,7 +1255,7 @@ __global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A) {
   flush_acc(acc, &Sx.fe, &Sx.es, &Sx.im, &Sx.sa, &Sx.se);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st_agent(&C->step, step);
-    st_agent(&C->bar_base, bar_base + epoch * gridDim.x);
+    st_agent(&C->bar_base, bar_base + epoch);
     st_agent_i(&C->converged, status);
     st_agent(&C->done, 1u);
   }
@@ -1633,7 +1632,7 @@ dawn_status utile_persistent(const TileArgs& a, hipStream_t stream) {
   const int threads = T.wg_threads > 0 ? T.wg_threads : kTilePersistentThreads;
   auto k = a.nseg <= 1 ? utile_persistent_kernel<1> : a.nseg <= 2 ? utile_persistent_kernel<2>
          : a.nseg <= 4 ? utile_persistent_kernel<4> : utile_persistent_kernel<8>;
-  int grid = residency_of(k, threads).grid;
+  int grid = std::min(residency_of(k, threads).grid, kMaxGrid);
   if (T.grid > 0 && T.grid < grid) grid = T.grid;
   void* tk = ktimer_begin(stream);
   const hipError_t e = launch_persistent(k, grid, threads, stream, a);
@@ -1649,7 +1648,7 @@ static dawn_status tile_steps_t(const TileArgs& a, bool persistent, int32_t max_
   const int32_t cap_n = persistent ? 1 : 0;
   if (persistent) {
     const int pthreads = T.wg_threads > 0 ? T.wg_threads : kTilePersistentThreads;
-    int grid = residency_of(tile_persistent_kernel<F32>, pthreads).grid;
+    int grid = std::min(residency_of(tile_persistent_kernel<F32>, pthreads).grid, kMaxGrid);
     if (T.grid > 0 && T.grid < grid) grid = T.grid;
     TileArgs aa = a;
     aa.pull_min = -1;  // pull steps need the step-launch path
