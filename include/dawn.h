@@ -106,7 +106,10 @@ typedef enum { DAWN_W_U32 = 0, DAWN_W_F32 = 1, DAWN_W_I32 = 2, DAWN_W_UNIT = 3 }
  *                    previous step and having out-edges);
  *   edges_scanned    sum over steps of the out-degrees of the rows expanded
  *                    (single source with ss_skip: a row lowered again within
- *                    its step is expanded, and counted, in the next step only);
+ *                    its step is expanded, and counted, in the next step only;
+ *                    single-source and batch runs with uint32 or fp32 weights
+ *                    may leave rows far above the frontier's smallest distance
+ *                    for a later step, which then counts them);
  *   improvements     per step, the vertices whose distance the step lowered
  *                    (two decreases of one vertex in one step count once).
  * For a batched call the counters are summed over its sources and `steps` is
@@ -188,7 +191,8 @@ typedef struct {
                            one workgroup, one launch (no grid barrier); default 131072,
                            0 = never */
   int32_t step_min_m;   /* mode 0: graphs with at least this many edges start with step
-                           launches (see mode); default 1 << 25 */
+                           launches (see mode); default INT32_MAX: none do, except
+                           runs with pull steps from 1 << 25 edges on */
   int32_t tile_sparse;  /* tile rows (and workgroup chunks) with at most this many active
                            sources are relaxed one edge per lane, 4 bytes per source,
                            instead of 16 lanes per 64-source segment; 0..512, default 8 */

@@ -37,9 +37,20 @@ struct alignas(128) LineU32 {
 // Grid barrier of persistent launches (grid_sync): a slot per workgroup and the
 // release word, each run's epochs counting up from the control block's bar_base.
 constexpr int kMaxGrid = 2048;  // workgroups of a persistent launch
+struct alignas(128) LineU64 {
+  unsigned long long v;
+};
 struct alignas(128) GridBar {
-  LineU32 release;
-  uint32_t slot[kMaxGrid];
+  LineU64 release;
+  unsigned long long slot[kMaxGrid];
+};
+
+// Deferral of far rows in multi-workgroup single-source runs (NearFar below).
+struct NfState {
+  uint32_t thr;    // key: the step expands frontier rows up to it
+  float delta;     // thr minus the smallest frontier distance, in distance units
+  float floor;     // the smallest delta; 0: no deferral in this run
+  uint32_t big;    // a step has reached nf_work edges
 };
 
 // Counters of a single-source run.  Every workgroup of a step adds to them
@@ -63,8 +74,11 @@ struct alignas(256) SsCtl {
   uint32_t overflow;          // a queue capacity was exceeded (cannot happen on valid input)
   uint32_t bar_base;          // the last barrier epoch of earlier persistent launches
   uint32_t negfloor;          // int32 weights: a path sum fell to or below INT32_MIN
+  NfState nf;                 // of the next step
+  unsigned long long es_seen; // ctr.es before the step (step launches)
   alignas(128) uint32_t upd[kRot];  // [step % 4]: any improvement during the previous step
   LineU32 arrive;             // last-block detection of step launches
+  LineU32 minp[kRot];         // [step % 4]: smallest distance key of the step's frontier (step launches)
   LineU32 cnt[kRot][4];       // [step % 4][tier]: lane, wave, workgroup-chunk records
   SsCounters ctr;
   GridBar bar;
@@ -316,6 +330,18 @@ __device__ __forceinline__ void deal_rows(DealRows<WIN>& st, int32_t start, int3
   }
 }
 
+// Minimum over the 64 lanes of a wavefront (the same in every lane).
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) {
+  const int none = -1;
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)x, 0x111, 0xF, 0xF, false));
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)x, 0x112, 0xF, 0xF, false));
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)x, 0x114, 0xF, 0xF, false));
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)x, 0x118, 0xF, 0xF, false));
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)x, 0x142, 0xA, 0xF, false));
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)x, 0x143, 0xC, 0xF, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+
 // Append `val` for every lane with `pred` set: one atomic per wavefront
 // reserves the range, each lane writes at base + (number of lanes below it).
 // Must be reached by the whole wavefront.
@@ -368,11 +394,16 @@ __device__ __forceinline__ void wait_own_stores() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 }
 
-__device__ __forceinline__ bool grid_wait(const uint32_t* word, uint32_t target,
+// Waits until the epoch in a 64-bit barrier word (its low 32 bits, from bit
+// SHIFT up) has reached `target`; `word` returns the word.
+template <int SHIFT>
+__device__ __forceinline__ bool grid_wait(const unsigned long long* p, uint32_t target,
                                           uint32_t* abort_flag, unsigned long long t0,
-                                          unsigned long long ticks) {
+                                          unsigned long long ticks, unsigned long long& word) {
   for (uint32_t it = 0;; it++) {
-    if ((int32_t)(ld_agent(word) - target) >= 0) return true;
+    word = ld_agent64(p);
+    const uint32_t at = (uint32_t)word & ~((1u << SHIFT) - 1u);
+    if ((int32_t)(at - (target << SHIFT)) >= 0) return true;
     if ((it & 7u) == 7u && ld_agent(abort_flag)) return false;
     if (__builtin_amdgcn_s_memrealtime() - t0 > ticks) {
       st_agent(abort_flag, 1u);
@@ -392,20 +423,21 @@ __device__ __forceinline__ bool grid_sync(GridBar* bar, uint32_t* abort_flag, ui
   epoch += 1;
   const uint32_t target = base + epoch;
   const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+  unsigned long long word;
   if (blockIdx.x == 0) {
     for (uint32_t b = 1 + threadIdx.x; b < nblocks; b += blockDim.x)
-      if (!grid_wait(&bar->slot[b], target, abort_flag, t0, ticks)) {
+      if (!grid_wait<0>(&bar->slot[b], target, abort_flag, t0, ticks, word)) {
         s_ok = 0;
         break;
       }
     __syncthreads();
     if (threadIdx.x == 0) {
-      if (s_ok) st_agent(&bar->release.v, target);
+      if (s_ok) st_agent64(&bar->release.v, target);
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
   } else if (threadIdx.x == 0) {
-    st_agent(&bar->slot[blockIdx.x], target);
-    if (!grid_wait(&bar->release.v, target, abort_flag, t0, ticks)) s_ok = 0;
+    st_agent64(&bar->slot[blockIdx.x], target);
+    if (!grid_wait<0>(&bar->release.v, target, abort_flag, t0, ticks, word)) s_ok = 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
   __syncthreads();
@@ -534,6 +566,7 @@ struct SsArgs {
   int32_t skip;           // skip expanding a row already lowered again in this step
   TGraph T;               // reverse graph for pull steps, or hdr == nullptr
   long long pull_min;     // pull when the frontier has >= this many out-edges; < 0: never
+  bool counted;           // the step launches before have counted the frontier they left
   int32_t t_lane, t_wave, t_chunk;
   int32_t* qlane[2];      // delta of one-workgroup runs [step % 2]
   int32_t* qwave[2];      // delta, wave tier

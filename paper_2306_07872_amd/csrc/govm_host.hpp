@@ -26,7 +26,7 @@ struct Tuning {
   int32_t tile_t_group = 8;
   int32_t tile_skip = 0;
   int32_t small_m = 131072;
-  int32_t step_min_m = 1 << 25;
+  int32_t step_min_m = INT32_MAX;
   int32_t tile_sparse = 8;
   int32_t tile_pull = 400;
   int32_t tile_pull_src = 16;

@@ -21,6 +21,8 @@
 //   right next-step queue (wavefront ballot + mbcnt prefix, gathered per
 //   workgroup in LDS, one atomicAdd per tier and workgroup).  The scan clears
 //   the bitmap of the current step, n/32 words per step.
+// - Rows far above the frontier's smallest distance may be left in the frontier
+//   for a later step (see "deferral of far rows").
 // - The relaxation reads alpha[v] with a plain load first (a stale value can
 //   only be higher, so skipping on it is safe) and uses atomicMin only when
 //   the candidate is smaller.  Order of updates inside a step does not matter:
@@ -38,6 +40,114 @@
 namespace dawn {
 
 // ---------------------------------------------------------------------------
+// deferral of far rows
+//
+// A frontier row whose distance lies far above the smallest one is likely to be
+// lowered again before its turn comes; expanding it now is work done twice.  On
+// a 2048 x 2048 grid with fp32 weights every vertex used to be expanded 72
+// times, on an ER graph 2.8 times.  So a step expands the frontier rows up to
+// thr = M + delta (M: the smallest distance in the frontier) and leaves the
+// others in the frontier.  The fixed point does not depend on the order
+// (distances are unique), and a row at M is always expanded.  With weights >= 0
+// no later path can lower it, so every step settles a vertex and at most n
+// steps are taken, as without deferral.  At unit weights all frontier rows have
+// one distance and nothing is ever deferred.
+//
+// delta starts at nf_delta mean weights.  A step of more than nf_work edges
+// keeps the chip busy: delta is halved, down to where it started.  A step of
+// less than half as many costs little beyond its barrier: delta grows by a
+// tenth, and doubles once there has been a busy step (the tail of a run).
+// Rows are deferred only where degrees are even (grids, ER): on skewed graphs
+// (R-MAT) the rows that matter are reached in few steps whose distances lie
+// close together, and deferral only adds steps (a CPU model of R-MAT scale 18
+// with lognormal weights: 15 steps instead of 12 for 1 % less work).  Measured:
+// 2048 x 2048 grid 73.8 -> 38 ms (1187M -> 66M edges expanded), 64 ER graphs in
+// one launch 11.8 -> 6.0 ms, together with the scan's order and kFresh below.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;  // above every distance that a row can have
+constexpr float kNfDelta = 1.2f;
+constexpr float kNfWork = 30000.f;
+constexpr int kNfSamples = 4096;
+
+template <int WT>
+__device__ __forceinline__ constexpr bool nf_weights() {
+  return WT == kWU32 || WT == kWF32;
+}
+
+// M + delta as a key, at least M (and not 0, which says "no frontier").
+template <int WT>
+__device__ __forceinline__ uint32_t nf_threshold(uint32_t M, float delta) {
+  if constexpr (WT == kWF32) {
+    const uint32_t t = __float_as_uint(__uint_as_float(M) + delta);
+    return t > M ? t : M + 1u;
+  } else {
+    const uint32_t d = delta >= 4.0e9f ? kNoKey : delta < 1.f ? 1u : (uint32_t)delta;
+    const uint32_t t = M + d;
+    return t < M ? kNoKey : t;
+  }
+}
+
+// The next step's threshold, from the frontier's smallest key and the edges of
+// the step that ended.
+template <int WT>
+__device__ __forceinline__ void nf_advance(NfState& s, uint32_t M, float work) {
+  if (!nf_weights<WT>() || s.floor == 0.f) return;
+  if (work > kNfWork) {
+    s.delta = fmaxf(0.5f * s.delta, s.floor);
+    s.big = 1u;
+  } else if (work < 0.5f * kNfWork && s.delta < 1e30f) {
+    s.delta *= s.big ? 2.f : 1.1f;
+  }
+  s.thr = nf_threshold<WT>(M, s.delta);
+}
+
+// Samples of the weights (their mean) and of the row lengths (deferral only
+// where the mean length of an edge's row is at most four times the mean length
+// of a row).  One workgroup; the control block is zero before it.
+template <int WT>
+__device__ void nf_init(SsCtl* ctl, int64_t n, int64_t m, const int32_t* rowptr,
+                        const uint32_t* w) {
+  if (threadIdx.x == 0) ctl->nf.thr = kNoKey;
+  if (!nf_weights<WT>() || !rowptr || !w || m < 1) return;
+  __shared__ float part[3][kMaxWavesPerBlock];
+  float sw = 0.f, sd = 0.f, sd2 = 0.f;
+  const int64_t ew = m > kNfSamples ? m / kNfSamples : 1, rw = n > kNfSamples ? n / kNfSamples : 1;
+  const int ne = (int)(m < kNfSamples ? m : kNfSamples), nr = (int)(n < kNfSamples ? n : kNfSamples);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < ne; i += blockDim.x)
+    sw += WT == kWF32 ? __uint_as_float(w[i * ew]) : (float)w[i * ew];
+#pragma unroll 4
+  for (int i = threadIdx.x; i < nr; i += blockDim.x) {
+    const float d = (float)(rowptr[i * rw + 1] - rowptr[i * rw]);
+    sd += d;
+    sd2 += d * d;
+  }
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    sw += __shfl_xor(sw, off, kWave);
+    sd += __shfl_xor(sd, off, kWave);
+    sd2 += __shfl_xor(sd2, off, kWave);
+  }
+  const int wv = threadIdx.x / kWave;
+  if (lane_id() == 0) {
+    part[0][wv] = sw;
+    part[1][wv] = sd;
+    part[2][wv] = sd2;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  sw = sd = sd2 = 0.f;
+  for (int i = 0; i < (int)(blockDim.x / kWave); i++) {
+    sw += part[0][i];
+    sd += part[1][i];
+    sd2 += part[2][i];
+  }
+  // sd2 / sd <= 4 * sd / nr
+  if (!(sd2 * nr <= 4.f * sd * sd)) return;
+  ctl->nf.floor = fmaxf(kNfDelta * (sw / ne), 1e-30f);
+  ctl->nf.delta = ctl->nf.floor;
+}
+
+// ---------------------------------------------------------------------------
 // init
 // ---------------------------------------------------------------------------
 // hv (may be null): bit v set when row v has more than t_lane edges, the rows
@@ -45,7 +155,7 @@ namespace dawn {
 template <int WT>
 __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_t* bm1,
                                int64_t nwords, SsCtl* ctl, const int32_t* rowptr, uint32_t* hv,
-                               int32_t t_lane) {
+                               int32_t t_lane, const uint32_t* w, int64_t m) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = tid; i < n; i += stride) dist[i] = inf_key<WT>();
@@ -62,9 +172,15 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
       if ((lane & 31) == 0 && wi < nwords) hv[wi] = (uint32_t)(b >> (lane & 32));
     }
   }
+  // the barrier's slots, then the other control words (one workgroup, which
+  // also takes the run's samples)
+  for (int64_t i = tid; i < kMaxGrid; i += stride) ctl->bar.slot[i] = 0ull;
   if (blockIdx.x == 0) {
     uint32_t* c = reinterpret_cast<uint32_t*>(ctl);
-    for (int i = threadIdx.x; i < (int)(sizeof(SsCtl) / 4); i += blockDim.x) c[i] = 0;
+    for (int i = threadIdx.x; i < (int)(offsetof(SsCtl, bar.slot) / 4); i += blockDim.x) c[i] = 0;
+    __syncthreads();
+    if (threadIdx.x < kRot) ctl->minp[threadIdx.x].v = kNoKey;
+    nf_init<WT>(ctl, n, m, rowptr, w);
   }
 }
 
@@ -222,8 +338,22 @@ __device__ __forceinline__ void scan_rows(ScanRows& st, uint32_t bits, F&& f) {
 struct SsShared {
   DealRows<4096> rows[kMaxWavesPerBlock];  // lane-tier batch
   ScanRows scan[kMaxWavesPerBlock];        // bitmap block
+  uint32_t def[kMaxWavesPerBlock][kWave];  // deferred rows, by word of the block
   int32_t qw[kLdsQWave];
   uint32_t nqw, upd, gbase_w;
+  uint32_t minp, work, heavy;  // smallest key left in the frontier, edges expanded, rows queued
+};
+
+// How a step treats its frontier: kAll, every row is expanded; kNear, rows above
+// the threshold are left in the frontier; kFresh, as kNear, for steps of few
+// edges whose launch has not dropped stale cache lines (the targets' distances
+// are read at agent scope).
+constexpr int kAll = 0, kNear = 1, kFresh = 2;
+
+// What a lane has seen of a step: the smallest key that it put or left in the
+// next frontier, and the edges of the rows that it held.
+struct StepSeen {
+  uint32_t minp = kNoKey, work = 0u;
 };
 
 // Push `v` for lanes with `pred` into the workgroup's LDS queue; lanes past
@@ -243,33 +373,78 @@ __device__ __forceinline__ void block_push(bool pred, int32_t v, int32_t* sq, ui
   wave_push(spill, v, gq, gcnt, gcap, overflow);
 }
 
+// Lanes with `pred` append row v (edges [start, start + deg), deg > t_lane) to
+// the next step's queue of its tier.  Reached by the whole wavefront.
+__device__ __forceinline__ void ss_queue_row(const SsArgs& A, bool pred, int32_t v, int32_t start,
+                                             int32_t deg, int nxt, int rn, SsShared& sh) {
+  SsCtl* C = A.ctl;
+  if (__ballot(pred) == 0ull) return;
+  block_push(pred && deg <= A.t_wave, v, sh.qw, &sh.nqw, kLdsQWave, A.qwave[nxt],
+             &C->cnt[rn][1].v, A.cap_v, &C->overflow);
+  if (pred) sh.heavy = 1u;
+  if (pred && deg > A.t_wave) {
+    const uint32_t nch = (uint32_t)((deg + A.t_chunk - 1) / A.t_chunk);
+    const uint32_t base = atomicAdd(&C->cnt[rn][2].v, nch);
+    for (uint32_t c = 0; c < nch; c++) {
+      const int32_t off = (int32_t)c * A.t_chunk;
+      if (base + c < A.cap_wg)
+        st_queue4(&A.qwg[nxt][base + c], v, start + off, min(A.t_chunk, deg - off), c == 0);
+      else
+        atomicOr(&C->overflow, 1u);
+    }
+  }
+}
+
 // Record improvements of alpha[v[i]] (lanes with imp[i]): the ptr flag, the
 // beta bitmap, and for the first setter of a bit whose row has more than
 // t_lane edges, the next-step queue of its degree tier (shorter rows are found
-// by the next step's bitmap scan).  Reached by the whole wavefront.  CNT: also
-// count the next frontier's rows and out-edges (the pull decision of the next
-// step).
-template <int WT, int U, bool CNT>
+// by the next step's bitmap scan).  kFresh: hvw holds the targets' long-row words.
+// Reached by the whole wavefront.  CNT: also count the vertices lowered (else
+// the next step's scan does) and the next frontier's rows and out-edges (the
+// pull decision of the next step).
+template <int WT, int U, bool CNT, int MODE>
 __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U],
                                            const int32_t (&v)[U], const uint32_t (&cand)[U],
-                                           int nxt, int rn, Acc& acc, SsShared& sh) {
+                                           const uint32_t (&hvw)[U], int nxt, int rn, Acc& acc,
+                                           SsShared& sh, StepSeen& seen) {
   bool any = false;
 #pragma unroll
-  for (int i = 0; i < U; i++) any |= imp[i];
+  for (int i = 0; i < U; i++) {
+    any |= imp[i];
+    if (MODE != kAll && imp[i]) seen.minp = min(seen.minp, cand[i]);
+  }
   if (__ballot(any) == 0) return;
   SsCtl* C = A.ctl;
   if (any) sh.upd = 1u;
-  bool newv[U];
-  uint32_t hvw[U];  // heavy-row words, loaded beside the test-and-set
+  bool newv[U];  // first setters that have to queue the row (CNT: all first setters)
 #pragma unroll
-  for (int i = 0; i < U; i++) hvw[i] = imp[i] && !CNT ? A.hv[v[i] >> 5] : 0u;
+  for (int i = 0; i < U; i++) newv[i] = false;
+  if constexpr (MODE == kFresh) {
+    // the long-row words are there: a short row needs no answer, and the
+    // atomic is not waited for
 #pragma unroll
-  for (int i = 0; i < U; i++) {
-    newv[i] = false;
-    if (imp[i]) {
-      const uint32_t bit = 1u << (v[i] & 31);
-      newv[i] = (atomicOr(&A.bm[nxt][v[i] >> 5], bit) & bit) == 0u;
+    for (int i = 0; i < U; i++) {
+      if (imp[i]) {
+        uint32_t* word = &A.bm[nxt][v[i] >> 5];
+        const uint32_t bit = 1u << (v[i] & 31);
+        if (hvw[i] & bit) newv[i] = (atomicOr(word, bit) & bit) == 0u;
+        else atomicOr(word, bit);
+      }
     }
+  } else {
+    // the long-row words of the few improved targets, loaded beside the test-and-set
+    uint32_t hw[U];
+#pragma unroll
+    for (int i = 0; i < U; i++) hw[i] = imp[i] && !CNT ? A.hv[v[i] >> 5] : ~0u;
+#pragma unroll
+    for (int i = 0; i < U; i++) {
+      if (imp[i]) {
+        const uint32_t bit = 1u << (v[i] & 31);
+        newv[i] = (atomicOr(&A.bm[nxt][v[i] >> 5], bit) & bit) == 0u;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < U; i++) newv[i] = newv[i] && ((hw[i] >> (v[i] & 31)) & 1u);
   }
 #pragma unroll
   for (int i = 0; i < U; i++) {
@@ -281,15 +456,17 @@ __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U]
       else atomicMin(&A.dist[v[i]], cand[i]);  // result unused: not waited for
     }
   }
+  if (CNT) {
 #pragma unroll
-  for (int i = 0; i < U; i++)
-    if (newv[i]) acc.im += 1;  // a vertex lowered in this step counts once
+    for (int i = 0; i < U; i++)
+      if (newv[i]) acc.im += 1;  // a vertex lowered in this step counts once
+  }
   int32_t start[U], deg[U];
 #pragma unroll
   for (int i = 0; i < U; i++) {
     start[i] = 0;
     deg[i] = 0;
-    if (newv[i] && (CNT || ((hvw[i] >> (v[i] & 31)) & 1u))) {
+    if (newv[i]) {
       start[i] = A.rowptr[v[i]];
       deg[i] = A.rowptr[v[i] + 1] - start[i];
       if (CNT && deg[i] > 0) {
@@ -299,23 +476,8 @@ __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U]
     }
   }
 #pragma unroll
-  for (int i = 0; i < U; i++) {
-    const bool tw = newv[i] && deg[i] > A.t_lane && deg[i] <= A.t_wave;
-    block_push(tw, v[i], sh.qw, &sh.nqw, kLdsQWave, A.qwave[nxt], &C->cnt[rn][1].v, A.cap_v,
-               &C->overflow);
-    if (newv[i] && deg[i] > A.t_wave) {
-      const uint32_t nch = (uint32_t)((deg[i] + A.t_chunk - 1) / A.t_chunk);
-      const uint32_t base = atomicAdd(&C->cnt[rn][2].v, nch);
-      for (uint32_t c = 0; c < nch; c++) {
-        const int32_t off = (int32_t)c * A.t_chunk;
-        if (base + c < A.cap_wg)
-          st_queue4(&A.qwg[nxt][base + c], v[i], start[i] + off, min(A.t_chunk, deg[i] - off),
-                    c == 0);
-        else
-          atomicOr(&C->overflow, 1u);
-      }
-    }
-  }
+  for (int i = 0; i < U; i++)
+    ss_queue_row(A, newv[i] && deg[i] > A.t_lane, v[i], start[i], deg[i], nxt, rn, sh);
 }
 
 // Relax U edges per lane: all column/weight loads, then all target-distance
@@ -351,12 +513,13 @@ __device__ __forceinline__ void ss_relax_n(const SsArgs& A, const int32_t (&e)[U
 // so waiting for the test-and-set does not wait for the atomicMin too (gfx9's
 // vector-memory counter retires in order).  A candidate that passes the
 // pre-check but loses to a lower value written in the same step only sets a
-// bit that the writer of that value sets as well.
-template <int WT, int U>
+// bit that the writer of that value sets as well.  kFresh: read the targets'
+// distances at agent scope (no cache line from before the step may serve them).
+template <int WT, int U, int MODE>
 __device__ __forceinline__ void ss_relax_pre(const SsArgs& A, const int32_t (&e)[U],
                                              const bool (&valid)[U], const uint32_t (&du)[U],
                                              bool (&imp)[U], int32_t (&v)[U],
-                                             uint32_t (&cand)[U]) {
+                                             uint32_t (&cand)[U], uint32_t (&hvw)[U]) {
 #pragma unroll
   for (int i = 0; i < U; i++) {
     v[i] = 0;
@@ -369,8 +532,16 @@ __device__ __forceinline__ void ss_relax_pre(const SsArgs& A, const int32_t (&e)
     }
   }
   uint32_t cur[U];
+  if constexpr (MODE == kFresh) {
+    // the long-row words are loaded beside the distances
 #pragma unroll
-  for (int i = 0; i < U; i++) cur[i] = valid[i] ? A.dist[v[i]] : 0u;
+    for (int i = 0; i < U; i++) hvw[i] = valid[i] ? A.hv[v[i] >> 5] : 0u;
+#pragma unroll
+    for (int i = 0; i < U; i++) cur[i] = valid[i] ? ld_agent(&A.dist[v[i]]) : 0u;
+  } else {
+#pragma unroll
+    for (int i = 0; i < U; i++) cur[i] = valid[i] ? A.dist[v[i]] : 0u;
+  }
 #pragma unroll
   for (int i = 0; i < U; i++) imp[i] = valid[i] && cand[i] < cur[i] && v[i] != A.src;
 }
@@ -392,9 +563,10 @@ __device__ __forceinline__ uint32_t row16_min(uint32_t x) {
 // atomicMin per edge, one per improved target (a target whose in-edges span
 // several chunks may be improved from each).  The current bitmap is read
 // throughout and not cleared here (the step's last workgroup clears it).
-template <int WT>
+template <int WT, int MODE>
 __device__ __forceinline__ void ss_pull(const SsArgs& A, int cur, int nxt, int rn, uint32_t gw,
-                                        uint32_t nwv, Acc& acc, SsShared& sh) {
+                                        uint32_t nwv, Acc& acc, SsShared& sh,
+                                        StepSeen& seen) {
   const int lane = lane_id(), g = lane >> 4, j16 = lane & 15;
   const uint32_t nch = (uint32_t)min((long long)A.T.hdr->nchunks, (long long)A.T.cap_chunks);
   const uint32_t* fb = A.bm[cur];
@@ -420,8 +592,8 @@ __device__ __forceinline__ void ss_pull(const SsArgs& A, int cur, int nxt, int r
     best = row16_min(best);
     bool imp[1] = {cok && j16 == 0 && v != A.src && best < A.dist[v]};
     const int32_t vv[1] = {v};
-    const uint32_t cc[1] = {best};
-    ss_enqueue<WT, 1, true>(A, imp, vv, cc, nxt, rn, acc, sh);
+    const uint32_t cc[1] = {best}, hvw[1] = {0u};
+    ss_enqueue<WT, 1, true, MODE>(A, imp, vv, cc, hvw, nxt, rn, acc, sh, seen);
   }
 }
 
@@ -433,7 +605,28 @@ __device__ __forceinline__ bool ss_skip_row(const SsArgs& A, int nxt, int32_t u)
   return A.skip && ((ld_agent(&A.bm[nxt][u >> 5]) >> (u & 31)) & 1u);
 }
 
+// Leave row u (one of the queued tiers) in the frontier: its next bit, and for
+// its first setter the next queue.  Reached by the whole wavefront.
+__device__ __forceinline__ void ss_defer_row(const SsArgs& A, bool lead, int32_t u, uint32_t du,
+                                             int nxt, int rn, Acc& acc, SsShared& sh,
+                                             StepSeen& seen) {
+  bool first = false;
+  int32_t start = 0, deg = 0;
+  if (lead) {
+    const uint32_t bit = 1u << (u & 31);
+    first = (atomicOr(&A.bm[nxt][u >> 5], bit) & bit) == 0u;
+    seen.minp = min(seen.minp, du);
+    sh.upd = 1u;
+    acc.im -= first ? 1ull : 0ull;  // counted again by the next scan
+    start = A.rowptr[u];
+    deg = A.rowptr[u + 1] - start;
+  }
+  ss_queue_row(A, first, u, start, deg, nxt, rn, sh);
+}
+
 // Returns true when the step was a pull step.
+// thr: rows above it are left in the frontier (not kAll).  count: the scan counts the frontier's vertices as lowered by
+// the previous step (rows left in the frontier are taken off again).
 // PULL: pull steps may run (step launches with a reverse graph); the push-only
 // instance keeps none of their code.
 // The step's queue counts (lane, wave, workgroup-chunk tiers); read at the
@@ -452,9 +645,11 @@ __device__ __forceinline__ SsCounts ss_counts(const SsArgs& A, uint32_t step) {
   return SsCounts{min(ld_agent(&C->cnt[rc][1].v), A.cap_v), min(ld_agent(&C->cnt[rc][2].v), A.cap_wg)};
 }
 
-template <int WT, bool PULL>
-__device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb, Acc& acc,
-                        SsShared& sh, SsCounts counts) {
+template <int WT, bool PULL, int MODE>
+__device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb, Acc& acc,
+                        SsShared& sh, SsCounts counts, uint32_t thr, bool count) {
+  constexpr bool NF = MODE != kAll;
+  StepSeen seen;
   const int cur = step & 1, nxt = cur ^ 1;
   const int rc = step % kRot, rn = (step + 1) % kRot;
   SsCtl* C = A.ctl;
@@ -465,6 +660,9 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
   if (threadIdx.x == 0) {
     sh.nqw = 0u;
     sh.upd = 0u;
+    sh.minp = kNoKey;
+    sh.work = 0u;
+    sh.heavy = 0u;
   }
   __syncthreads();
   const uint32_t nw = counts.w, ng = counts.g;
@@ -472,24 +670,36 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
                     ld_agent64(&C->ctr.fedges[rc]) >= (unsigned long long)A.pull_min;
   if (pull) {
     if (gb == 0 && threadIdx.x == 0) acc.fe += ld_agent64(&C->ctr.frows[rc]);
-    ss_pull<WT>(A, cur, nxt, rn, gw, nwv, acc, sh);
+    ss_pull<WT, MODE>(A, cur, nxt, rn, gw, nwv, acc, sh, seen);
   } else {
 
     // workgroup tier: one chunk of one row per workgroup
     for (uint32_t i = gb; i < ng; i += nb) {
       const int4 r = ld_queue4(&A.qwg[cur][i]);
       const int32_t u = r.x, start = r.y;
-      const uint32_t du = ld_agent(&A.dist[u]);
-      const int32_t len = ss_skip_row(A, nxt, u) ? 0 : r.z;
+      const uint32_t dul = ld_agent(&A.dist[u]);
+      const bool skipped = ss_skip_row(A, nxt, u);  // (loaded beside the distance)
+      // one value per wavefront (another wavefront may read a lower one; then
+      // the row has been lowered in this step and is queued for the next)
+      const uint32_t du = (uint32_t)__builtin_amdgcn_readfirstlane((int)dul);
+      if (NF && du > thr) {
+        // left in the frontier: whichever chunk of the row sets the next bit
+        // queues the whole row again (a chunk that is expanded meanwhile, with a
+        // value lowered in this step, is expanded once more then)
+        if (wave == 0) ss_defer_row(A, lane == 0, u, du, nxt, rn, acc, sh, seen);
+        continue;
+      }
+      const int32_t len = skipped ? 0 : r.z;
       if (threadIdx.x == 0) {
         acc.es += (unsigned long long)len;
+        if (NF) seen.work += (uint32_t)len;
         if (r.w) acc.fe += 1;
       }
       const int32_t stride = (int32_t)blockDim.x;
       for (int32_t base = 0; base < len; base += stride * kUnroll) {
         int32_t e[kUnroll], v[kUnroll];
         bool ok[kUnroll], imp[kUnroll];
-        uint32_t d[kUnroll], cand[kUnroll];
+        uint32_t d[kUnroll], cand[kUnroll], hvw[kUnroll];
   #pragma unroll
         for (int j = 0; j < kUnroll; j++) {
           const int32_t k = base + j * stride + (int32_t)threadIdx.x;
@@ -497,90 +707,130 @@ __device__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb
           e[j] = start + k;
           d[j] = du;
         }
-        ss_relax_pre<WT, kUnroll>(A, e, ok, d, imp, v, cand);
-        ss_enqueue<WT, kUnroll, PULL>(A, imp, v, cand, nxt, rn, acc, sh);
+        ss_relax_pre<WT, kUnroll, MODE>(A, e, ok, d, imp, v, cand, hvw);
+        ss_enqueue<WT, kUnroll, PULL, MODE>(A, imp, v, cand, hvw, nxt, rn, acc, sh, seen);
       }
     }
 
     // wave tier: one wavefront per row
     for (uint32_t i = gw; i < nw; i += nwv) {
       const int32_t u = ld_queue(&A.qwave[cur][i]);
-      const int32_t start = A.rowptr[u];
-      const int32_t end = ss_skip_row(A, nxt, u) ? start : A.rowptr[u + 1];
-      const uint32_t du = ld_agent(&A.dist[u]);
+      const uint32_t dul = ld_agent(&A.dist[u]);
+      const int32_t start = A.rowptr[u], last = A.rowptr[u + 1];
+      const bool skipped = ss_skip_row(A, nxt, u);
+      const uint32_t du = (uint32_t)__builtin_amdgcn_readfirstlane((int)dul);
+      if (NF && du > thr) {
+        ss_defer_row(A, lane == 0, u, du, nxt, rn, acc, sh, seen);
+        continue;
+      }
+      const int32_t end = skipped ? start : last;
       if (lane == 0) {
         acc.fe += 1;
         acc.es += (unsigned long long)(end - start);
+        if (NF) seen.work += (uint32_t)(end - start);
       }
       for (int32_t base = start; base < end; base += kWave * kUnroll) {
         int32_t e[kUnroll], v[kUnroll];
         bool ok[kUnroll], imp[kUnroll];
-        uint32_t d[kUnroll], cand[kUnroll];
+        uint32_t d[kUnroll], cand[kUnroll], hvw[kUnroll];
   #pragma unroll
         for (int j = 0; j < kUnroll; j++) {
           e[j] = base + j * kWave + lane;
           ok[j] = e[j] < end;
           d[j] = du;
         }
-        ss_relax_pre<WT, kUnroll>(A, e, ok, d, imp, v, cand);
-        ss_enqueue<WT, kUnroll, PULL>(A, imp, v, cand, nxt, rn, acc, sh);
+        ss_relax_pre<WT, kUnroll, MODE>(A, e, ok, d, imp, v, cand, hvw);
+        ss_enqueue<WT, kUnroll, PULL, MODE>(A, imp, v, cand, hvw, nxt, rn, acc, sh, seen);
       }
     }
 
-    // lane tier: rows of at most t_lane edges are not queued.  Each wavefront
-    // scans blocks of bw words of the step's bitmap (bw <= 64, halved until
-    // there are at least as many blocks as wavefronts; the rows come in index
-    // order), clears them, and takes their short rows 64 at a time; the rows'
-    // edges are dealt out to the lanes through an LDS prefix sum of the row
-    // lengths.  The scan clears every word, heavy rows' bits included: nothing
-    // else reads this bitmap during a push step.
+    // lane tier: rows of at most t_lane edges are not queued.  The wavefronts
+    // scan the step's bitmap, clear it and take its short rows 64 at a time; the
+    // rows' edges are dealt out to the lanes.  Groups of 1 << gs neighbouring
+    // words go to the wavefronts in turn (four words, 128 vertices, or fewer when
+    // that leaves wavefronts without a group; up to 64 words a wavefront at a
+    // time), so a run of frontier rows is shared by many of them.  With blocks of
+    // 32 words per wavefront the slowest workgroup took 13 us of a 15 us step on
+    // a 2048 x 2048 grid, against 5 on average.  The scan clears every word,
+    // heavy rows' bits included: nothing else reads this bitmap during a push
+    // step.
     const int64_t nwords = ((int64_t)A.n + 31) / 32;
-    int bw = kWave;
-    while (bw > 1 && (nwords + bw - 1) / bw < (int64_t)nwv) bw >>= 1;
-    const uint32_t nblk = (uint32_t)((nwords + bw - 1) / bw);
-    for (uint32_t blk = gw; blk < nblk; blk += nwv) {
-      const int64_t wi = (int64_t)blk * bw + lane;
+    int gs = 2;
+    while (gs > 0 && (nwords >> gs) < (int64_t)nwv) gs--;
+    const int64_t span = (int64_t)nwv << gs;  // words that lie between a lane's neighbours' groups
+    const int64_t lo = ((int64_t)gw << gs) + (lane & ((1 << gs) - 1));
+    for (int64_t w0 = 0; w0 < nwords; w0 += span << (6 - gs)) {
+      const int64_t wi = w0 + lo + (lane >> gs) * span;
+      // (a group's first word; words of later groups lie further on)
+      if (w0 + ((int64_t)gw << gs) >= nwords) break;
       uint32_t bits = 0u;
-      if (lane < bw && wi < nwords) {
-        const uint32_t word = ld_agent(&A.bm[cur][wi]);
+      if (wi < nwords) {
+        const uint32_t word = ld_agent(&A.bm[cur][wi]), hv = A.hv[wi];
         if (word) {
           st_agent(&A.bm[cur][wi], 0u);
-          bits = word & ~A.hv[wi];
+          bits = word & ~hv;
+          if (count) acc.im += (unsigned long long)__popc(word);
         }
       }
+      uint32_t* def = sh.def[wave];
+      if (NF) def[lane] = 0u;
       scan_rows(sh.scan[wave], bits, [&](bool has, int o, int bit) {
         int32_t start = 0, deg = 0;
         uint32_t du = 0;
         if (has) {
-          const int32_t u = (int32_t)(((int64_t)blk * bw + o) * 32 + bit);
+          const int64_t wo = w0 + ((int64_t)gw << gs) + (o & ((1 << gs) - 1)) + (o >> gs) * span;
+          const int32_t u = (int32_t)(wo * 32 + bit);
           start = A.rowptr[u];
           deg = A.rowptr[u + 1] - start;
           du = ld_agent(&A.dist[u]);
           const bool skipped = ss_skip_row(A, nxt, u);
+          if (NF && du > thr) {
+            atomicOr(&def[o], 1u << bit);
+            seen.minp = min(seen.minp, du);
+            deg = 0;
+          }
           if (deg > 0) acc.fe += 1;  // a frontier row (rows without edges are not counted)
           if (skipped) deg = 0;
           acc.es += (unsigned long long)deg;
+          if (NF) seen.work += (uint32_t)deg;
         }
         deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, [&](const int32_t (&e)[kUnrollLane],
                                                                   const bool (&ok)[kUnrollLane],
                                                                   const uint32_t (&d)[kUnrollLane]) {
           int32_t v[kUnrollLane];
           bool imp[kUnrollLane];
-          uint32_t cand[kUnrollLane];
-          ss_relax_pre<WT, kUnrollLane>(A, e, ok, d, imp, v, cand);
-          ss_enqueue<WT, kUnrollLane, PULL>(A, imp, v, cand, nxt, rn, acc, sh);
+          uint32_t cand[kUnrollLane], hvw[kUnrollLane];
+          ss_relax_pre<WT, kUnrollLane, MODE>(A, e, ok, d, imp, v, cand, hvw);
+          ss_enqueue<WT, kUnrollLane, PULL, MODE>(A, imp, v, cand, hvw, nxt, rn, acc, sh, seen);
         });
       });
+      if (NF) {
+        wave_lds_sync();
+        const uint32_t x = def[lane];
+        if (x) {
+          acc.im -= (unsigned long long)__popc(x);  // counted again by the next scan
+          atomicOr(&A.bm[nxt][wi], x);
+          sh.upd = 1u;
+        }
+      }
     }
 
   }
 
   // publish the workgroup's next-frontier entries and ptr flag
+  if constexpr (NF) {
+    const uint32_t mp = wave_min(seen.minp), wk = (uint32_t)wave_incl_scan((int)seen.work);
+    if (lane == kWave - 1) {
+      if (mp != kNoKey) atomicMin(&sh.minp, mp);
+      if (wk) atomicAdd(&sh.work, wk);
+    }
+  }
   __syncthreads();
   const uint32_t n_w = min(sh.nqw, (uint32_t)kLdsQWave);
   if (threadIdx.x == 0) {
     if (n_w) sh.gbase_w = atomicAdd(&C->cnt[rn][1].v, n_w);
     if (sh.upd) st_agent(&C->upd[rn], 1u);
+    if (!NF && sh.upd) sh.minp = 0u;  // some row; its key does not matter
   }
   __syncthreads();
   for (uint32_t j = threadIdx.x; j < n_w; j += blockDim.x) {
@@ -595,8 +845,91 @@ __device__ __forceinline__ void ss_zero_rotation(SsCtl* C, uint32_t step) {
   const int rz = (step + 2) % kRot;
   for (int t = 0; t < 4; t++) st_agent(&C->cnt[rz][t].v, 0u);
   st_agent(&C->upd[rz], 0u);
+  st_agent(&C->minp[rz].v, kNoKey);
   st_agent64(&C->ctr.fedges[rz], 0ull);
   st_agent64(&C->ctr.frows[rz], 0ull);
+}
+
+// Grid barrier of the single-source steps (grid_sync): an arrival carries the
+// workgroup's smallest next-frontier key, whether it queued rows and the edges
+// it expanded (to an eighth, as an 8-bit float), and the release word brings
+// back the next step's threshold (0: the frontier is empty) and whether the
+// queues hold rows, so neither costs an atomic or a load of its own.
+//   slot:    key (32) | epoch (23) | queued (1) | edges (8)
+//   release: threshold (32) | epoch (30) | fresh (1) | queued (1)
+// After a step of few edges the next one is bound by its chain of dependent
+// loads, and the barrier does without the invalidation: distances are then read
+// at agent scope (fresh), and the CSR's lines, which neighbouring frontiers
+// share, stay in the caches.  (Only where rows are deferred: elsewhere, R-MAT
+// above all, one step can be thousands of times larger than the last.)
+constexpr float kFreshWork = 65536.f;
+
+struct SsNext {
+  uint32_t thr;
+  bool queued, fresh;
+};
+
+template <int WT>
+__device__ __forceinline__ bool ss_grid_sync(SsCtl* C, uint32_t nblocks, uint32_t base,
+                                             uint32_t& epoch, unsigned long long ticks,
+                                             const SsShared& sh, NfState& nf, SsNext& next) {
+  __shared__ int s_ok;
+  __shared__ uint32_t s_min, s_queued, s_thr, s_fresh;
+  __shared__ float s_work;
+  GridBar* bar = &C->bar;
+  wait_own_stores();
+  if (threadIdx.x == 0) {
+    s_ok = 1;
+    s_min = sh.minp;
+    s_queued = sh.heavy;
+    s_work = (float)sh.work;
+  }
+  __syncthreads();
+  epoch += 1;
+  const uint32_t target = base + epoch;
+  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+  unsigned long long word;
+  if (blockIdx.x == 0) {
+    for (uint32_t b = 1 + threadIdx.x; b < nblocks; b += blockDim.x) {
+      if (!grid_wait<9>(&bar->slot[b], target, &C->abort, t0, ticks, word)) {
+        s_ok = 0;
+        break;
+      }
+      const uint32_t lo = (uint32_t)word;
+      atomicMin(&s_min, (uint32_t)(word >> 32));
+      if (lo & 0x100u) s_queued = 1u;
+      if (lo & 0xFFu)
+        atomicAdd(&s_work, __uint_as_float(((lo & 0xFFu) << 20) + 0x3F800000u) - 1.f);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t t = 0u;  // empty frontier
+      if (s_min != kNoKey) {
+        nf_advance<WT>(nf, s_min, s_work);
+        t = nf.thr;
+      }
+      s_thr = t;
+      s_fresh = nf.floor != 0.f && s_work <= kFreshWork;
+      if (s_ok)
+        st_agent64(&bar->release.v, ((unsigned long long)t << 32) | (target << 2) |
+                                        (s_fresh ? 2u : 0u) | (s_queued ? 1u : 0u));
+      if (!s_fresh) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+  } else if (threadIdx.x == 0) {
+    const uint32_t wk = (__float_as_uint((float)(sh.work + 1u)) - 0x3F800000u) >> 20;
+    st_agent64(&bar->slot[blockIdx.x], ((unsigned long long)sh.minp << 32) | (target << 9) |
+                                           (sh.heavy ? 0x100u : 0u) | wk);
+    if (!grid_wait<2>(&bar->release.v, target, &C->abort, t0, ticks, word)) s_ok = 0;
+    s_thr = (uint32_t)(word >> 32);
+    s_queued = (uint32_t)word & 1u;
+    s_fresh = (uint32_t)word & 2u;
+    if (!s_fresh) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
+  __syncthreads();
+  next.thr = s_thr;
+  next.queued = s_queued != 0u;
+  next.fresh = s_fresh != 0u;
+  return s_ok != 0;
 }
 
 // All steps in one launch; a grid barrier separates the steps.  The grid must
@@ -613,22 +946,30 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A) {
   const uint32_t bar_base = ld_agent(&C->bar_base);
   uint32_t step = ld_agent(&C->step);
   SsCounts counts = ss_counts(A, step);
+  NfState nf = C->nf;  // (workgroup 0 keeps it; written by an earlier launch)
+  SsNext next{nf.thr, false, false};
+  // the frontier of the first step here: seeds, or counted already when step
+  // launches that count as they enqueue came before
+  bool count = step > 0 && !A.counted;
   int32_t status = 1;
   for (;;) {
     if (blockIdx.x == 0 && threadIdx.x == 0) ss_zero_rotation(C, step);
-    ss_step<WT, false>(A, step, blockIdx.x, gridDim.x, acc, sh, counts);
-    if (!grid_sync(&C->bar, &C->abort, gridDim.x, bar_base, epoch, A.bar_ticks)) {
+    const uint32_t gb = blockIdx.x, nb = gridDim.x;
+    if (nf_weights<WT>() && nf.floor != 0.f) {
+      if (next.fresh) ss_step<WT, false, kFresh>(A, step, gb, nb, acc, sh, counts, next.thr, count);
+      else ss_step<WT, false, kNear>(A, step, gb, nb, acc, sh, counts, next.thr, count);
+    } else {
+      ss_step<WT, false, kAll>(A, step, gb, nb, acc, sh, counts, kNoKey, count);
+    }
+    count = true;
+    if (!ss_grid_sync<WT>(C, gridDim.x, bar_base, epoch, A.bar_ticks, sh, nf, next)) {
       status = -2;
       break;
     }
-    // the step's update flag and the next step's queue counts, one round trip
-    // (all were written before the barrier; nothing writes them during the
-    // next step, whose pushes count in the rotation slot after)
-    const uint32_t upd = ld_agent(&C->upd[(step + 1) % kRot]);
-    counts = ss_counts(A, step + 1);
     step++;
-    if (!upd) { status = 1; break; }
+    if (next.thr == 0u) { status = 1; break; }
     if (step >= (uint32_t)A.n) { status = 0; break; }
+    counts = next.queued ? ss_counts(A, step) : SsCounts{0u, 0u};
   }
   SsCounters& S = C->ctr;
   flush_acc(acc, &S.fe, &S.es, &S.im, nullptr, nullptr);
@@ -649,7 +990,17 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
   const uint32_t step = ld_agent(&C->step);
   if (blockIdx.x == 0 && threadIdx.x == 0) ss_zero_rotation(C, step);
   Acc acc;
-  const bool pulled = ss_step<WT, PULL>(A, step, blockIdx.x, gridDim.x, acc, sh, ss_counts(A, step));
+  const uint32_t gb = blockIdx.x, nb = gridDim.x;
+  const bool near = nf_weights<WT>() && C->nf.floor != 0.f;  // (written by an earlier launch)
+  bool pulled;
+  if (near)
+    pulled = ss_step<WT, PULL, kNear>(A, step, gb, nb, acc, sh, ss_counts(A, step), C->nf.thr,
+                                      !PULL && step > 0);
+  else
+    pulled = ss_step<WT, PULL, kAll>(A, step, gb, nb, acc, sh, ss_counts(A, step), kNoKey,
+                                     !PULL && step > 0);
+  if (near && threadIdx.x == 0 && sh.minp != kNoKey)
+    atomicMin(&C->minp[(step + 1) % kRot].v, sh.minp);
   // counters, and the next frontier's out-edges and rows (its pull decision)
   SsCounters& S = C->ctr;
   flush_acc(acc, &S.fe, &S.es, &S.im, &S.fedges[(step + 1) % kRot], &S.frows[(step + 1) % kRot]);
@@ -663,6 +1014,13 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
     const uint32_t upd = ld_agent(&C->upd[(step + 1) % kRot]);
     const uint32_t ns = step + 1;
     st_agent(&C->step, ns);
+    if (near && upd) {
+      NfState nf = C->nf;  // (only a launch's last workgroup writes it)
+      const unsigned long long es = ld_agent64(&S.es);
+      nf_advance<WT>(nf, ld_agent(&C->minp[ns % kRot].v), (float)(es - C->es_seen));
+      C->es_seen = es;
+      C->nf = nf;
+    }
     if (!upd) {
       st_agent_i(&C->converged, 1);
       st_agent(&C->done, 1u);
@@ -1365,6 +1723,23 @@ Residency ss_persistent_residency(int threads) {
   return residency_of(ss_persistent_kernel<kWU32>, threads);
 }
 
+// Workgroups of a persistent launch.  A barrier costs 1.9 us with 64 and 3.3 us
+// with 256, and the steps of sparse or small graphs are bound by it and by one
+// chain of loads; steps with many edges need the whole chip.  m * (m / n) tells
+// the two apart.  Measured at 256 / 128 / 64 / 32 workgroups: grid 2048 x 2048
+// 43.5 / 37.9 / 41.2 / 50.1 ms, grid 512 x 512 12.9 / 11.3 / 10.4 / 9.2 ms, ER
+// n = 100,000 420 / 359 / 352 / 366 us, ER n = 1,000,000 910 / 863 / 1053 /
+// 1519 us, R-MAT scale 16 447 / 439 / 444 / 460 us, scale 20 820 / 952 / 1320 /
+// 2129 us.  Powers of two: workgroup b runs on XCD b mod 8, and with 125 or 112
+// workgroups the 2048 x 2048 grid took 43.4 and 40.4 ms, against 37.9 with 128
+// (the rows below each other of a grid then stay on one XCD).
+static int ss_persistent_wgs(int64_t n, int64_t m, int resident) {
+  const double grow = (double)m * ((double)m / (double)n) / (double)(1 << 26);
+  int wgs = m < 6 * n ? 32 : 64;
+  while (wgs < resident && grow * 128 > wgs * 1.42) wgs *= 2;
+  return std::min(wgs, resident);
+}
+
 template <int WT>
 static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_t* colidx,
                             const SsSeeds& seeds, const SsLayout& L, dawn_run_info* info,
@@ -1372,14 +1747,15 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   const Tuning& T = tuning();
   const DevInfo& di = dev_info();
   // mode 0 picks: one workgroup when m <= small_m; step launches first when
-  // m >= step_min_m; otherwise the persistent launch alone.  Measured on
-  // MI355X: on R-MAT scale 22 (67M edges) step launches of 512-thread
-  // workgroups take a third of the time of the persistent launch; on
-  // 16.7M-edge graphs (R-MAT scale 20, the 2048^2 grid) the persistent launch
-  // of 1024-thread workgroups is faster.
+  // m >= step_min_m (by default never); otherwise the persistent launch alone.
+  // Measured, persistent against step launches of 512-thread workgroups: R-MAT
+  // scale 22 2.21 / 2.55 ms, scale 20 0.81 / 0.99 ms, 64 ER graphs (118M edges)
+  // 5.74 / 6.10 ms, the 2048^2 grid 43.4 / 47.2 ms.
   int mode = T.mode;
+  // (Pull steps need step launches: large graphs with a reverse graph keep them.)
   if (mode == 0) mode = (int64_t)A.m <= (int64_t)T.small_m ? 3
-                        : (int64_t)A.m >= (int64_t)T.step_min_m ? 1 : 2;
+                        : (int64_t)A.m >= (int64_t)T.step_min_m ||
+                          (A.pull_min >= 0 && A.m >= 1 << 25) ? 1 : 2;
   const int threads = T.wg_threads > 0 ? T.wg_threads : mode == 1 ? 512 : 1024;
   const int fill_blocks = (int)std::min<int64_t>(4096, (A.n + 255) / 256 + 1);
   dawn_status st;
@@ -1387,7 +1763,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     // one workgroup, one launch (after the optional device validation)
     if (T.validate) {
       hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
-                         (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, nullptr, nullptr, 0);
+                         (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, nullptr, nullptr, 0, nullptr, 0);
       const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
       hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
                          A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
@@ -1410,7 +1786,8 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     return hip_check(hipGetLastError(), "small-graph launch");
   }
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
-                     (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, rowptr, A.hv, A.t_lane);
+                     (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, rowptr, A.hv, A.t_lane, A.w,
+                     (int64_t)A.m);
   if (T.validate) {
     const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
     hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
@@ -1436,10 +1813,11 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   }
   {
     const Residency r = residency_of(ss_persistent_kernel<WT>, threads);
-    int grid = std::min(r.grid, kMaxGrid);
+    int grid = std::min(std::min(r.grid, kMaxGrid), ss_persistent_wgs(A.n, A.m, r.grid));
     if (T.grid > 0 && T.grid < grid) grid = T.grid;
     if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
     SsArgs a = A;
+    a.counted = mode == 1 && A.pull_min >= 0;
     a.pull_min = -1;  // pull steps need step launches (the last workgroup clears the bitmap)
     void* args[] = {&a};
     hipError_t e;
