@@ -476,7 +476,8 @@ __global__ void dawn_info_add_kernel(dawn_run_info* acc, const dawn_run_info* pa
   acc->union_edges += part->union_edges;
 }
 
-// A multi-source run, tile by tile.  Each tile: reset, seeding,
+// A multi-source run: one workgroup per source on small graphs, copies of the
+// graph for a few sources, else tile by tile.  Each tile: reset, seeding,
 // `tile_step_launches` step launches (a step launch returns at once once the
 // tile's run has ended), then one persistent launch for whatever steps remain
 // (tuning mode 2: the persistent launch alone), the transposed store and the
@@ -494,6 +495,9 @@ static dawn_status msssp_impl(const int32_t* rowptr, const int32_t* colidx, cons
                         sources, k, dist_out, info, stream);
   const int32_t kt = std::min(k, g_tuning.tile_k);
   const TileLayout L = tile_layout(n, m, kt, unweighted);
+  if (ss_copies_fit(n, m, k, unweighted, L.total))
+    return ss_copies_run(rowptr, colidx, weights, unweighted ? kWUNIT : f32 ? kWF32 : kWU32, n, m,
+                         sources, k, dist_out, ws, info, stream);
   TileArgs A = tile_args(rowptr, colidx, weights, n, m, L, ws);
   if (tgraph && g_tuning.tile_pull <= 1000) {
     A.T = tgraph_view(tgraph, n, m);

@@ -285,20 +285,22 @@ __device__ __forceinline__ int deal_rank(const DealMarks<WIN>& mk, int base, int
   return r;
 }
 
-// Staging of one wavefront's rows: {first edge minus prefix, distance} by rank.
-template <int WIN>
+// Staging of one wavefront's rows: {first edge minus prefix, distance} by rank,
+// and with X a further word of the row.
+template <int WIN, bool X = false>
 struct DealRows {
   int2 row[kWave];
+  int32_t extra[X ? kWave : 1];
   DealMarks<WIN> mk;
 };
 
 // Deal the edges of the rows held one per lane (edges [start, start + deg),
-// row distance du) to the lanes, U per lane at a time: f(e, ok, d) with edge
-// ids e[U], their validity and their row's distance.  Reached by the whole
-// wavefront.
-template <int U, int WIN, typename F>
-__device__ __forceinline__ void deal_rows(DealRows<WIN>& st, int32_t start, int32_t deg,
-                                          uint32_t du, F&& f) {
+// row distance du) to the lanes, U per lane at a time: f(e, ok, d, x) with edge
+// ids e[U], their validity, their row's distance and (X) its further word.
+// Reached by the whole wavefront.
+template <int U, int WIN, bool X, typename F>
+__device__ __forceinline__ void deal_rows(DealRows<WIN, X>& st, int32_t start, int32_t deg,
+                                          uint32_t du, int32_t extra, F&& f) {
   static_assert(WIN % (64 * U) == 0, "whole rounds per window");
   const int lane = lane_id();
   const int incl = wave_incl_scan(deg);
@@ -306,25 +308,30 @@ __device__ __forceinline__ void deal_rows(DealRows<WIN>& st, int32_t start, int3
   if (total == 0) return;
   const int excl = incl - deg;
   const unsigned long long nz = __ballot(deg > 0);
-  if (deg > 0) st.row[lanes_below(nz)] = make_int2(start - excl, (int)du);
+  if (deg > 0) {
+    st.row[lanes_below(nz)] = make_int2(start - excl, (int)du);
+    if (X) st.extra[lanes_below(nz)] = extra;
+  }
   int before = 0;
   for (int wb = 0; wb < total; wb += WIN) {
     deal_mark(st.mk, excl, deg, wb);
     const int end = min(total - wb, WIN);
     for (int base = 0; base < end; base += kWave * U) {
-      int32_t e[U];
+      int32_t e[U], x[U];
       bool ok[U];
       uint32_t d[U];
 #pragma unroll
       for (int j = 0; j < U; j++) {
         const int k = wb + base + j * kWave + lane;
         // past the end the rank stays the last list's: a row that was stored
-        const int2 r = st.row[deal_rank(st.mk, base + j * kWave, before)];
+        const int rk = deal_rank(st.mk, base + j * kWave, before);
+        const int2 r = st.row[rk];
+        x[j] = X ? st.extra[rk] : 0;
         ok[j] = k < total;
         e[j] = r.x + k;
         d[j] = (uint32_t)r.y;
       }
-      f(e, ok, d);
+      f(e, ok, d, x);
     }
     wave_lds_sync();
   }
@@ -562,6 +569,11 @@ struct SsArgs {
   const uint32_t* w;      // uint32 weights, or fp32 weights as bits
   uint32_t* dist;         // alpha
   int32_t n, m;
+  // Copies: a run of several sources on one graph, whose vertices are numbered
+  // copy * n1 + v (n = copies * n1); else n1 = n.
+  int32_t n1;
+  uint32_t inv1;          // floor(2^32 / n1)
+  float nf_work;          // edges per step that keep the chip busy (deferral)
   int32_t src;            // the "index != source" guard; -1 with many seeds
   int32_t skip;           // skip expanding a row already lowered again in this step
   TGraph T;               // reverse graph for pull steps, or hdr == nullptr

@@ -135,6 +135,13 @@ dawn_status ss_multi_run(const int32_t* rowptr, const int32_t* colidx, const voi
                          int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
                          dawn_run_info* info, hipStream_t stream);
 
+// Multi-source calls of few sources: one run on copies of the graph,
+// dist[j * n + v], in ws_bytes of workspace.
+bool ss_copies_fit(int64_t n, int64_t m, int32_t k, bool unit, size_t ws_bytes);
+dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
+                          int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
+                          void* ws, dawn_run_info* info, hipStream_t stream);
+
 // ----- distance tile ---------------------------------------------------------
 struct TileLayout {
   size_t ctl, info, D, mk[3], qgrp[3], qwave[3], qwg[3], fbm[2], vis, planes, total;

@@ -69,6 +69,10 @@ constexpr float kNfDelta = 1.2f;
 constexpr float kNfWork = 30000.f;
 constexpr int kNfSamples = 4096;
 
+// Copies (several sources in one run): a step holds the work of all.  (Three
+// times as much: grid 1000 x 1021, k = 2 24.6 -> 30.8 ms, k = 8 37.4 -> 36.8.)
+constexpr float copies_work(int k) { return k < 4 ? 1.f : (float)k / 4.f; }
+
 template <int WT>
 __device__ __forceinline__ constexpr bool nf_weights() {
   return WT == kWU32 || WT == kWF32;
@@ -90,12 +94,12 @@ __device__ __forceinline__ uint32_t nf_threshold(uint32_t M, float delta) {
 // The next step's threshold, from the frontier's smallest key and the edges of
 // the step that ended.
 template <int WT>
-__device__ __forceinline__ void nf_advance(NfState& s, uint32_t M, float work) {
+__device__ __forceinline__ void nf_advance(NfState& s, uint32_t M, float work, float busy) {
   if (!nf_weights<WT>() || s.floor == 0.f) return;
-  if (work > kNfWork) {
+  if (work > busy) {
     s.delta = fmaxf(0.5f * s.delta, s.floor);
     s.big = 1u;
-  } else if (work < 0.5f * kNfWork && s.delta < 1e30f) {
+  } else if (work < 0.5f * busy && s.delta < 1e30f) {
     s.delta *= s.big ? 2.f : 1.1f;
   }
   s.thr = nf_threshold<WT>(M, s.delta);
@@ -155,7 +159,7 @@ __device__ void nf_init(SsCtl* ctl, int64_t n, int64_t m, const int32_t* rowptr,
 template <int WT>
 __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_t* bm1,
                                int64_t nwords, SsCtl* ctl, const int32_t* rowptr, uint32_t* hv,
-                               int32_t t_lane, const uint32_t* w, int64_t m) {
+                               int32_t t_lane, const uint32_t* w, int64_t m, int32_t n1) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = tid; i < n; i += stride) dist[i] = inf_key<WT>();
@@ -166,7 +170,8 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
     const int lane = lane_id();
     for (int64_t v0 = tid - lane; v0 < n; v0 += stride) {
       const int64_t v = v0 + lane;
-      const bool heavy = v < n && rowptr[v + 1] - rowptr[v] > t_lane;
+      const uint32_t u = (uint32_t)v % (uint32_t)n1;  // (the row of a copy's vertex)
+      const bool heavy = v < n && rowptr[u + 1] - rowptr[u] > t_lane;
       const unsigned long long b = __ballot(heavy);
       const int64_t wi = v0 / 32 + (lane >> 5);
       if ((lane & 31) == 0 && wi < nwords) hv[wi] = (uint32_t)(b >> (lane & 32));
@@ -180,7 +185,7 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
     for (int i = threadIdx.x; i < (int)(offsetof(SsCtl, bar.slot) / 4); i += blockDim.x) c[i] = 0;
     __syncthreads();
     if (threadIdx.x < kRot) ctl->minp[threadIdx.x].v = kNoKey;
-    nf_init<WT>(ctl, n, m, rowptr, w);
+    nf_init<WT>(ctl, n1, m, rowptr, w);
   }
 }
 
@@ -336,7 +341,7 @@ __device__ __forceinline__ void scan_rows(ScanRows& st, uint32_t bits, F&& f) {
 }
 
 struct SsShared {
-  DealRows<4096> rows[kMaxWavesPerBlock];  // lane-tier batch
+  DealRows<4096, true> rows[kMaxWavesPerBlock];  // lane-tier batch
   ScanRows scan[kMaxWavesPerBlock];        // bitmap block
   uint32_t def[kMaxWavesPerBlock][kWave];  // deferred rows, by word of the block
   int32_t qw[kLdsQWave];
@@ -402,9 +407,11 @@ __device__ __forceinline__ void ss_queue_row(const SsArgs& A, bool pred, int32_t
 // Reached by the whole wavefront.  CNT: also count the vertices lowered (else
 // the next step's scan does) and the next frontier's rows and out-edges (the
 // pull decision of the next step).
+// off: what the copy adds to vertex ids (v has it added).
 template <int WT, int U, bool CNT, int MODE>
 __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U],
-                                           const int32_t (&v)[U], const uint32_t (&cand)[U],
+                                           const int32_t (&v)[U], const int32_t (&off)[U],
+                                           const uint32_t (&cand)[U],
                                            const uint32_t (&hvw)[U], int nxt, int rn, Acc& acc,
                                            SsShared& sh, StepSeen& seen) {
   bool any = false;
@@ -467,8 +474,8 @@ __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U]
     start[i] = 0;
     deg[i] = 0;
     if (newv[i]) {
-      start[i] = A.rowptr[v[i]];
-      deg[i] = A.rowptr[v[i] + 1] - start[i];
+      start[i] = A.rowptr[v[i] - off[i]];
+      deg[i] = A.rowptr[v[i] - off[i] + 1] - start[i];
       if (CNT && deg[i] > 0) {
         acc.sa += (unsigned long long)deg[i];  // the next frontier's out-edges
         acc.se += 1;                           // and rows
@@ -518,14 +525,15 @@ __device__ __forceinline__ void ss_relax_n(const SsArgs& A, const int32_t (&e)[U
 template <int WT, int U, int MODE>
 __device__ __forceinline__ void ss_relax_pre(const SsArgs& A, const int32_t (&e)[U],
                                              const bool (&valid)[U], const uint32_t (&du)[U],
-                                             bool (&imp)[U], int32_t (&v)[U],
-                                             uint32_t (&cand)[U], uint32_t (&hvw)[U]) {
+                                             const int32_t (&off)[U], bool (&imp)[U],
+                                             int32_t (&v)[U], uint32_t (&cand)[U],
+                                             uint32_t (&hvw)[U]) {
 #pragma unroll
   for (int i = 0; i < U; i++) {
     v[i] = 0;
     cand[i] = 0u;
     if (valid[i]) {
-      v[i] = A.colidx[e[i]];
+      v[i] = A.colidx[e[i]] + off[i];
       cand[i] = relax_key<WT>(du[i], WT == kWUNIT ? 1u : A.w[e[i]]);
       if constexpr (WT == kWI32)
         if (cand[i] == 0u) atomicOr(&A.ctl->negfloor, 1u);  // sum left the int32 range
@@ -591,9 +599,9 @@ __device__ __forceinline__ void ss_pull(const SsArgs& A, int cur, int nxt, int r
     }
     best = row16_min(best);
     bool imp[1] = {cok && j16 == 0 && v != A.src && best < A.dist[v]};
-    const int32_t vv[1] = {v};
+    const int32_t vv[1] = {v}, off[1] = {0};
     const uint32_t cc[1] = {best}, hvw[1] = {0u};
-    ss_enqueue<WT, 1, true, MODE>(A, imp, vv, cc, hvw, nxt, rn, acc, sh, seen);
+    ss_enqueue<WT, 1, true, MODE>(A, imp, vv, off, cc, hvw, nxt, rn, acc, sh, seen);
   }
 }
 
@@ -607,8 +615,8 @@ __device__ __forceinline__ bool ss_skip_row(const SsArgs& A, int nxt, int32_t u)
 
 // Leave row u (one of the queued tiers) in the frontier: its next bit, and for
 // its first setter the next queue.  Reached by the whole wavefront.
-__device__ __forceinline__ void ss_defer_row(const SsArgs& A, bool lead, int32_t u, uint32_t du,
-                                             int nxt, int rn, Acc& acc, SsShared& sh,
+__device__ __forceinline__ void ss_defer_row(const SsArgs& A, bool lead, int32_t u, int32_t off,
+                                             uint32_t du, int nxt, int rn, Acc& acc, SsShared& sh,
                                              StepSeen& seen) {
   bool first = false;
   int32_t start = 0, deg = 0;
@@ -618,10 +626,20 @@ __device__ __forceinline__ void ss_defer_row(const SsArgs& A, bool lead, int32_t
     seen.minp = min(seen.minp, du);
     sh.upd = 1u;
     acc.im -= first ? 1ull : 0ull;  // counted again by the next scan
-    start = A.rowptr[u];
-    deg = A.rowptr[u + 1] - start;
+    start = A.rowptr[u - off];
+    deg = A.rowptr[u - off + 1] - start;
   }
   ss_queue_row(A, first, u, start, deg, nxt, rn, sh);
+}
+
+// What the copy of vertex u adds to vertex ids (0 without copies).
+template <bool COPIES>
+__device__ __forceinline__ int32_t copy_off(const SsArgs& A, int32_t u) {
+  if constexpr (!COPIES) return 0;
+  // floor(2^32 / n1) gives the quotient or one less
+  int32_t off = (int32_t)(__umulhi((uint32_t)u, A.inv1) * (uint32_t)A.n1);
+  if (u - off >= A.n1) off += A.n1;
+  return off;
 }
 
 // Returns true when the step was a pull step.
@@ -645,7 +663,7 @@ __device__ __forceinline__ SsCounts ss_counts(const SsArgs& A, uint32_t step) {
   return SsCounts{min(ld_agent(&C->cnt[rc][1].v), A.cap_v), min(ld_agent(&C->cnt[rc][2].v), A.cap_wg)};
 }
 
-template <int WT, bool PULL, int MODE>
+template <int WT, bool PULL, int MODE, bool COPIES>
 __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb, Acc& acc,
                         SsShared& sh, SsCounts counts, uint32_t thr, bool count) {
   constexpr bool NF = MODE != kAll;
@@ -676,7 +694,7 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
     // workgroup tier: one chunk of one row per workgroup
     for (uint32_t i = gb; i < ng; i += nb) {
       const int4 r = ld_queue4(&A.qwg[cur][i]);
-      const int32_t u = r.x, start = r.y;
+      const int32_t u = r.x, start = r.y, uoff = copy_off<COPIES>(A, u);
       const uint32_t dul = ld_agent(&A.dist[u]);
       const bool skipped = ss_skip_row(A, nxt, u);  // (loaded beside the distance)
       // one value per wavefront (another wavefront may read a lower one; then
@@ -686,7 +704,7 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
         // left in the frontier: whichever chunk of the row sets the next bit
         // queues the whole row again (a chunk that is expanded meanwhile, with a
         // value lowered in this step, is expanded once more then)
-        if (wave == 0) ss_defer_row(A, lane == 0, u, du, nxt, rn, acc, sh, seen);
+        if (wave == 0) ss_defer_row(A, lane == 0, u, uoff, du, nxt, rn, acc, sh, seen);
         continue;
       }
       const int32_t len = skipped ? 0 : r.z;
@@ -697,7 +715,7 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
       }
       const int32_t stride = (int32_t)blockDim.x;
       for (int32_t base = 0; base < len; base += stride * kUnroll) {
-        int32_t e[kUnroll], v[kUnroll];
+        int32_t e[kUnroll], v[kUnroll], off[kUnroll];
         bool ok[kUnroll], imp[kUnroll];
         uint32_t d[kUnroll], cand[kUnroll], hvw[kUnroll];
   #pragma unroll
@@ -706,21 +724,22 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
           ok[j] = k < len;
           e[j] = start + k;
           d[j] = du;
+          off[j] = uoff;
         }
-        ss_relax_pre<WT, kUnroll, MODE>(A, e, ok, d, imp, v, cand, hvw);
-        ss_enqueue<WT, kUnroll, PULL, MODE>(A, imp, v, cand, hvw, nxt, rn, acc, sh, seen);
+        ss_relax_pre<WT, kUnroll, MODE>(A, e, ok, d, off, imp, v, cand, hvw);
+        ss_enqueue<WT, kUnroll, PULL, MODE>(A, imp, v, off, cand, hvw, nxt, rn, acc, sh, seen);
       }
     }
 
     // wave tier: one wavefront per row
     for (uint32_t i = gw; i < nw; i += nwv) {
-      const int32_t u = ld_queue(&A.qwave[cur][i]);
+      const int32_t u = ld_queue(&A.qwave[cur][i]), uoff = copy_off<COPIES>(A, u);
       const uint32_t dul = ld_agent(&A.dist[u]);
-      const int32_t start = A.rowptr[u], last = A.rowptr[u + 1];
+      const int32_t start = A.rowptr[u - uoff], last = A.rowptr[u - uoff + 1];
       const bool skipped = ss_skip_row(A, nxt, u);
       const uint32_t du = (uint32_t)__builtin_amdgcn_readfirstlane((int)dul);
       if (NF && du > thr) {
-        ss_defer_row(A, lane == 0, u, du, nxt, rn, acc, sh, seen);
+        ss_defer_row(A, lane == 0, u, uoff, du, nxt, rn, acc, sh, seen);
         continue;
       }
       const int32_t end = skipped ? start : last;
@@ -730,7 +749,7 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
         if (NF) seen.work += (uint32_t)(end - start);
       }
       for (int32_t base = start; base < end; base += kWave * kUnroll) {
-        int32_t e[kUnroll], v[kUnroll];
+        int32_t e[kUnroll], v[kUnroll], off[kUnroll];
         bool ok[kUnroll], imp[kUnroll];
         uint32_t d[kUnroll], cand[kUnroll], hvw[kUnroll];
   #pragma unroll
@@ -738,9 +757,10 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
           e[j] = base + j * kWave + lane;
           ok[j] = e[j] < end;
           d[j] = du;
+          off[j] = uoff;
         }
-        ss_relax_pre<WT, kUnroll, MODE>(A, e, ok, d, imp, v, cand, hvw);
-        ss_enqueue<WT, kUnroll, PULL, MODE>(A, imp, v, cand, hvw, nxt, rn, acc, sh, seen);
+        ss_relax_pre<WT, kUnroll, MODE>(A, e, ok, d, off, imp, v, cand, hvw);
+        ss_enqueue<WT, kUnroll, PULL, MODE>(A, imp, v, off, cand, hvw, nxt, rn, acc, sh, seen);
       }
     }
 
@@ -775,13 +795,14 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
       uint32_t* def = sh.def[wave];
       if (NF) def[lane] = 0u;
       scan_rows(sh.scan[wave], bits, [&](bool has, int o, int bit) {
-        int32_t start = 0, deg = 0;
+        int32_t start = 0, deg = 0, uoff = 0;
         uint32_t du = 0;
         if (has) {
           const int64_t wo = w0 + ((int64_t)gw << gs) + (o & ((1 << gs) - 1)) + (o >> gs) * span;
           const int32_t u = (int32_t)(wo * 32 + bit);
-          start = A.rowptr[u];
-          deg = A.rowptr[u + 1] - start;
+          uoff = copy_off<COPIES>(A, u);
+          start = A.rowptr[u - uoff];
+          deg = A.rowptr[u - uoff + 1] - start;
           du = ld_agent(&A.dist[u]);
           const bool skipped = ss_skip_row(A, nxt, u);
           if (NF && du > thr) {
@@ -794,14 +815,17 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
           acc.es += (unsigned long long)deg;
           if (NF) seen.work += (uint32_t)deg;
         }
-        deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, [&](const int32_t (&e)[kUnrollLane],
-                                                                  const bool (&ok)[kUnrollLane],
-                                                                  const uint32_t (&d)[kUnrollLane]) {
-          int32_t v[kUnrollLane];
+        deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, uoff, [&](const int32_t (&e)[kUnrollLane],
+                                                                        const bool (&ok)[kUnrollLane],
+                                                                        const uint32_t (&d)[kUnrollLane],
+                                                                        const int32_t (&offs)[kUnrollLane]) {
+          int32_t v[kUnrollLane], off[kUnrollLane];
+#pragma unroll
+          for (int j = 0; j < kUnrollLane; j++) off[j] = COPIES ? offs[j] : 0;
           bool imp[kUnrollLane];
           uint32_t cand[kUnrollLane], hvw[kUnrollLane];
-          ss_relax_pre<WT, kUnrollLane, MODE>(A, e, ok, d, imp, v, cand, hvw);
-          ss_enqueue<WT, kUnrollLane, PULL, MODE>(A, imp, v, cand, hvw, nxt, rn, acc, sh, seen);
+          ss_relax_pre<WT, kUnrollLane, MODE>(A, e, ok, d, off, imp, v, cand, hvw);
+          ss_enqueue<WT, kUnrollLane, PULL, MODE>(A, imp, v, off, cand, hvw, nxt, rn, acc, sh, seen);
         });
       });
       if (NF) {
@@ -857,13 +881,11 @@ __device__ __forceinline__ void ss_zero_rotation(SsCtl* C, uint32_t step) {
 // queues hold rows, so neither costs an atomic or a load of its own.
 //   slot:    key (32) | epoch (23) | queued (1) | edges (8)
 //   release: threshold (32) | epoch (30) | fresh (1) | queued (1)
-// After a step of few edges the next one is bound by its chain of dependent
+// After a step of few edges (at most twice nf_work) the next one is bound by its chain of dependent
 // loads, and the barrier does without the invalidation: distances are then read
 // at agent scope (fresh), and the CSR's lines, which neighbouring frontiers
 // share, stay in the caches.  (Only where rows are deferred: elsewhere, R-MAT
 // above all, one step can be thousands of times larger than the last.)
-constexpr float kFreshWork = 65536.f;
-
 struct SsNext {
   uint32_t thr;
   bool queued, fresh;
@@ -872,7 +894,7 @@ struct SsNext {
 template <int WT>
 __device__ __forceinline__ bool ss_grid_sync(SsCtl* C, uint32_t nblocks, uint32_t base,
                                              uint32_t& epoch, unsigned long long ticks,
-                                             const SsShared& sh, NfState& nf, SsNext& next) {
+                                             const SsShared& sh, NfState& nf, float busy, SsNext& next) {
   __shared__ int s_ok;
   __shared__ uint32_t s_min, s_queued, s_thr, s_fresh;
   __shared__ float s_work;
@@ -905,11 +927,11 @@ __device__ __forceinline__ bool ss_grid_sync(SsCtl* C, uint32_t nblocks, uint32_
     if (threadIdx.x == 0) {
       uint32_t t = 0u;  // empty frontier
       if (s_min != kNoKey) {
-        nf_advance<WT>(nf, s_min, s_work);
+        nf_advance<WT>(nf, s_min, s_work, busy);
         t = nf.thr;
       }
       s_thr = t;
-      s_fresh = nf.floor != 0.f && s_work <= kFreshWork;
+      s_fresh = nf.floor != 0.f && s_work <= 2.f * busy;
       if (s_ok)
         st_agent64(&bar->release.v, ((unsigned long long)t << 32) | (target << 2) |
                                         (s_fresh ? 2u : 0u) | (s_queued ? 1u : 0u));
@@ -936,7 +958,7 @@ __device__ __forceinline__ bool ss_grid_sync(SsCtl* C, uint32_t nblocks, uint32_
 // be co-resident: its size is what the compute units hold at once by the
 // kernel's compiled resources (residency_of); should a barrier wait still give
 // up, the run ends with status -2, reported to the caller.
-template <int WT>
+template <int WT, bool COPIES>
 __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A) {
   __shared__ SsShared sh;
   SsCtl* C = A.ctl;
@@ -956,13 +978,15 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A) {
     if (blockIdx.x == 0 && threadIdx.x == 0) ss_zero_rotation(C, step);
     const uint32_t gb = blockIdx.x, nb = gridDim.x;
     if (nf_weights<WT>() && nf.floor != 0.f) {
-      if (next.fresh) ss_step<WT, false, kFresh>(A, step, gb, nb, acc, sh, counts, next.thr, count);
-      else ss_step<WT, false, kNear>(A, step, gb, nb, acc, sh, counts, next.thr, count);
+      if (next.fresh)
+        ss_step<WT, false, kFresh, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count);
+      else
+        ss_step<WT, false, kNear, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count);
     } else {
-      ss_step<WT, false, kAll>(A, step, gb, nb, acc, sh, counts, kNoKey, count);
+      ss_step<WT, false, kAll, COPIES>(A, step, gb, nb, acc, sh, counts, kNoKey, count);
     }
     count = true;
-    if (!ss_grid_sync<WT>(C, gridDim.x, bar_base, epoch, A.bar_ticks, sh, nf, next)) {
+    if (!ss_grid_sync<WT>(C, gridDim.x, bar_base, epoch, A.bar_ticks, sh, nf, A.nf_work, next)) {
       status = -2;
       break;
     }
@@ -994,10 +1018,10 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
   const bool near = nf_weights<WT>() && C->nf.floor != 0.f;  // (written by an earlier launch)
   bool pulled;
   if (near)
-    pulled = ss_step<WT, PULL, kNear>(A, step, gb, nb, acc, sh, ss_counts(A, step), C->nf.thr,
+    pulled = ss_step<WT, PULL, kNear, false>(A, step, gb, nb, acc, sh, ss_counts(A, step), C->nf.thr,
                                       !PULL && step > 0);
   else
-    pulled = ss_step<WT, PULL, kAll>(A, step, gb, nb, acc, sh, ss_counts(A, step), kNoKey,
+    pulled = ss_step<WT, PULL, kAll, false>(A, step, gb, nb, acc, sh, ss_counts(A, step), kNoKey,
                                      !PULL && step > 0);
   if (near && threadIdx.x == 0 && sh.minp != kNoKey)
     atomicMin(&C->minp[(step + 1) % kRot].v, sh.minp);
@@ -1017,7 +1041,7 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
     if (near && upd) {
       NfState nf = C->nf;  // (only a launch's last workgroup writes it)
       const unsigned long long es = ld_agent64(&S.es);
-      nf_advance<WT>(nf, ld_agent(&C->minp[ns % kRot].v), (float)(es - C->es_seen));
+      nf_advance<WT>(nf, ld_agent(&C->minp[ns % kRot].v), (float)(es - C->es_seen), A.nf_work);
       C->es_seen = es;
       C->nf = nf;
     }
@@ -1112,9 +1136,10 @@ __global__ void __launch_bounds__(1024) ss_small_kernel(SsArgs A, const int32_t*
             acc.es += (unsigned long long)deg;
           }
         }
-        deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, [&](const int32_t (&e)[kUnrollLane],
-                                                                  const bool (&ok)[kUnrollLane],
-                                                                  const uint32_t (&d)[kUnrollLane]) {
+        deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, 0, [&](const int32_t (&e)[kUnrollLane],
+                                                                     const bool (&ok)[kUnrollLane],
+                                                                     const uint32_t (&d)[kUnrollLane],
+                                                                     const int32_t (&)[kUnrollLane]) {
           int32_t v[kUnrollLane];
           bool imp[kUnrollLane];
           ss_relax_n<WT, kUnrollLane>(A, e, ok, d, imp, v);
@@ -1387,9 +1412,10 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
             if (A.skip && ((bn[u >> 5] >> (u & 31)) & 1u)) deg = 0;
             acc.es += (unsigned long long)deg;
           }
-          deal_rows<kUnrollCu>(st.rows, start, deg, du, [&](const int32_t (&e)[kUnrollCu],
-                                                            const bool (&ok)[kUnrollCu],
-                                                            const uint32_t (&d)[kUnrollCu]) {
+          deal_rows<kUnrollCu>(st.rows, start, deg, du, 0, [&](const int32_t (&e)[kUnrollCu],
+                                                               const bool (&ok)[kUnrollCu],
+                                                               const uint32_t (&d)[kUnrollCu],
+                                                               const int32_t (&)[kUnrollCu]) {
             int32_t v[kUnrollCu];
             uint32_t cand[kUnrollCu], dv[kUnrollCu];
 #pragma unroll
@@ -1720,7 +1746,7 @@ dawn_status ss_multi_run(const int32_t* rowptr, const int32_t* colidx, const voi
 
 Residency ss_persistent_residency(int threads) {
   if (threads <= 0) threads = 1024;
-  return residency_of(ss_persistent_kernel<kWU32>, threads);
+  return residency_of(ss_persistent_kernel<kWU32, false>, threads);
 }
 
 // Workgroups of a persistent launch.  A barrier costs 1.9 us with 64 and 3.3 us
@@ -1763,7 +1789,8 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     // one workgroup, one launch (after the optional device validation)
     if (T.validate) {
       hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
-                         (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, nullptr, nullptr, 0, nullptr, 0);
+                         (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, nullptr, nullptr, 0, nullptr, 0,
+                         A.n1);
       const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
       hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
                          A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
@@ -1787,7 +1814,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   }
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, rowptr, A.hv, A.t_lane, A.w,
-                     (int64_t)A.m);
+                     (int64_t)A.m, A.n1);
   if (T.validate) {
     const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
     hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
@@ -1812,7 +1839,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     if ((st = hip_check(hipGetLastError(), "step launches")) != DAWN_OK) return st;
   }
   {
-    const Residency r = residency_of(ss_persistent_kernel<WT>, threads);
+    const Residency r = residency_of(ss_persistent_kernel<WT, false>, threads);
     int grid = std::min(std::min(r.grid, kMaxGrid), ss_persistent_wgs(A.n, A.m, r.grid));
     if (T.grid > 0 && T.grid < grid) grid = T.grid;
     if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
@@ -1823,10 +1850,10 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     hipError_t e;
     void* tk = capture ? nullptr : ktimer_begin(stream);
     if (!capture && di.coop && T.coop) {
-      e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&ss_persistent_kernel<WT>),
+      e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&ss_persistent_kernel<WT, false>),
                                      dim3(grid), dim3(threads), args, 0, stream);
     } else {
-      hipLaunchKernelGGL(ss_persistent_kernel<WT>, dim3(grid), dim3(threads), 0, stream, a);
+      hipLaunchKernelGGL((ss_persistent_kernel<WT, false>), dim3(grid), dim3(threads), 0, stream, a);
       e = hipGetLastError();
     }
     ktimer_end(tk, stream, 1);
@@ -1842,6 +1869,146 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   return st;
 }
 
+// ---------------------------------------------------------------------------
+// a few sources on one graph: copies
+//
+// k sources run as one single-source run on k copies of the graph: vertex v of
+// source j has the id j * n + v in the distances (the [k x n] output itself),
+// the bitmaps and the queues, and the rows are read from the one CSR.  Every
+// step then serves all sources with one barrier, rows are deferred as in a
+// single-source run, and there is no tile to fill, scan or transpose.
+// ---------------------------------------------------------------------------
+// A source outside [0, n) ends the run before its first step (converged = -1),
+// as in a tile.
+template <int WT>
+__global__ void ss_copy_seed_kernel(SsArgs A, const int32_t* sources, int32_t count) {
+  SsCtl* C = A.ctl;
+  for (int j = threadIdx.x; j < count; j += blockDim.x) {
+    const int32_t s = sources[j];
+    if (s < 0 || s >= A.n1) {
+      st_agent_i(&C->converged, -1);
+      st_agent(&C->done, 1u);
+      continue;
+    }
+    const int32_t x = j * A.n1 + s;
+    A.dist[x] = zero_key<WT>();
+    atomicOr(&A.bm[0][x >> 5], 1u << (x & 31));
+    const int32_t start = A.rowptr[s], deg = A.rowptr[s + 1] - start;
+    if (deg <= A.t_lane) continue;
+    if (deg <= A.t_wave) {
+      A.qwave[0][atomicAdd(&C->cnt[0][1].v, 1u)] = x;
+    } else {
+      const uint32_t nch = (deg + A.t_chunk - 1) / A.t_chunk;
+      const uint32_t p = atomicAdd(&C->cnt[0][2].v, nch);
+      for (uint32_t c = 0; c < nch; c++) {
+        const int32_t off = (int32_t)c * A.t_chunk;
+        if (p + c < A.cap_wg)
+          A.qwg[0][p + c] = make_int4(x, start + off, min(A.t_chunk, deg - off), c == 0);
+      }
+    }
+  }
+}
+
+// Workspace of a run on copies: the queues hold each long row of each copy once
+// per step.
+static SsLayout ss_copies_layout(int64_t n, int64_t m, int64_t k) {
+  const Tuning& T = tuning();
+  SsLayout L{};
+  Carver c;
+  L.cap_v = (uint32_t)(k * std::min<int64_t>(n, m / (T.t_lane + 1)) + 1);
+  L.cap_wg = (uint32_t)(k * (m / (T.t_wave + 1) + m / T.t_chunk) + 1);
+  L.nwords = (k * n + 31) / 32;
+  L.ctl = c.take(sizeof(SsCtl));
+  for (int i = 0; i < 2; i++) L.qwave[i] = c.take((size_t)L.cap_v * 4);
+  for (int i = 0; i < 2; i++) L.qwg[i] = c.take((size_t)L.cap_wg * 16);
+  for (int i = 0; i < 2; i++) L.bm[i] = c.take((size_t)L.nwords * 4);
+  L.hv = c.take((size_t)L.nwords * 4);
+  L.total = c.off;
+  return L;
+}
+
+// The work of a run on copies grows with k; a tile reads each row once for all
+// its sources, but pays for whole 64-column rows and scans every vertex each
+// step.  Measured (copies / tile): grid 1000 x 1021 (4 edges per vertex), k = 8
+// 37.4 / 77.7 ms, k = 32 60.0 / 157.4 ms; ER n = 100,000 (8 per vertex), k = 8
+// 642 / 990 us, k = 32 1378 / 1416, k = 64 2265 / 1842; ER n = 1,000,000, k = 32
+// 10.0 / 11.4 ms (9.5 with a reverse graph); R-MAT (16 per vertex) scale 16,
+// k = 8 678 / 672 us, k = 16 948 / 751; scale 18, k = 8 1435 / 1541, k = 16 2441
+// / 1596.  Hop counts, whose tiles keep no distances: grid 500 x 500, k = 12
+// 12.9 / 25.9 ms; ER n = 300,000, k = 8 579 / 673 us, k = 32 1738 / 811; R-MAT
+// scale 18, k = 2 332 / 471, k = 8 656 / 523.
+static int ss_copies_most(int64_t n, int64_t m, bool unit) {
+  if (m < 6 * n) return 32;
+  if (m < 12 * n) return unit ? 8 : 24;
+  return unit ? 4 : 8;
+}
+
+bool ss_copies_fit(int64_t n, int64_t m, int32_t k, bool unit, size_t ws_bytes) {
+  const Tuning& T = tuning();
+  return T.mode == 0 && T.tile_step_launches > 0 && T.validate == 0 && k >= 2 &&
+         k <= ss_copies_most(n, m, unit) && n >= 1024 && k * n <= (int64_t)1 << 30 &&
+         ss_copies_layout(n, m, k).total <= ws_bytes;
+}
+
+template <int WT>
+static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int32_t* sources,
+                                   int32_t k, dawn_run_info* info, hipStream_t stream) {
+  const Tuning& T = tuning();
+  const int threads = T.wg_threads > 0 ? T.wg_threads : 1024;
+  const int fill_blocks = (int)std::min<int64_t>(4096, ((int64_t)A.n + 255) / 256 + 1);
+  hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
+                     (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, A.rowptr, A.hv, A.t_lane, A.w,
+                     (int64_t)A.m, A.n1);
+  hipLaunchKernelGGL(ss_copy_seed_kernel<WT>, dim3(1), dim3(64), 0, stream, A, sources, k);
+  const Residency r = residency_of(ss_persistent_kernel<WT, true>, threads);
+  int grid = std::min(std::min(r.grid, kMaxGrid),
+                      ss_persistent_wgs(A.n, (int64_t)k * A.m, r.grid));
+  if (T.grid > 0 && T.grid < grid) grid = T.grid;
+  void* tk = ktimer_begin(stream);
+  hipLaunchKernelGGL((ss_persistent_kernel<WT, true>), dim3(grid), dim3(threads), 0, stream, A);
+  ktimer_end(tk, stream, 1);
+  hipLaunchKernelGGL(ss_finalize_kernel<WT>, dim3(1), dim3(64), 0, stream, A.ctl, info, A.latch);
+  return hip_check(hipGetLastError(), "copies launch");
+}
+
+dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
+                          int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
+                          void* ws, dawn_run_info* info, hipStream_t stream) {
+  const Tuning& T = tuning();
+  const SsLayout L = ss_copies_layout(n, m, k);
+  char* base = static_cast<char*>(ws);
+  SsArgs A{};
+  A.rowptr = rowptr;
+  A.colidx = colidx;
+  A.w = static_cast<const uint32_t*>(w);
+  A.dist = static_cast<uint32_t*>(dist);
+  A.n = k * n;
+  A.n1 = n;
+  A.inv1 = (uint32_t)(((uint64_t)1 << 32) / (uint64_t)n);
+  A.nf_work = kNfWork * copies_work(k);
+  A.m = m;
+  A.src = -1;
+  A.skip = T.ss_skip;
+  A.pull_min = -1;
+  A.t_lane = T.t_lane;
+  A.t_wave = T.t_wave;
+  A.t_chunk = T.t_chunk;
+  for (int i = 0; i < 2; i++) {
+    A.qwave[i] = reinterpret_cast<int32_t*>(base + L.qwave[i]);
+    A.qwg[i] = reinterpret_cast<int4*>(base + L.qwg[i]);
+    A.bm[i] = reinterpret_cast<uint32_t*>(base + L.bm[i]);
+  }
+  A.hv = reinterpret_cast<uint32_t*>(base + L.hv);
+  A.cap_v = L.cap_v;
+  A.cap_wg = L.cap_wg;
+  A.ctl = reinterpret_cast<SsCtl*>(base + L.ctl);
+  A.bar_ticks = (unsigned long long)T.barrier_ms * kTicksPerMs;
+  A.latch = dev_info().latch;
+  if (wt == kWF32) return ss_copies_run_t<kWF32>(A, L, sources, k, info, stream);
+  if (wt == kWUNIT) return ss_copies_run_t<kWUNIT>(A, L, sources, k, info, stream);
+  return ss_copies_run_t<kWU32>(A, L, sources, k, info, stream);
+}
+
 dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
                    int32_t n, int32_t m, const SsSeeds& seeds, bool guard_source, void* dist,
                    void* ws, dawn_run_info* info, hipStream_t stream, bool capture,
@@ -1855,6 +2022,8 @@ dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, 
   A.w = static_cast<const uint32_t*>(w);
   A.dist = static_cast<uint32_t*>(dist);
   A.n = n;
+  A.n1 = n;
+  A.nf_work = kNfWork;
   A.m = m;
   A.src = guard_source ? seeds.source : -1;
   A.t_lane = T.t_lane;
