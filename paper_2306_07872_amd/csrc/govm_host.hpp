@@ -50,11 +50,20 @@ const DevInfo& dev_info();
 
 // Run-status latch of the current device: runs that are given no
 // dawn_run_info record here a status other than 1 (converged), for
-// dawn_run_status.  latch[0] counts such runs, latch[1] holds the last status.
+// dawn_run_status.  latch[0] counts such runs, latch[1] holds the last status;
+// latch[2..3] hold the device address of a word in host memory (or 0), set to 1
+// beside them: dawn_run_status reads that word and needs no copy from the device
+// when no run has failed.
 __device__ __forceinline__ void latch_status(uint32_t* latch, int32_t conv) {
   if (conv != 1 && latch) {
     atomicAdd(&latch[0], 1u);
     atomicExch(&latch[1], (uint32_t)conv);
+    __threadfence();
+    const unsigned long long p = __hip_atomic_load(
+        reinterpret_cast<unsigned long long*>(latch + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (p)
+      __hip_atomic_store(reinterpret_cast<uint32_t*>(p), 1u, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
