@@ -105,18 +105,19 @@ __device__ __forceinline__ void nf_advance(NfState& s, uint32_t M, float work, f
   s.thr = nf_threshold<WT>(M, s.delta);
 }
 
-// Samples of the weights (their mean) and of the row lengths (deferral only
-// where the mean length of an edge's row is at most four times the mean length
-// of a row).  One workgroup; the control block is zero before it.
+// The run's smallest delta, or 0 for no deferral: from samples of the weights
+// (their mean) and of the row lengths (deferral only where the mean length of an
+// edge's row is at most four times the mean length of a row).  Every thread of
+// the workgroup calls it and gets the result.
 template <int WT>
-__device__ void nf_init(SsCtl* ctl, int64_t n, int64_t m, const int32_t* rowptr,
-                        const uint32_t* w) {
-  if (threadIdx.x == 0) ctl->nf.thr = kNoKey;
-  if (!nf_weights<WT>() || !rowptr || !w || m < 1) return;
+__device__ float nf_floor(int64_t n, int64_t m, const int32_t* rowptr, const uint32_t* w,
+                          int samples) {
+  if (!nf_weights<WT>() || !rowptr || !w || m < 1) return 0.f;
   __shared__ float part[3][kMaxWavesPerBlock];
+  __shared__ float s_floor;
   float sw = 0.f, sd = 0.f, sd2 = 0.f;
-  const int64_t ew = m > kNfSamples ? m / kNfSamples : 1, rw = n > kNfSamples ? n / kNfSamples : 1;
-  const int ne = (int)(m < kNfSamples ? m : kNfSamples), nr = (int)(n < kNfSamples ? n : kNfSamples);
+  const int64_t ew = m > samples ? m / samples : 1, rw = n > samples ? n / samples : 1;
+  const int ne = (int)(m < samples ? m : samples), nr = (int)(n < samples ? n : samples);
 #pragma unroll 4
   for (int i = threadIdx.x; i < ne; i += blockDim.x)
     sw += WT == kWF32 ? __uint_as_float(w[i * ew]) : (float)w[i * ew];
@@ -138,17 +139,18 @@ __device__ void nf_init(SsCtl* ctl, int64_t n, int64_t m, const int32_t* rowptr,
     part[2][wv] = sd2;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  sw = sd = sd2 = 0.f;
-  for (int i = 0; i < (int)(blockDim.x / kWave); i++) {
-    sw += part[0][i];
-    sd += part[1][i];
-    sd2 += part[2][i];
+  if (threadIdx.x == 0) {
+    sw = sd = sd2 = 0.f;
+    for (int i = 0; i < (int)(blockDim.x / kWave); i++) {
+      sw += part[0][i];
+      sd += part[1][i];
+      sd2 += part[2][i];
+    }
+    // sd2 / sd <= 4 * sd / nr
+    s_floor = sd2 * nr <= 4.f * sd * sd ? fmaxf(kNfDelta * (sw / ne), 1e-30f) : 0.f;
   }
-  // sd2 / sd <= 4 * sd / nr
-  if (!(sd2 * nr <= 4.f * sd * sd)) return;
-  ctl->nf.floor = fmaxf(kNfDelta * (sw / ne), 1e-30f);
-  ctl->nf.delta = ctl->nf.floor;
+  __syncthreads();
+  return s_floor;
 }
 
 // ---------------------------------------------------------------------------
@@ -185,7 +187,8 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
     for (int i = threadIdx.x; i < (int)(offsetof(SsCtl, bar.slot) / 4); i += blockDim.x) c[i] = 0;
     __syncthreads();
     if (threadIdx.x < kRot) ctl->minp[threadIdx.x].v = kNoKey;
-    nf_init<WT>(ctl, n1, m, rowptr, w);
+    const float floor = nf_floor<WT>(n1, m, rowptr, w, kNfSamples);
+    if (threadIdx.x == 0) ctl->nf = NfState{kNoKey, floor, floor, 0u};
   }
 }
 
@@ -1303,6 +1306,13 @@ __device__ __forceinline__ uint32_t key_value(uint32_t key) {
 // second workgroup per compute unit.
 constexpr int kCuMidN = 16384, kCuMaxN = 32768;
 constexpr int kUnrollCu = 4;  // edges in flight per lane
+// Deferral here: edges per step that keep one compute unit busy, and the fewest
+// edges with which a run has such steps.  Below, tracking the smallest key only
+// costs (grid of 10,000 vertices, 39,212 edges: 365 -> 404 us).  Measured without
+// / with: ER n = 15,013, m = 120,104 195 / 170 us; n = 32,768, m = 262,144 366 /
+// 297 us, m = 131,072 275 / 277; grid of 32,761 vertices 1014 / 837 us.
+constexpr float kNfWorkCu = 1000.f;
+constexpr int kNfMinCu = 65536;
 constexpr int kCuWin = 1024;  // edges marked at a time (sized so that kCuMaxN fits)
 
 template <int N>
@@ -1319,6 +1329,7 @@ struct SsCuShared {
     unsigned long long part[kMaxWavesPerBlock][3];  // the report's sums, after the last step
   };
   uint32_t upd[3];
+  uint32_t minp[3], work[3];  // deferral: smallest key left in the frontier, edges expanded
 };
 static_assert(sizeof(SsCuShared<kCuMaxN>) <= 160 * 1024, "LDS of a compute unit");
 static_assert(sizeof(SsCuShared<kCuMidN>) <= 160 * 1024, "LDS of a compute unit");
@@ -1356,7 +1367,11 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
     }
     if constexpr (kRows)
       for (int i = threadIdx.x; i <= n; i += blockDim.x) sh.rp[i] = A.rowptr[i];
-    if (threadIdx.x < 3) sh.upd[threadIdx.x] = 0u;
+    if (threadIdx.x < 3) {
+      sh.upd[threadIdx.x] = 0u;
+      sh.minp[threadIdx.x] = kNoKey;
+      sh.work[threadIdx.x] = 0u;
+    }
     if (!MULTI && threadIdx.x == 0) {
       // the status words the report reads: the workspace may hold an earlier
       // run's (atomics, as the later reports are)
@@ -1364,6 +1379,11 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
       atomicExch(&C->abort, 0u);
       atomicExch(&C->overflow, 0u);
     }
+    // far rows wait, as in the multi-workgroup runs
+    const float floor =
+        A.m >= kNfMinCu ? nf_floor<WT>(n, A.m, A.rowptr, A.w, 1024) : 0.f;
+    NfState nf{kNoKey, floor, floor, 0u};
+    const bool near = nf_weights<WT>() && floor != 0.f;
     __syncthreads();
     if constexpr (MULTI) {
       if (threadIdx.x == 0) {
@@ -1384,6 +1404,7 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
       uint32_t* bc = sh.bm[step & 1];
       uint32_t* bn = sh.bm[(step & 1) ^ 1];
       bool upd = false;
+      StepSeen seen;
       // wavefront w scans words w, w + W, ..., up to 64 of them at a time (one
       // pass at 1024 threads): a frontier band is shared by all wavefronts, and
       // a wavefront's rows wait for one chain of loads per 64 of them
@@ -1407,10 +1428,16 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
               deg = A.rowptr[u + 1] - start;
             }
             du = sh.dist[u];
+            if (near && du > nf.thr) {
+              atomicOr(&bn[u >> 5], 1u << (u & 31));
+              seen.minp = min(seen.minp, du);
+              deg = 0;
+            }
             if (deg > 0) acc.fe += 1;  // a frontier row (rows without edges are not counted)
             // lowered again in this step: expanded in the next, with the lower value
             if (A.skip && ((bn[u >> 5] >> (u & 31)) & 1u)) deg = 0;
             acc.es += (unsigned long long)deg;
+            seen.work += (uint32_t)deg;
           }
           deal_rows<kUnrollCu>(st.rows, start, deg, du, 0, [&](const int32_t (&e)[kUnrollCu],
                                                                const bool (&ok)[kUnrollCu],
@@ -1437,6 +1464,7 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
                   cand[j] < atomicMin(&sh.dist[v[j]], cand[j])) {
                 acc.im += 1;
                 upd = true;
+                seen.minp = min(seen.minp, cand[j]);
                 __hip_atomic_fetch_or(&bn[v[j] >> 5], 1u << (v[j] & 31), __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_WORKGROUP);
               }
@@ -1446,10 +1474,27 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
       }
       // three flags rotate: step t sets (t+1) mod 3, read after the barrier,
       // and clears (t+2) mod 3, which nothing else touches before step t+1 ends
-      if (threadIdx.x == 0) sh.upd[(step + 2) % 3] = 0u;
-      if (upd) sh.upd[(step + 1) % 3] = 1u;
+      if (threadIdx.x == 0) {
+        sh.upd[(step + 2) % 3] = 0u;
+        sh.minp[(step + 2) % 3] = kNoKey;
+        sh.work[(step + 2) % 3] = 0u;
+      }
+      if (near) {
+        const uint32_t mp = wave_min(seen.minp), wk = (uint32_t)wave_incl_scan((int)seen.work);
+        if (lane == kWave - 1) {
+          if (mp != kNoKey) atomicMin(&sh.minp[(step + 1) % 3], mp);
+          if (wk) atomicAdd(&sh.work[(step + 1) % 3], wk);
+        }
+      } else if (upd) {
+        sh.upd[(step + 1) % 3] = 1u;
+      }
       __syncthreads();
-      const uint32_t more = sh.upd[(step + 1) % 3];
+      uint32_t more = sh.upd[(step + 1) % 3];
+      if (near) {
+        const uint32_t mp = sh.minp[(step + 1) % 3];
+        more = mp != kNoKey;
+        nf_advance<WT>(nf, mp, (float)sh.work[(step + 1) % 3], kNfWorkCu);
+      }
       step++;
       if (!more) { status = 1; break; }
       if (step >= (uint32_t)n) { status = 0; break; }

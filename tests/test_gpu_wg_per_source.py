@@ -95,3 +95,17 @@ def test_source_out_of_range_is_reported(dawn, n, m):
         info = dawn.info_tensor()
         dawn.msssp(csr, np.array([3, bad, 5], np.int32), info=info, check=False)
         assert dawn.read_info(info)["converged"] == -1
+
+
+@pytest.mark.parametrize("wk", ["u32", "f32unit"])
+def test_far_rows_wait(dawn, wk):
+    """Even graphs with enough edges that steps leave far rows for later."""
+    for g in (graphgen.er(9001, 70001, 3, weights=wk), graphgen.grid(150, 151, 0.01, 5, weights=wk),
+              graphgen.er(32768, 131072, 4, weights=wk)):
+        csr = dawn.Csr.from_graph(g)
+        srcs = graphgen.pick_sources(g, 3, 8)
+        announce("workgroup per source, far rows", g.name, wk)
+        D = to_np(dawn.msssp(csr, srcs))
+        for j, s in enumerate(srcs):
+            assert_sssp_matches(g, int(s), D[j], tag=f"{g.name} {wk} col {j}")
+            assert np.array_equal(to_np(dawn.sssp(csr, int(s))).view(np.uint32), D[j].view(np.uint32))
