@@ -187,9 +187,10 @@ typedef struct {
                            already lowered again in the same step is not expanded (it is
                            expanded next step with the lower value); 0 (default): every
                            pair of the frontier is expanded, as Algorithm 2 states */
-  int32_t small_m;      /* single-source and batch runs with mode 0 and m <= small_m run in
-                           one workgroup, one launch (no grid barrier); default 131072,
-                           0 = never */
+  int32_t small_m;      /* single-source and batch runs with mode 0, m <= small_m and
+                           n <= 32768 run in one workgroup, one launch (no grid barrier);
+                           multi-source calls on such graphs in one workgroup per source;
+                           default 131072, 0 = never */
   int32_t step_min_m;   /* mode 0: graphs with at least this many edges start with step
                            launches (see mode); default INT32_MAX: none do, except
                            runs with pull steps from 1 << 25 edges on */

@@ -78,6 +78,36 @@ const DevInfo& dev_info() {
   return di;
 }
 
+bool stream_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
+
+// One event per device, created by its first gated launch and kept until the
+// process ends.
+static std::mutex g_gate_mu[64];
+static hipEvent_t g_gate[64];
+
+PersistentGate::PersistentGate(hipStream_t s, int grid)
+    : stream(s), on(grid > 1 && !stream_capturing(s)) {
+  if (!on) return;
+  const int d = dev_info().device;
+  g_gate_mu[d].lock();
+  if (g_gate[d]) {
+    hipStreamWaitEvent(stream, g_gate[d], 0);
+  } else if (hipEventCreateWithFlags(&g_gate[d], hipEventDisableTiming) != hipSuccess) {
+    g_gate[d] = nullptr;
+    (void)hipGetLastError();
+  }
+}
+
+PersistentGate::~PersistentGate() {
+  if (!on) return;
+  const int d = dev_info().device;
+  if (g_gate[d]) hipEventRecord(g_gate[d], stream);
+  g_gate_mu[d].unlock();
+}
+
 // Residency rule of a gfx950 compute unit: 4 SIMDs, each with 512 VGPRs per
 // lane for wave64 (allocated in granules of 8) and at most 8 waves, and 160 KiB
 // of LDS shared by the CU's workgroups; a workgroup's waves are spread evenly
@@ -525,7 +555,9 @@ static dawn_status msssp_impl(const int32_t* rowptr, const int32_t* colidx, cons
                         sources, k, dist_out, info, stream);
   const int32_t kt = std::min(k, g_tuning.tile_k);
   const TileLayout L = tile_layout(n, m, kt, unweighted);
-  if (ss_copies_fit(n, m, k, unweighted, L.total))
+  // (Not in a captured call: its replays on several streams would be persistent
+  // launches that nothing orders.)
+  if (ss_copies_fit(n, m, k, unweighted, L.total) && !stream_capturing(stream))
     return ss_copies_run(rowptr, colidx, weights, unweighted ? kWUNIT : f32 ? kWF32 : kWU32, n, m,
                          sources, k, dist_out, ws, info, stream);
   TileArgs A = tile_args(rowptr, colidx, weights, n, m, L, ws);

@@ -580,7 +580,6 @@ struct SsArgs {
   long long pull_min;     // pull when the frontier has >= this many out-edges; < 0: never
   bool counted;           // the step launches before have counted the frontier they left
   int32_t t_lane, t_wave, t_chunk;
-  int32_t* qlane[2];      // delta of one-workgroup runs [step % 2]
   int32_t* qwave[2];      // delta, wave tier
   int4* qwg[2];           // delta, workgroup tier: {row, first edge, edges, first chunk?}
   uint32_t* bm[2];        // beta dedup bitmaps [step % 2]

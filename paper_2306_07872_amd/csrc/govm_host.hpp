@@ -48,6 +48,22 @@ struct DevInfo {
 };
 const DevInfo& dev_info();
 
+// Orders persistent launches of one device.  Workgroups of a persistent launch
+// wait for each other at grid barriers, so two such launches on different
+// streams that each got some of the compute units would wait until their
+// barriers give up.  Held around a launch, the gate makes the stream wait for
+// the last persistent launch on any stream and records the new one.  A stream
+// that is being captured is left alone (events from outside would end the
+// capture).
+struct PersistentGate {
+  hipStream_t stream;
+  bool on;
+  PersistentGate(hipStream_t s, int grid);
+  ~PersistentGate();
+};
+// Whether `stream` is being captured into a graph.
+bool stream_capturing(hipStream_t stream);
+
 // Run-status latch of the current device: runs that are given no
 // dawn_run_info record here a status other than 1 (converged), for
 // dawn_run_status.  latch[0] counts such runs, latch[1] holds the last status;
@@ -113,7 +129,7 @@ struct Carver {
 
 // ----- single source ---------------------------------------------------------
 struct SsLayout {
-  size_t ctl, qlane[2], qwave[2], qwg[2], bm[2], hv, total;
+  size_t ctl, qwave[2], qwg[2], bm[2], hv, total;
   uint32_t cap_v, cap_wg;
   int64_t nwords;
 };

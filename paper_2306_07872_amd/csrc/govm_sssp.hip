@@ -490,34 +490,6 @@ __device__ __forceinline__ void ss_enqueue(const SsArgs& A, const bool (&imp)[U]
     ss_queue_row(A, newv[i] && deg[i] > A.t_lane, v[i], start[i], deg[i], nxt, rn, sh);
 }
 
-// Relax U edges per lane: all column/weight loads, then all target-distance
-// loads, then the atomic mins of the lanes whose candidate is smaller.
-template <int WT, int U>
-__device__ __forceinline__ void ss_relax_n(const SsArgs& A, const int32_t (&e)[U],
-                                           const bool (&valid)[U], const uint32_t (&du)[U],
-                                           bool (&imp)[U], int32_t (&v)[U]) {
-  uint32_t cand[U];
-#pragma unroll
-  for (int i = 0; i < U; i++) {
-    v[i] = 0;
-    cand[i] = 0u;
-    if (valid[i]) {
-      v[i] = A.colidx[e[i]];
-      cand[i] = relax_key<WT>(du[i], WT == kWUNIT ? 1u : A.w[e[i]]);
-      if constexpr (WT == kWI32)
-        if (cand[i] == 0u) atomicOr(&A.ctl->negfloor, 1u);  // sum left the int32 range
-    }
-  }
-  uint32_t cur[U];
-#pragma unroll
-  for (int i = 0; i < U; i++) cur[i] = valid[i] ? A.dist[v[i]] : 0u;
-#pragma unroll
-  for (int i = 0; i < U; i++) {
-    imp[i] = false;
-    if (valid[i] && cand[i] < cur[i] && v[i] != A.src) imp[i] = cand[i] < atomicMin(&A.dist[v[i]], cand[i]);
-  }
-}
-
 // Candidates and the plain-load pre-check only, for ss_enqueue: it issues the
 // next-frontier test-and-set first and the non-returning atomicMin after it,
 // so waiting for the test-and-set does not wait for the atomicMin too (gfx9's
@@ -1059,151 +1031,6 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
 }
 
 // ---------------------------------------------------------------------------
-// small graphs: one workgroup runs the whole loop
-//
-// When the edge list is short, a step's work is a few microseconds and the
-// grid barrier between steps (device-scope fences over the L2s of all XCDs)
-// would dominate.  One workgroup then runs init, seeding and every step in a
-// single launch, with a workgroup barrier between steps.  delta is one queue:
-// each wavefront takes 64 rows and deals their edges out to its lanes through
-// an LDS prefix sum of the row lengths (the lane tier's scheme, any degree).
-// Data that one step writes and a later step reads (distances, the beta
-// bitmaps, queue entries) go through device-scope atomics, as in the other
-// kernels; the queue length and the ptr flag live in LDS.
-// ---------------------------------------------------------------------------
-struct SsSmallShared {
-  DealRows<4096> rows[kMaxWavesPerBlock];
-  uint32_t cnt_next, upd;
-};
-
-template <int WT>
-__global__ void __launch_bounds__(1024) ss_small_kernel(SsArgs A, const int32_t* sources,
-                                                        const int64_t* voff, int32_t count,
-                                                        int32_t single, int32_t check_valid,
-                                                        dawn_run_info* info) {
-  __shared__ SsSmallShared sh;
-  SsCtl* C = A.ctl;
-  const int lane = lane_id(), wave = threadIdx.x >> 6, W = blockDim.x >> 6;
-  const int64_t n = A.n, nwords = (n + 31) / 32;
-  uint32_t step = 0;
-  int32_t status = 1;
-  Acc acc;
-  if (check_valid && ld_agent(&C->done)) {
-    status = -1;
-  } else {
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) A.dist[i] = inf_key<WT>();
-    for (int64_t i = threadIdx.x; i < nwords; i += blockDim.x) {
-      A.bm[0][i] = 0u;
-      A.bm[1][i] = 0u;
-    }
-    if (threadIdx.x == 0) {
-      sh.cnt_next = 0u;
-      sh.upd = 0u;
-      // the status words the report reads: the workspace may hold an earlier
-      // run's (atomics, as the later reports are)
-      atomicExch(&C->negfloor, 0u);
-      atomicExch(&C->abort, 0u);
-      atomicExch(&C->overflow, 0u);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    // seeds: alpha = 0, queued once (a repeated seed finds its bit set)
-    for (int j = threadIdx.x; j < count; j += blockDim.x) {
-      int64_t s = sources ? (int64_t)sources[j] : (int64_t)single;
-      if (voff) s += voff[j];
-      st_agent(&A.dist[s], zero_key<WT>());
-      const uint32_t bit = 1u << (s & 31);
-      if (atomicOr(&A.bm[0][s >> 5], bit) & bit) continue;
-      st_agent_i(&A.qlane[0][atomicAdd(&sh.cnt_next, 1u)], (int32_t)s);
-    }
-    __syncthreads();
-    uint32_t cnt = sh.cnt_next;
-    __syncthreads();
-    if (threadIdx.x == 0) sh.cnt_next = 0u;
-    __syncthreads();
-    for (;;) {
-      const int cur = step & 1, nxt = cur ^ 1;
-      for (uint32_t bi = wave; (uint64_t)bi * kWave < cnt; bi += W) {
-        const uint32_t i = bi * kWave + lane;
-        int32_t u = 0, start = 0, deg = 0;
-        uint32_t du = 0;
-        if (i < cnt) {
-          u = ld_queue(&A.qlane[cur][i]);
-          start = A.rowptr[u];
-          deg = A.rowptr[u + 1] - start;
-          du = ld_agent(&A.dist[u]);
-          st_agent(&A.bm[cur][u >> 5], 0u);
-          if (deg > 0) {
-            acc.fe += 1;
-            acc.es += (unsigned long long)deg;
-          }
-        }
-        deal_rows<kUnrollLane>(sh.rows[wave], start, deg, du, 0, [&](const int32_t (&e)[kUnrollLane],
-                                                                     const bool (&ok)[kUnrollLane],
-                                                                     const uint32_t (&d)[kUnrollLane],
-                                                                     const int32_t (&)[kUnrollLane]) {
-          int32_t v[kUnrollLane];
-          bool imp[kUnrollLane];
-          ss_relax_n<WT, kUnrollLane>(A, e, ok, d, imp, v);
-#pragma unroll
-          for (int j = 0; j < kUnrollLane; j++) {
-            bool newv = false;
-            if (imp[j]) {
-              acc.im += 1;
-              sh.upd = 1u;
-              const uint32_t bit = 1u << (v[j] & 31);
-              newv = (atomicOr(&A.bm[nxt][v[j] >> 5], bit) & bit) == 0u;
-            }
-            const unsigned long long b = __ballot(newv);
-            if (b != 0ull) {
-              const int leader = __ffsll((long long)b) - 1;
-              uint32_t pos = 0;
-              if (lane == leader) pos = atomicAdd(&sh.cnt_next, (uint32_t)__popcll(b));
-              pos = __shfl(pos, leader, kWave) + lanes_below(b);
-              if (newv) {
-                if (pos < A.cap_v) st_agent_i(&A.qlane[nxt][pos], v[j]);
-                else atomicOr(&C->overflow, 1u);
-              }
-            }
-          }
-        });
-      }
-      __syncthreads();
-      const uint32_t upd = sh.upd, cn = min(sh.cnt_next, A.cap_v);
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        sh.upd = 0u;
-        sh.cnt_next = 0u;
-      }
-      __syncthreads();
-      step++;
-      cnt = cn;
-      if (!upd) { status = 1; break; }
-      if (step >= (uint32_t)A.n) { status = 0; break; }
-    }
-  }
-  // counters, state and run info
-  // thread i zeroes the counter that it then adds to (flush_acc: fe, es, im)
-  SsCounters& S = C->ctr;
-  if (threadIdx.x == 0) st_agent64(&S.fe, 0ull);
-  if (threadIdx.x == 1) st_agent64(&S.es, 0ull);
-  if (threadIdx.x == 2) st_agent64(&S.im, 0ull);
-  flush_acc(acc, &S.fe, &S.es, &S.im, nullptr, nullptr);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (status != -1) {
-      st_agent(&C->step, step);
-      st_agent_i(&C->converged, status);
-      st_agent(&C->done, 1u);
-    }
-    ss_report<WT>(C, info, A.latch);
-  }
-}
-
-// ---------------------------------------------------------------------------
 // one workgroup per source: the run's state in LDS
 //
 // With n <= kCuMaxN the distances and both beta bitmaps of a run fit in one
@@ -1718,9 +1545,6 @@ SsLayout ss_layout(int64_t n, int64_t m) {
   L.nwords = (n + 31) / 32;
   L.ctl = c.take(sizeof(SsCtl));
   for (int i = 0; i < 2; i++) L.qwave[i] = c.take((size_t)n * 4);
-  // The one-workgroup kernel's queues share the wave-tier queues' memory: a
-  // one-workgroup run has no wave tier, and the other runs queue no short rows.
-  for (int i = 0; i < 2; i++) L.qlane[i] = L.qwave[i];
   for (int i = 0; i < 2; i++) L.qwg[i] = c.take((size_t)L.cap_wg * 16);
   for (int i = 0; i < 2; i++) L.bm[i] = c.take((size_t)L.nwords * 4);
   L.hv = c.take((size_t)L.nwords * 4);
@@ -1823,10 +1647,16 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   // scale 22 2.21 / 2.55 ms, scale 20 0.81 / 0.99 ms, 64 ER graphs (118M edges)
   // 5.74 / 6.10 ms, the 2048^2 grid 43.4 / 47.2 ms.
   int mode = T.mode;
-  // (Pull steps need step launches: large graphs with a reverse graph keep them.)
-  if (mode == 0) mode = (int64_t)A.m <= (int64_t)T.small_m ? 3
+  // (Pull steps need step launches: large graphs with a reverse graph keep them.
+  // So do captured runs, whose replays on several streams would else be
+  // persistent launches that nothing orders.)
+  // One workgroup only where its LDS holds the run: past that, a kernel with the
+  // state in global memory took 1606 us on an ER graph of 60,000 vertices and
+  // 120,000 edges, the persistent launch 404 us.
+  if (mode == 0) mode = (int64_t)A.m <= (int64_t)T.small_m && A.n <= kCuMaxN ? 3
                         : (int64_t)A.m >= (int64_t)T.step_min_m ||
-                          (A.pull_min >= 0 && A.m >= 1 << 25) ? 1 : 2;
+                          ((A.pull_min >= 0 || stream_capturing(stream)) && A.m >= 1 << 25)
+                            ? 1 : 2;
   const int threads = T.wg_threads > 0 ? T.wg_threads : mode == 1 ? 512 : 1024;
   const int fill_blocks = (int)std::min<int64_t>(4096, (A.n + 255) / 256 + 1);
   dawn_status st;
@@ -1841,20 +1671,11 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
                          A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
     }
     void* tk = capture ? nullptr : ktimer_begin(stream);
-    const bool in_lds = A.n <= kCuMaxN;
-    if (in_lds)
-      hipLaunchKernelGGL((ss_wg_kernel<WT, false>(A.n, A.m)), dim3(1),
-                         dim3(ss_wg_whole(A.n, A.m) ? kLdsThreads : threads), 0, stream, A,
-                         seeds.sources_dev, seeds.voff_dev, seeds.count, seeds.source,
-                         (int32_t)(T.validate != 0), info);
-    else
-      hipLaunchKernelGGL(ss_small_kernel<WT>, dim3(1), dim3(threads), 0, stream, A,
-                         seeds.sources_dev, seeds.voff_dev, seeds.count, seeds.source,
-                         (int32_t)(T.validate != 0), info);
+    hipLaunchKernelGGL((ss_wg_kernel<WT, false>(A.n, A.m)), dim3(1),
+                       dim3(ss_wg_whole(A.n, A.m) ? kLdsThreads : threads), 0, stream, A,
+                       seeds.sources_dev, seeds.voff_dev, seeds.count, seeds.source,
+                       (int32_t)(T.validate != 0), info);
     ktimer_end(tk, stream, 1);
-    if (WT == kWI32 && !in_lds)
-      hipLaunchKernelGGL(ss_decode_i32_kernel, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
-                         (int64_t)A.n);
     return hip_check(hipGetLastError(), "small-graph launch");
   }
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
@@ -1893,6 +1714,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     a.pull_min = -1;  // pull steps need step launches (the last workgroup clears the bitmap)
     void* args[] = {&a};
     hipError_t e;
+    const PersistentGate gate(stream, grid);
     void* tk = capture ? nullptr : ktimer_begin(stream);
     if (!capture && di.coop && T.coop) {
       e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&ss_persistent_kernel<WT, false>),
@@ -2009,6 +1831,7 @@ static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int
   int grid = std::min(std::min(r.grid, kMaxGrid),
                       ss_persistent_wgs(A.n, (int64_t)k * A.m, r.grid));
   if (T.grid > 0 && T.grid < grid) grid = T.grid;
+  const PersistentGate gate(stream, grid);
   void* tk = ktimer_begin(stream);
   hipLaunchKernelGGL((ss_persistent_kernel<WT, true>), dim3(grid), dim3(threads), 0, stream, A);
   ktimer_end(tk, stream, 1);
@@ -2082,7 +1905,6 @@ dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, 
   A.t_wave = T.t_wave;
   A.t_chunk = T.t_chunk;
   for (int i = 0; i < 2; i++) {
-    A.qlane[i] = reinterpret_cast<int32_t*>(base + L.qlane[i]);
     A.qwave[i] = reinterpret_cast<int32_t*>(base + L.qwave[i]);
     A.qwg[i] = reinterpret_cast<int4*>(base + L.qwg[i]);
     A.bm[i] = reinterpret_cast<uint32_t*>(base + L.bm[i]);

@@ -1615,9 +1615,8 @@ template <typename K, typename... Args>
 static hipError_t launch_persistent(K kernel, int grid, int threads, hipStream_t stream,
                                     Args... args) {
   const Tuning& T = tuning();
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  const bool capturing =
-      hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+  const bool capturing = stream_capturing(stream);
+  const PersistentGate gate(stream, grid);
   if (dev_info().coop && T.coop && !capturing) {
     void* ptrs[] = {&args...};
     return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(kernel), dim3(grid),

@@ -105,3 +105,31 @@ def test_source_out_of_range_is_reported(dawn):
         with pytest.raises(dawn.DawnError) as e:
             dawn.msssp(csr, np.array([3, bad, 5], np.int32))
         assert e.value.status == dawn.E_INCOMPLETE and "-1" in str(e.value)
+
+
+def test_persistent_runs_on_two_streams(dawn):
+    """Single-source and few-source runs whose launches hold a grid barrier, put
+    on two streams by turns with nothing ordering them: all converge."""
+    import torch
+    g = graphgen.grid(300, 301, 0.01, 12, weights="f32unit")
+    h = graphgen.rmat(15, 16, 13, weights="u32")
+    cg, ch = dawn.Csr.from_graph(g), dawn.Csr.from_graph(h)
+    sg, sh = graphgen.pick_sources(g, 4, 2), graphgen.pick_sources(h, 4, 3)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    src = [torch.as_tensor(x[:3].copy(), dtype=torch.int32, device="cuda") for x in (sg, sh)]
+    ws = [dawn.workspace(dawn.msssp_workspace_bytes(c.n, c.m, 3)) for c in (cg, ch)]
+    out = [torch.empty((3, c.n), dtype=dawn.dist_dtype(c.wtype), device="cuda") for c in (cg, ch)]
+    one = [torch.empty(c.n, dtype=dawn.dist_dtype(c.wtype), device="cuda") for c in (cg, ch)]
+    torch.cuda.synchronize()
+    announce("two streams of persistent runs")
+    for rep in range(6):
+        for i, (c, s) in enumerate(((cg, sg), (ch, sh))):
+            with torch.cuda.stream(streams[i]):
+                dawn.msssp(c, src[i], out=out[i], ws=ws[i], stream=streams[i], check=False)
+                dawn.sssp(c, int(s[3]), out=one[i], stream=streams[i], check=False)
+    torch.cuda.synchronize()
+    assert dawn.run_status() == (0, 1)
+    for i, (gr, s) in enumerate(((g, sg), (h, sh))):
+        for j in range(3):
+            assert_sssp_matches(gr, int(s[j]), to_np(out[i])[j], tag="two streams", check_invariants=False)
+        assert_sssp_matches(gr, int(s[3]), to_np(one[i]), tag="two streams", check_invariants=False)
