@@ -141,6 +141,9 @@ typedef struct {
  *   wave tier      d <= t_wave   one wavefront per row (t_wave >= 64);
  *   workgroup tier d >  t_wave   the row is cut into chunks of t_chunk edges,
  *                                one workgroup per chunk.
+ * A persistent launch cuts long rows finer than step launches do: its wave tier
+ * ends at three eighths of t_wave (at least t_lane), its chunks hold a quarter of
+ * t_chunk edges (at least 256).
  * mode: how the step loop (Algorithm 2's `while`) is launched.  No mode waits
  * on the host: a run is a fixed launch sequence, and a launch that finds the
  * run already ended returns at once.

@@ -185,8 +185,9 @@ dawn_status tile_reset(const TileArgs& a, bool f32, hipStream_t stream);
 // Seed columns [0, count) with sources_dev (msssp), on a freshly reset tile.
 dawn_status tile_seed_all(const TileArgs& a, const int32_t* sources_dev, int32_t count,
                           bool validate, bool f32, hipStream_t stream);
-// Admit one query into column col (between steps).
-dawn_status tile_admit(const TileArgs& a, bool f32, int32_t col, int32_t source,
+// Admit one query into column col (between steps); clean: the column's distances
+// are INF already.
+dawn_status tile_admit(const TileArgs& a, bool f32, int32_t col, int32_t source, bool clean,
                        hipStream_t stream);
 dawn_status tile_evict(const TileArgs& a, bool f32, int32_t col, hipStream_t stream);
 // Run steps: persistent (all until done) or `max_steps` step launches.

@@ -1635,6 +1635,19 @@ static int ss_persistent_wgs(int64_t n, int64_t m, int resident) {
   return std::min(wgs, resident);
 }
 
+// Tier bounds of persistent launches, relative to the tuning's (which are those of
+// step launches, with twice the wavefronts per compute unit): a step waits for
+// its slowest wavefront, so long rows are cut finer.  Measured at 2048 / 8192
+// (wave-tier rows, chunk) against 768 / 2048: R-MAT scale 16 432 / 310 us, 17
+// 690 / 508, 18 (int32) 643 / 542, 19 662 / 512, 20 809 / 797, 21 1396 / 1335,
+// 22 2233 / 2035, 22 hop counts 1074 / 953; 2048 / 2048 gives 409 us and 657 us
+// at scales 16 and 19, 512 / 1024 2271 us at 22.
+static void ss_persistent_tiers(SsArgs& A) {
+  const Tuning& T = tuning();
+  A.t_wave = std::max(std::max(64, T.t_lane), T.t_wave * 3 / 8);
+  A.t_chunk = std::max(256, T.t_chunk / 4);
+}
+
 template <int WT>
 static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_t* colidx,
                             const SsSeeds& seeds, const SsLayout& L, dawn_run_info* info,
@@ -1711,6 +1724,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
     SsArgs a = A;
     a.counted = mode == 1 && A.pull_min >= 0;
+    ss_persistent_tiers(a);
     a.pull_min = -1;  // pull steps need step launches (the last workgroup clears the bitmap)
     void* args[] = {&a};
     hipError_t e;
@@ -1783,7 +1797,9 @@ static SsLayout ss_copies_layout(int64_t n, int64_t m, int64_t k) {
   SsLayout L{};
   Carver c;
   L.cap_v = (uint32_t)(k * std::min<int64_t>(n, m / (T.t_lane + 1)) + 1);
-  L.cap_wg = (uint32_t)(k * (m / (T.t_wave + 1) + m / T.t_chunk) + 1);
+  SsArgs A{};
+  ss_persistent_tiers(A);
+  L.cap_wg = (uint32_t)(k * (m / (A.t_wave + 1) + m / A.t_chunk) + 1);
   L.nwords = (k * n + 31) / 32;
   L.ctl = c.take(sizeof(SsCtl));
   for (int i = 0; i < 2; i++) L.qwave[i] = c.take((size_t)L.cap_v * 4);
@@ -1859,8 +1875,7 @@ dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const vo
   A.skip = T.ss_skip;
   A.pull_min = -1;
   A.t_lane = T.t_lane;
-  A.t_wave = T.t_wave;
-  A.t_chunk = T.t_chunk;
+  ss_persistent_tiers(A);
   for (int i = 0; i < 2; i++) {
     A.qwave[i] = reinterpret_cast<int32_t*>(base + L.qwave[i]);
     A.qwg[i] = reinterpret_cast<int4*>(base + L.qwg[i]);

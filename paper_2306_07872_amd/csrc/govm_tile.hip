@@ -1582,11 +1582,13 @@ dawn_status tile_seed_all(const TileArgs& a, const int32_t* sources_dev, int32_t
   return hip_check(hipGetLastError(), "tile seed");
 }
 
-dawn_status tile_admit(const TileArgs& a, bool f32, int32_t col, int32_t source,
+dawn_status tile_admit(const TileArgs& a, bool f32, int32_t col, int32_t source, bool clean,
                        hipStream_t stream) {
   const int g = grid_for(a.n, 256);
-  if (f32) hipLaunchKernelGGL(tile_col_fill_kernel<true>, dim3(g), dim3(256), 0, stream, a, col);
-  else hipLaunchKernelGGL(tile_col_fill_kernel<false>, dim3(g), dim3(256), 0, stream, a, col);
+  if (!clean && f32)
+    hipLaunchKernelGGL(tile_col_fill_kernel<true>, dim3(g), dim3(256), 0, stream, a, col);
+  else if (!clean)
+    hipLaunchKernelGGL(tile_col_fill_kernel<false>, dim3(g), dim3(256), 0, stream, a, col);
   hipLaunchKernelGGL(tile_admit_kernel, dim3(1), dim3(64), 0, stream, a, col, source);
   return hip_check(hipGetLastError(), "tile admit");
 }
