@@ -309,9 +309,9 @@ def main() -> int:
     if tune["mode"] == 2:
         kname = "tile_persistent_kernel<false>"
     elif tg is not None:
-        kname = "tile relaxation: tile_step_kernel<false> (push steps) + tile_pull_kernel<false> (pull steps)"
+        kname = "tile relaxation: tile_step_kernel<false, true> (push and pull steps)"
     else:
-        kname = "tile_step_kernel<false>"
+        kname = "tile_step_kernel<false, false>"
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": measured_traffic(tune, f"rmat{args.scale}_ef16_u32_k{k}"),

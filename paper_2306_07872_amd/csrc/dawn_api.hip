@@ -569,8 +569,11 @@ static dawn_status msssp_impl(const int32_t* rowptr, const int32_t* colidx, cons
   // per-tile summary, inside the workspace (no allocation on this path)
   dawn_run_info* part = reinterpret_cast<dawn_run_info*>(static_cast<char*>(ws) + L.info);
   dawn_status st;
-  const int32_t launches =
+  int32_t launches =
       g_tuning.mode == 2 ? 0 : (int32_t)std::min<int64_t>(g_tuning.tile_step_launches, (int64_t)n + 1);
+  // hop counts on graphs of many edges per vertex: the dense steps are over by
+  // then, and a spare step costs two launches (9 us)
+  if (unweighted && g_tuning.mode == 0 && m >= 12 * (int64_t)n) launches = std::min(launches, 10);
   for (int32_t j0 = 0; j0 < k; j0 += kt) {
     const int32_t cnt = std::min(kt, k - j0);
     if ((st = tile_reset(A, f32, stream)) != DAWN_OK) return st;

@@ -98,7 +98,6 @@ struct alignas(256) TileCtl {
   uint32_t step, done;
   int32_t converged;
   uint32_t abort, overflow, bar_base;
-  uint32_t cstep;                      // the step whose compaction ran last
   GridBar bar;
   LineU32 arrive;                      // last-block detection of step launches
   LineU32 cnt[kRot][4];                // [step % 4][tier]: group, wave, workgroup-chunk
@@ -452,20 +451,20 @@ __device__ __forceinline__ bool grid_sync(GridBar* bar, uint32_t* abort_flag, ui
 }
 
 // Last-block detection for step launches: returns true in every thread of
-// the workgroup that arrives last, once all other workgroups' write-through
+// the workgroup that arrives last of nb, once all other workgroups' write-through
 // stores and atomics are visible to it, and leaves the arrival word at zero
 // for the next launch.  (Plain stores are not: the kernel's end writes those
 // back for the next launch.)  Every thread must call it.  (Arrivals in two
 // levels, over striped words, measured no faster: a step's workgroups do not
 // finish all at once.)
-__device__ __forceinline__ bool last_block_arrive(LineU32* arrive) {
+__device__ __forceinline__ bool last_block_arrive(LineU32* arrive, uint32_t nb) {
   __shared__ int s_last;
   wait_own_stores();
   __syncthreads();
   if (threadIdx.x == 0) {
     int last = 0;
     if (__hip_atomic_fetch_add(&arrive->v, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-        gridDim.x - 1) {
+        nb - 1) {
       st_agent(&arrive->v, 0u);
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       last = 1;

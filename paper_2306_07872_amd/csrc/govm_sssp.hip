@@ -1003,7 +1003,7 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
   // counters, and the next frontier's out-edges and rows (its pull decision)
   SsCounters& S = C->ctr;
   flush_acc(acc, &S.fe, &S.es, &S.im, &S.fedges[(step + 1) % kRot], &S.frows[(step + 1) % kRot]);
-  if (last_block_arrive(&C->arrive)) {
+  if (last_block_arrive(&C->arrive, gridDim.x)) {
     // a pull step read the current bitmap throughout: clear it now, before it
     // serves as the next step's next-frontier bitmap
     if (pulled)

@@ -128,7 +128,6 @@ __device__ __forceinline__ void tile_prologue(TileCtl* C, uint32_t step, int K) 
   // zero the counters of the next step and count this step for active columns
   const int rz = (step + 1) % kRot, rc = step % kRot;
   if (threadIdx.x < 4) st_agent(&C->cnt[rz][threadIdx.x].v, 0u);
-  if (threadIdx.x == 4) st_agent(&C->cstep, step);
   if (threadIdx.x < kCtrStripes) {
     st_agent64(&C->ctr[threadIdx.x].fedges[rz], 0ull);
     st_agent64(&C->ctr[threadIdx.x].fpairs[rz], 0ull);
@@ -644,7 +643,7 @@ __device__ __forceinline__ void tile_clear_prev(const TileArgs& A, uint32_t step
 }
 
 template <bool F32>
-__device__ void tile_relax(const TileArgs& A, uint32_t step, uint32_t gb, uint32_t nb,
+__device__ __forceinline__ void tile_relax(const TileArgs& A, uint32_t step, uint32_t gb, uint32_t nb,
                            unsigned long long* sh_colact) {
   const int q = step % 3, qn = (step + 1) % 3, qp = (step + 2) % 3;
   const int rc = step % kRot, rn = (step + 1) % kRot, rp = (step + 3) % kRot;
@@ -852,10 +851,11 @@ __device__ __forceinline__ bool tile_is_pull_step(const TileArgs& A, uint32_t st
   return ctr_sum(A.ctl->ctr, offp) >= (unsigned long long)A.pull_src * fe;
 }
 
-// End of a step launch: the last workgroup advances the step and detects the end.
-__device__ __forceinline__ void tile_end_step(const TileArgs& A, uint32_t step, int32_t cap_n) {
+// End of a step launch: the last of its nb workgroups advances the step and detects the end.
+__device__ __forceinline__ void tile_end_step(const TileArgs& A, uint32_t step, uint32_t nb,
+                                              int32_t cap_n) {
   TileCtl* C = A.ctl;
-  if (last_block_arrive(&C->arrive) && threadIdx.x == 0) {
+  if (last_block_arrive(&C->arrive, nb) && threadIdx.x == 0) {
     const bool act = any_active(C, (step + 1) % kRot, A.nseg);
     const uint32_t ns = step + 1;
     st_agent(&C->step, ns);
@@ -867,17 +867,6 @@ __device__ __forceinline__ void tile_end_step(const TileArgs& A, uint32_t step, 
       st_agent(&C->done, 1u);
     }
   }
-}
-
-template <bool F32>
-__global__ void __launch_bounds__(1024) tile_step_kernel(TileArgs A, int32_t cap_n) {
-  __shared__ unsigned long long sh_colact[kSegMax];
-  TileCtl* C = A.ctl;
-  if (ld_agent(&C->done)) return;
-  const uint32_t step = ld_agent(&C->step);
-  if (tile_is_pull_step(A, step)) return;  // the pull kernel runs this step
-  tile_relax<F32>(A, step, blockIdx.x, gridDim.x, sh_colact);
-  tile_end_step(A, step, cap_n);
 }
 
 // ---------------------------------------------------------------------------
@@ -904,7 +893,6 @@ __global__ void __launch_bounds__(1024) tile_step_kernel(TileArgs A, int32_t cap
 // no active source is rare in the steps dense enough to pull) and saves the
 // gather of u's mask words.
 // ---------------------------------------------------------------------------
-constexpr int kPullThreads = 256;
 constexpr int kPullU = 8;  // in-edges gathered at a time per 16-lane group
 
 // E: in-edges taken at a time by the groups of one segment (4 / segments in
@@ -1015,23 +1003,18 @@ __device__ __forceinline__ void tile_pull_chunk(const TileArgs& A, const int4 ch
   }
 }
 
+// One pull step over workgroups gb of nb.
 template <bool F32>
-__global__ void __launch_bounds__(kPullThreads) tile_pull_kernel(TileArgs A, int32_t cap_n) {
-  __shared__ unsigned long long sh_colact[kSegMax];
+__device__ __forceinline__ void tile_pull_step(const TileArgs& A, uint32_t step, uint32_t gb,
+                                               uint32_t nb, unsigned long long* sh_colact) {
   TileCtl* C = A.ctl;
-  if (ld_agent(&C->done)) return;
-  const uint32_t step = ld_agent(&C->step);
-  // after a push step the push kernel has already advanced the step: the new
-  // one has no compaction yet
-  if (step != ld_agent(&C->cstep)) return;
-  if (!tile_is_pull_step(A, step)) return;  // the push kernel runs this step
   const int qn = (step + 1) % 3, rn = (step + 1) % kRot;
-  tile_clear_prev(A, step, blockIdx.x, gridDim.x);
+  tile_clear_prev(A, step, gb, nb);
   if (threadIdx.x < kSegMax) sh_colact[threadIdx.x] = 0ull;
   __syncthreads();
-  const int wave = threadIdx.x >> 6;
-  const uint32_t gw = blockIdx.x * (kPullThreads / kWave) + wave;
-  const uint32_t nwv = gridDim.x * (kPullThreads / kWave);
+  const int wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+  const uint32_t gw = gb * W + wave;
+  const uint32_t nwv = nb * W;
   const uint32_t nq = (uint32_t)((A.nseg + 3) / 4);
   const uint32_t nch = (uint32_t)min((long long)A.T.hdr->nchunks, (long long)A.T.cap_chunks);
   const uint32_t* fbm = A.fbm[step & 1];
@@ -1047,7 +1030,24 @@ __global__ void __launch_bounds__(kPullThreads) tile_pull_kernel(TileArgs A, int
   __syncthreads();
   if ((int)threadIdx.x < A.nseg && sh_colact[threadIdx.x])
     or_new_bits(&C->colact[rn][threadIdx.x], sh_colact[threadIdx.x]);
-  tile_end_step(A, step, cap_n);
+}
+
+// The relaxation of a step: a pull step on all workgroups, or a push step on the
+// first `push_wgs` of them (the others leave at once).  One launch for either: a
+// launch that finds the step is not its own costs 4.5 us, on a call of 30 or more.
+template <bool F32, bool PULL>
+__global__ void __launch_bounds__(1024) tile_step_kernel(TileArgs A, uint32_t push_wgs,
+                                                         int32_t cap_n) {
+  __shared__ unsigned long long sh_colact[kSegMax];
+  TileCtl* C = A.ctl;
+  if (ld_agent(&C->done)) return;
+  const uint32_t step = ld_agent(&C->step);
+  const bool pull = PULL && tile_is_pull_step(A, step);
+  const uint32_t nb = pull ? gridDim.x : push_wgs;
+  if (blockIdx.x >= nb) return;
+  if (PULL && pull) tile_pull_step<F32>(A, step, blockIdx.x, nb, sh_colact);
+  else tile_relax<F32>(A, step, blockIdx.x, nb, sh_colact);
+  tile_end_step(A, step, nb, cap_n);
 }
 
 // ---------------------------------------------------------------------------
@@ -1209,17 +1209,6 @@ __device__ void utile_push_step(const TileArgs& A, uint32_t step, uint32_t gb, u
     or_new_bits(&C->colact[rn][threadIdx.x], sh_colact[threadIdx.x]);
 }
 
-template <int S>
-__global__ void __launch_bounds__(1024) utile_push_kernel(TileArgs A, int32_t cap_n) {
-  __shared__ unsigned long long sh_colact[kSegMax];
-  TileCtl* C = A.ctl;
-  if (ld_agent(&C->done)) return;
-  const uint32_t step = ld_agent(&C->step);
-  if (tile_is_pull_step(A, step)) return;  // the pull kernel runs this step
-  utile_push_step<S>(A, step, blockIdx.x, gridDim.x, sh_colact);
-  tile_end_step(A, step, cap_n);
-}
-
 // The remaining steps of a hop-count tile in one launch (push steps only),
 // with a grid barrier after each compaction and each push step; at most n
 // steps in all.  As tile_persistent_kernel.
@@ -1262,22 +1251,24 @@ __global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A) {
 }
 
 // Pull: each 16-lane group takes one in-edge chunk of a target v, 16 in-edges
-// at a time; lane j (< nseg) of the group holds v's segment-j words.
+// at a time; lane j (< nseg) of the group holds v's segment-j words.  Chunks of
+// more than kUtileLong in-edges take the whole wavefront.
+// Measured at k = 256, 200 and 100 (R-MAT scales 20, 19, 20; us per call): all
+// chunks by groups 2261, 1792, 1763; from 65 in-edges on by wavefronts 2190, 1586,
+// 1682; from 33 on 2227, 1596, 1690; from 129 on 2192, 1640, 1704.
+constexpr int kUtileLong = 64;
 template <int S>
-__global__ void __launch_bounds__(kPullThreads) utile_pull_kernel(TileArgs A, int32_t cap_n) {
-  __shared__ unsigned long long sh_colact[kSegMax];
+__device__ __forceinline__ void utile_pull_step(const TileArgs& A, uint32_t step, uint32_t gb,
+                                                uint32_t nb, unsigned long long* sh_colact) {
   TileCtl* C = A.ctl;
-  if (ld_agent(&C->done)) return;
-  const uint32_t step = ld_agent(&C->step);
-  if (step != ld_agent(&C->cstep)) return;  // a push step ran (see tile_pull_kernel)
-  if (!tile_is_pull_step(A, step)) return;  // the push kernel runs this step
   const int q = step % 3, qn = (step + 1) % 3, rn = (step + 1) % kRot;
-  tile_clear_prev(A, step, blockIdx.x, gridDim.x);
+  tile_clear_prev(A, step, gb, nb);
   if (threadIdx.x < kSegMax) sh_colact[threadIdx.x] = 0ull;
   __syncthreads();
   const int lane = lane_id(), g = lane >> 4, j16 = lane & 15, nseg = A.nseg;
-  const uint32_t gw = blockIdx.x * (kPullThreads / kWave) + (threadIdx.x >> 6);
-  const uint32_t nwv = gridDim.x * (kPullThreads / kWave);
+  const int W = blockDim.x >> 6;
+  const uint32_t gw = gb * W + (threadIdx.x >> 6);
+  const uint32_t nwv = nb * W;
   const uint32_t nch = (uint32_t)min((long long)A.T.hdr->nchunks, (long long)A.T.cap_chunks);
   const uint32_t* fbm = A.fbm[step & 1];
   const unsigned long long live = j16 < nseg ? ld_agent64(&C->live[j16]) : 0ull;
@@ -1299,8 +1290,11 @@ __global__ void __launch_bounds__(kPullThreads) utile_pull_kernel(TileArgs A, in
       acc[s] = 0ull;
       open |= need[s] != 0ull;
     }
-    for (int32_t b = 0; __ballot(open && b < len) != 0ull; b += 16) {
-      const bool act = open && b + j16 < len;
+    // Chunks of many in-edges are left to the whole wavefront below: its four
+    // groups would else wait for the longest of four lists.
+    const bool big = len > kUtileLong;
+    for (int32_t b = 0; __ballot(open && !big && b < len) != 0ull; b += 16) {
+      const bool act = open && !big && b + j16 < len;
       int32_t u = 0;
       bool fr = false;
       if (act) {
@@ -1319,7 +1313,49 @@ __global__ void __launch_bounds__(kPullThreads) utile_pull_kernel(TileArgs A, in
           full = full && acc[s] == need[s];
         }
       }
-      if (full) open = false;
+      if (full && !big) open = false;
+    }
+    // the long chunks, 64 in-edges at a time; found pairs are gathered lane by
+    // lane and combined every few rounds
+    for (unsigned long long todo = __ballot(open && big && j16 == 0); todo; todo &= todo - 1ull) {
+      const int lead = __ffsll((long long)todo) - 1;  // lane 16 * group
+      const int32_t bstart = __builtin_amdgcn_readlane(start, lead);
+      const int32_t blen = __builtin_amdgcn_readlane(len, lead);
+      unsigned long long bneed[S], found[S], part[S];
+#pragma unroll
+      for (int s = 0; s < S; s++) {
+        bneed[s] = lane64(nd, lead + s);
+        found[s] = 0ull;
+        part[s] = 0ull;
+      }
+      bool full = false;
+      int round = 0;
+      for (int32_t b = 0; b < blen && !full; b += kWave) {
+        if (b + lane < blen) {
+          const int32_t u = A.T.colidx[bstart + b + lane];
+          if ((fbm[u >> 5] >> (u & 31)) & 1u) {
+            unsigned long long m[S];
+            load_mask_row<S>(A.mk[q] + (size_t)u * nseg, nseg, m);
+#pragma unroll
+            for (int s = 0; s < S; s++) part[s] |= m[s];
+          }
+        }
+        round++;
+        if ((round & (round - 1)) == 0 || b + kWave >= blen) {  // rounds 1, 2, 4, 8, ... and the last
+          full = true;
+#pragma unroll
+          for (int s = 0; s < S; s++) {
+            if (s < nseg) {
+              found[s] |= wave_or64(part[s]) & bneed[s];
+              full = full && found[s] == bneed[s];
+            }
+          }
+        }
+      }
+      if (g == lead >> 4) {
+#pragma unroll
+        for (int s = 0; s < S; s++) acc[s] = found[s];
+      }
     }
     // the pairs reached become v's next mask words, one lane per segment
     unsigned long long x = 0ull;
@@ -1337,7 +1373,22 @@ __global__ void __launch_bounds__(kPullThreads) utile_pull_kernel(TileArgs A, in
   __syncthreads();
   if ((int)threadIdx.x < A.nseg && sh_colact[threadIdx.x])
     or_new_bits(&C->colact[rn][threadIdx.x], sh_colact[threadIdx.x]);
-  tile_end_step(A, step, cap_n);
+}
+
+// One step, push or pull, as tile_step_kernel.
+template <int S, bool PULL>
+__global__ void __launch_bounds__(1024) utile_step_kernel(TileArgs A, uint32_t push_wgs,
+                                                          int32_t cap_n) {
+  __shared__ unsigned long long sh_colact[kSegMax];
+  TileCtl* C = A.ctl;
+  if (ld_agent(&C->done)) return;
+  const uint32_t step = ld_agent(&C->step);
+  const bool pull = PULL && tile_is_pull_step(A, step);
+  const uint32_t nb = pull ? gridDim.x : push_wgs;
+  if (blockIdx.x >= nb) return;
+  if (PULL && pull) utile_pull_step<S>(A, step, blockIdx.x, nb, sh_colact);
+  else utile_push_step<S>(A, step, blockIdx.x, nb, sh_colact);
+  tile_end_step(A, step, nb, cap_n);
 }
 
 // ---------------------------------------------------------------------------
@@ -1670,13 +1721,13 @@ static dawn_status tile_steps_t(const TileArgs& a, bool persistent, int32_t max_
   // compaction: one 1024-thread workgroup per CU (fewer for small graphs)
   const int cgrid = (int)std::max<int64_t>(1, std::min<int64_t>(cus, ((int64_t)a.n + 1023) / 1024));
   const bool pull = a.T.hdr != nullptr && a.pull_min >= 0;
-  const int pgrid = 16 * cus;
+  // pull steps: 16 workgroups of 256 threads per CU
+  const int lgrid = pull ? std::max(grid, 16 * cus * 256 / threads) : grid;
+  auto stepk = pull ? tile_step_kernel<F32, true> : tile_step_kernel<F32, false>;
   for (int s = 0; s < max_steps; s++) {
     hipLaunchKernelGGL(tile_compact_kernel<false>, dim3(cgrid), dim3(1024), 0, stream, a);
     void* tk = ktimer_begin(stream);
-    hipLaunchKernelGGL(tile_step_kernel<F32>, dim3(grid), dim3(threads), 0, stream, a, 0);
-    if (pull)
-      hipLaunchKernelGGL(tile_pull_kernel<F32>, dim3(pgrid), dim3(kPullThreads), 0, stream, a, 0);
+    hipLaunchKernelGGL(stepk, dim3(lgrid), dim3(threads), 0, stream, a, (uint32_t)grid, 0);
     ktimer_end(tk, stream, 1);
   }
   return hip_check(hipGetLastError(), "tile step launches");
@@ -1690,17 +1741,20 @@ dawn_status utile_steps(const TileArgs& a, int32_t max_steps, hipStream_t stream
                               : (int)std::max<int64_t>(cus, std::min<int64_t>(4 * cus, ((int64_t)a.n + 63) / 64));
   const int cgrid = (int)std::max<int64_t>(1, std::min<int64_t>(cus, ((int64_t)a.n + 1023) / 1024));
   const bool pull = a.T.hdr != nullptr && a.pull_min >= 0;
-  const int pgrid = 16 * cus;
+  const int lgrid = pull ? std::max(grid, 16 * cus * 256 / threads) : grid;
   // kernels specialised for the largest segment count they serve
-  auto push = a.nseg <= 1 ? utile_push_kernel<1> : a.nseg <= 2 ? utile_push_kernel<2>
-            : a.nseg <= 4 ? utile_push_kernel<4> : utile_push_kernel<8>;
-  auto pullk = a.nseg <= 1 ? utile_pull_kernel<1> : a.nseg <= 2 ? utile_pull_kernel<2>
-             : a.nseg <= 4 ? utile_pull_kernel<4> : utile_pull_kernel<8>;
+  auto stepk = pull ? (a.nseg <= 1   ? utile_step_kernel<1, true>
+                       : a.nseg <= 2 ? utile_step_kernel<2, true>
+                       : a.nseg <= 4 ? utile_step_kernel<4, true>
+                                     : utile_step_kernel<8, true>)
+                    : (a.nseg <= 1   ? utile_step_kernel<1, false>
+                       : a.nseg <= 2 ? utile_step_kernel<2, false>
+                       : a.nseg <= 4 ? utile_step_kernel<4, false>
+                                     : utile_step_kernel<8, false>);
   for (int s = 0; s < max_steps; s++) {
     hipLaunchKernelGGL(tile_compact_kernel<true>, dim3(cgrid), dim3(1024), 0, stream, a);
     void* tk = ktimer_begin(stream);
-    hipLaunchKernelGGL(push, dim3(grid), dim3(threads), 0, stream, a, 0);
-    if (pull) hipLaunchKernelGGL(pullk, dim3(pgrid), dim3(kPullThreads), 0, stream, a, 0);
+    hipLaunchKernelGGL(stepk, dim3(lgrid), dim3(threads), 0, stream, a, (uint32_t)grid, 0);
     ktimer_end(tk, stream, 1);
   }
   return hip_check(hipGetLastError(), "hop-count tile step launches");
