@@ -178,14 +178,15 @@ typedef struct {
   int32_t step_launches; /* single source, mode 1: step launches before the persistent
                             launch, 0..4096, default 20 */
   int32_t tile_k;     /* default 256 */
-  int32_t tile_t_wave;  /* workgroup-tier threshold of the tile kernel, 32..65536, default 64 */
+  int32_t tile_t_wave;  /* workgroup-tier threshold of the tile kernel, 32..65536, default 64
+                           (weighted tiles: rows of up to twice as many edges stay below it) */
   int32_t tile_t_chunk; /* edges per workgroup chunk in the tile kernel, 64..65536, default 256 */
   int32_t validate;     /* 1 = check the CSR on the device before running */
   int32_t coop;         /* 1 = launch persistent kernels with hipLaunchCooperativeKernel
                            (not under graph capture); 0 (default) = an ordinary launch of
                            the same grid */
-  int32_t tile_t_group; /* tile rows of out-degree <= this go one per 16-lane group,
-                           0..64, default 8 (0: none) */
+  int32_t tile_t_group; /* tile rows of out-degree <= this (weighted tiles: three times
+                           this) go one per 16-lane group, 0..64, default 8 (0: none) */
   int32_t tile_skip;    /* 1: in a tile step, a (row, source) pair whose distance was
                            already lowered again in the same step is not expanded (it is
                            expanded next step with the lower value); 0 (default): every

@@ -1581,9 +1581,15 @@ TileArgs tile_args(const int32_t* rowptr, const int32_t* colidx, const void* w, 
   A.m = m;
   A.K = L.K;
   A.nseg = L.nseg;
-  A.t_wave = T.tile_t_wave;
+  // Weighted tiles: rows of up to three times tile_t_group edges by 16-lane groups
+  // and of up to twice tile_t_wave by wavefronts (24 and 128 by default): setting a
+  // row up costs more round trips than 16 lanes take for its edges.  Measured at 8
+  // and 64 / 24 and 128: R-MAT scale 18, k = 24 session 2353 / 2241 us, k = 100
+  // 3836 / 3608; scale 16, k = 37 813 / 795; ER n = 400,000, k = 200 10.1 / 9.5 ms.
+  // Hop counts, a row per lane, lose by it (610 / 643 us on R-MAT 17 at 16 and 64).
+  A.t_wave = L.unweighted ? T.tile_t_wave : 2 * T.tile_t_wave;
+  A.t_group = L.unweighted ? T.tile_t_group : std::min(3 * T.tile_t_group, A.t_wave - 1);
   A.t_chunk = T.tile_t_chunk;
-  A.t_group = T.tile_t_group;
   A.skip = T.tile_skip;
   A.sparse = T.tile_sparse;
   A.T = TGraph{};
