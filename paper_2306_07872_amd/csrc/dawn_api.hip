@@ -80,7 +80,9 @@ const DevInfo& dev_info() {
 
 bool stream_capturing(hipStream_t stream) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
 }
 
 // One event per device, created by its first gated launch and kept until the
@@ -935,8 +937,11 @@ struct dawn_tile {
   const void* tgraph = nullptr;  // reverse graph for pull steps, or null
   // columns whose distances are INF throughout: never admitted, or evicted since
   // (an evicted column's leftover mask bits make no candidate below INF), so the
-  // next query needs no fill (5 us on 262,144 vertices, a launch per query)
+  // next query needs no fill (5 us on 262,144 vertices, a launch per query).  Once
+  // an admission or eviction has been captured into a graph, its replays change
+  // columns unseen from here: from then on every admission fills.
   bool clean[DAWN_TILE_K_MAX];
+  bool unseen = false;
   // a captured run (dawn_tile_capture)
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -992,7 +997,8 @@ extern "C" dawn_status dawn_tile_admit(dawn_tile* t, int32_t col, int32_t source
   if (!t) return set_error(DAWN_E_INVALID, "null tile");
   if (col < 0 || col >= t->k) return set_error(DAWN_E_INVALID, "column %d out of range", col);
   if (source < 0 || source >= t->A.n) return set_error(DAWN_E_INVALID, "source out of range");
-  const bool clean = t->clean[col];
+  if (stream_capturing(stream)) t->unseen = true;
+  const bool clean = t->clean[col] && !t->unseen;
   t->clean[col] = false;
   return tile_admit(t->A, t->f32, col, source, clean, stream);
 }
@@ -1077,6 +1083,7 @@ extern "C" dawn_status dawn_tile_steps(dawn_tile* t, int32_t* steps_out, hipStre
 extern "C" dawn_status dawn_tile_evict(dawn_tile* t, int32_t col, hipStream_t stream) {
   if (!t) return set_error(DAWN_E_INVALID, "null tile");
   if (col < 0 || col >= t->k) return set_error(DAWN_E_INVALID, "column %d out of range", col);
+  if (stream_capturing(stream)) t->unseen = true;
   const dawn_status st = tile_evict(t->A, t->f32, col, stream);
   t->clean[col] = st == DAWN_OK;
   return st;
