@@ -218,9 +218,9 @@ def c2(args, dawn, torch, np):
            "steps_mean": float(np.mean(steps)),
            "roofline": {"bound": "hbm",
                         "kernel": ("ss_step_kernel<0, false> (uint32 weights) + "
-                                   "ss_persistent_kernel<0> (the steps after the step launches)"
+                                   "ss_persistent_kernel<0, false> (the steps after the step launches)"
                                    if g.m >= dawn.get_tuning()["step_min_m"]
-                                   else "ss_persistent_kernel<0> (uint32 weights)"),
+                                   else "ss_persistent_kernel<0, false> (uint32 weights)"),
                         "achieved": kb / (kms * 1e-3) / 1e9, "peak": 8000.0, "unit": "GB/s",
                         "frac": kb / (kms * 1e-3) / 1e9 / 8000.0},
            "parity": note_parity("c2", bad, len(srcs)), "cpu_baseline": cpu}

@@ -149,7 +149,10 @@ typedef struct {
  * run already ended returns at once.
  *   0 auto: single source and batches of graphs run in one workgroup when
  *     m <= small_m, as mode 1 when m >= step_min_m, else as mode 2; tiles
- *     (dawn_msssp, dawn_apsp, dawn_umsssp_ws) as mode 1;
+ *     (dawn_msssp, dawn_apsp, dawn_umsssp_ws) as mode 1, unless the
+ *     call runs in one workgroup per source (see small_m) or, with few
+ *     sources and not under graph capture, as one single-source run on
+ *     copies of the graph;
  *   1 `step_launches` (tiles: `tile_step_launches`) launches of one step
  *     each, then one persistent launch for the steps that remain;
  *   2 one persistent launch for all steps, with a grid barrier between steps.
@@ -202,13 +205,17 @@ typedef struct {
                            sources are relaxed one edge per lane, 4 bytes per source,
                            instead of 16 lanes per 64-source segment; 0..512, default 8 */
   int32_t tile_pull;    /* with a reverse graph (dawn_msssp_tg_ws), a tile step whose
-                           frontier rows hold at least tile_pull / 1000 of the m edges, and
-                           whose frontier edges carry on average at least tile_pull_src
-                           active sources, is run as a pull step over the in-edges of every
-                           vertex; 0 = every step, 1001 = never; default 400 */
+                           frontier rows hold at least tile_pull / 1000 of the m edges (hop
+                           counts: three quarters of that), and that passes tile_pull_src,
+                           is run as a pull step over the in-edges of every vertex; 0 =
+                           every step, 1001 = never; default 400 */
   int32_t tile_pull_src; /* see tile_pull: a pull step reads a frontier in-neighbour's whole
-                           64-source segments, a push step only its active sources, so tiles
-                           holding few queries stay with push; 0..512, default 16 */
+                           64-source segments, a push step only its active sources, so a
+                           step pulls when half of the tile's columns are live and its
+                           frontier edges carry on average at least tile_pull_src active
+                           sources (a quarter of that while the frontier grows; twice that
+                           on a shrinking frontier of a one-segment tile).  Hop counts: an
+                           eighth, whatever is live.  0: no such test; 0..512, default 16 */
   int32_t ss_skip;      /* single source, multi-workgroup launches: 1 = a frontier row that
                            another row lowered again within the step is expanded only in the
                            next step (once, with the lower value); 0 or 1 (default: on

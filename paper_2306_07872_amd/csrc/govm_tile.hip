@@ -37,10 +37,8 @@ namespace dawn {
 
 constexpr int kTileU = 4;  // edges in flight per 16-lane group
 // Persistent tile launches default to one 1024-thread workgroup per compute
-// unit: each workgroup's arrival at a grid barrier costs serial time at the
-// barrier word, and runs with thousands of steps (grids) pay two barriers per
-// step (measured on a 2048 x 2048 grid: about 130 us per step instead of 335
-// with four 256-thread workgroups per compute unit).
+// unit: runs with thousands of steps (grids) pay two barriers per step, and a
+// barrier costs by the workgroups that arrive at it.
 constexpr int kTilePersistentThreads = 1024;
 
 // ---------------------------------------------------------------------------
@@ -835,20 +833,41 @@ __global__ void __launch_bounds__(1024) tile_compact_kernel(TileArgs A) {
   flush_acc(acc, &S.fe, &S.es, &S.im, &S.sa, &S.se, &S.fedges[step % kRot], &S.fpairs[step % kRot]);
 }
 
-// A step is a pull step when the reverse graph is there, the frontier has at
-// least pull_min out-edges and those carry at least pull_src active sources
-// each on average (a pull step reads whole segment rows; with few active
-// sources the push step reads far less).  Both counts come from the
-// compaction, before both relaxation kernels of the step run, so both take
-// the same decision.
+// Whether a step pulls.  The counts come from the compaction, before the step's
+// relaxation, so every workgroup takes the same decision.  A pull step reads
+// whole segment rows of the frontier's in-neighbours whatever is active there; a
+// push step reads active segments and pays for each improvement (about 50 ps: an
+// atomic at the memory side).  How many there will be shows in whether the
+// frontier's (edge, source) pairs grow: ER n = 400,000, k = 200 at 15 sources per
+// edge and growing 1904 us pushed, 600 pulled; at 16 and shrinking 704, 418; k =
+// 64, m = 16n, 9 and growing 1563, 379.  So with half of the tile's columns live
+// a step pulls from pull_src sources per edge on, and from a quarter of that while
+// growing.  A tile of one segment reads 256 bytes per in-edge either way and
+// pushes a shrinking frontier sooner: below 2 * pull_src (R-MAT scale 18, 60
+// queries, 26 per edge: 196 us pushed, 356 pulled; ER k = 64, 39 per edge: 480,
+// 383).  With few columns live a pull reads mostly others' distances: R-MAT scale
+// 18, 24 of 64 live, the steps at 22 and 16 per edge 221 and 192 pushed, 372 and
+// 369 pulled.  Hop counts: a pull reads masks alone and stops at a target's last
+// missing source, so it pays from 2 sources per edge on (R-MAT scale 20, k = 256:
+// 37 % of the edges, 2.6 per edge 403 us pushed, 244 pulled; ER, 8 per edge and
+// shrinking 161, 72) and from a frontier of three quarters of pull_min.
+template <bool HOPS>
 __device__ __forceinline__ bool tile_is_pull_step(const TileArgs& A, uint32_t step) {
   if (A.T.hdr == nullptr || A.pull_min < 0) return false;
   const size_t off = offsetof(CtrStripe, fedges) + (step % kRot) * sizeof(unsigned long long);
   const unsigned long long fe = ctr_sum(A.ctl->ctr, off);
-  if (fe < (unsigned long long)A.pull_min) return false;
+  if (fe < (unsigned long long)(HOPS ? A.pull_min / 4 * 3 : A.pull_min)) return false;
   if (A.pull_src <= 0) return true;
-  const size_t offp = offsetof(CtrStripe, fpairs) + (step % kRot) * sizeof(unsigned long long);
-  return ctr_sum(A.ctl->ctr, offp) >= (unsigned long long)A.pull_src * fe;
+  const size_t offp = offsetof(CtrStripe, fpairs);
+  const unsigned long long now = ctr_sum(A.ctl->ctr, offp + (step % kRot) * sizeof(unsigned long long));
+  const unsigned long long least = (unsigned long long)A.pull_src * fe;
+  if (HOPS) return now >= least / 8;
+  int live = 0;
+  for (int s = 0; s < A.nseg; s++) live += __popcll(ld_agent64(&A.ctl->colact[step % kRot][s]));
+  if (2 * live < A.K) return false;
+  const unsigned long long before =
+      ctr_sum(A.ctl->ctr, offp + ((step + kRot - 1) % kRot) * sizeof(unsigned long long));
+  return now >= (now > before ? least / 4 : A.nseg == 1 ? 2 * least : least);
 }
 
 // End of a step launch: the last of its nb workgroups advances the step and detects the end.
@@ -1042,7 +1061,7 @@ __global__ void __launch_bounds__(1024) tile_step_kernel(TileArgs A, uint32_t pu
   TileCtl* C = A.ctl;
   if (ld_agent(&C->done)) return;
   const uint32_t step = ld_agent(&C->step);
-  const bool pull = PULL && tile_is_pull_step(A, step);
+  const bool pull = PULL && tile_is_pull_step<false>(A, step);
   const uint32_t nb = pull ? gridDim.x : push_wgs;
   if (blockIdx.x >= nb) return;
   if (PULL && pull) tile_pull_step<F32>(A, step, blockIdx.x, nb, sh_colact);
@@ -1383,7 +1402,7 @@ __global__ void __launch_bounds__(1024) utile_step_kernel(TileArgs A, uint32_t p
   TileCtl* C = A.ctl;
   if (ld_agent(&C->done)) return;
   const uint32_t step = ld_agent(&C->step);
-  const bool pull = PULL && tile_is_pull_step(A, step);
+  const bool pull = PULL && tile_is_pull_step<true>(A, step);
   const uint32_t nb = pull ? gridDim.x : push_wgs;
   if (blockIdx.x >= nb) return;
   if (PULL && pull) utile_pull_step<S>(A, step, blockIdx.x, nb, sh_colact);
@@ -1717,10 +1736,10 @@ static dawn_status tile_steps_t(const TileArgs& a, bool persistent, int32_t max_
     return hip_check(e, "tile persistent launch");
   }
   // push relaxation: 4 workgroups per CU, fewer for small graphs (about one
-  // workgroup per 64 vertices, at least one per CU).  Each workgroup ends the
-  // step with an agent-scope release (an L2 write-back) and an arrival on one
-  // counter, about 50 ns of serial time apiece: on R-MAT scale 20, 16 per CU
-  // made a push step with a near-empty frontier cost ~200 us instead of ~20.
+  // workgroup per 64 vertices, at least one per CU): every workgroup ends the
+  // step with an arrival on one counter.  Measured at 2, 4, 6, 8 and 16 per CU:
+  // R-MAT scale 16, k = 37 853, 815, 874, 868, 1099 us; scale 18, k = 24 session
+  // 2471, 2217, 2409, 2383, 2494; scale 20, k = 256 16.4, 15.4, 15.6, 15.3, 15.3 ms.
   const int cus = dev_info().cus;
   const int grid = T.grid > 0 ? T.grid
                               : (int)std::max<int64_t>(cus, std::min<int64_t>(4 * cus, ((int64_t)a.n + 63) / 64));

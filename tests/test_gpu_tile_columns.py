@@ -117,3 +117,24 @@ def test_hop_count_pull_around_the_long_chunk_limit(dawn, k):
         for j in (0, k // 2, k - 1):
             lv = oracle.bfs(g, int(srcs[j]))
             assert np.array_equal(D[j], np.where(lv < 0, 0xFFFFFFFF, lv).astype(np.uint32)), (tune, j)
+
+
+@pytest.mark.parametrize("wtype", ["u32", "f32lognormal"])
+@pytest.mark.parametrize("k", [28, 31, 32, 33, 64, 65, 200])
+def test_steps_that_turn_from_push_to_pull_and_back(dawn, wtype, k):
+    # frontiers that grow and shrink through the limits of the pull rule, with
+    # fewer and more than half of a tile's columns live
+    for g in (graphgen.er(40009, 320009, 51, weights=wtype), graphgen.rmat(14, 16, 52, weights=wtype)):
+        csr = dawn.Csr.from_graph(g)
+        tg = dawn.tgraph(csr)
+        srcs = graphgen.pick_sources(g, k, 53)
+        announce("push and pull by turns", g.name, k)
+        prev = dawn.set_tuning(small_m=0)
+        try:
+            D = to_np(dawn.msssp(csr, srcs, tgraph=tg))
+            P = to_np(dawn.msssp(csr, srcs))
+        finally:
+            dawn.set_tuning(**prev)
+        assert np.array_equal(D.view(np.uint32), P.view(np.uint32))
+        for j in (0, k - 1):
+            assert_sssp_matches(g, int(srcs[j]), D[j], tag=f"{g.name} col {j}", check_invariants=False)
