@@ -3,10 +3,10 @@
 // GOVM (Section 3.4, Algorithm 2) keeps three vectors: alpha (distances),
 // delta (rows to expand this step) and beta (rows changed this step).  Here:
 //   alpha -> the caller's distance array (uint32, or fp32 kept as its bits);
-//   delta -> per-tier frontier queues of vertex ids (compacted, no dense scan);
+//   delta -> the frontier bitmap of the step, scanned, and queues of its long rows;
 //   beta  -> a bitmap that deduplicates the next frontier, whose first setter
-//            of each bit appends the vertex to the next queues with a
-//            wavefront ballot + prefix count (one atomic per wavefront);
+//            of a long row's bit appends the row to the next queues with a
+//            wavefront ballot + prefix count (one atomic per workgroup);
 //   ptr   -> a per-step "something improved" flag.
 // Distances only decrease, so the relaxation is an atomic min; for
 // non-negative fp32 values the bit patterns order like uint32, so one uint32

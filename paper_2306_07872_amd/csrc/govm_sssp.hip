@@ -28,9 +28,11 @@
 //   the candidate is smaller.  Order of updates inside a step does not matter:
 //   the fixed point is unique (Section 3.5: the method does not care in which
 //   order paths appear).
-// - Step loop: one persistent launch with a grid barrier per step, or a fixed
-//   number of launches of one step each (last-block bookkeeping) followed by
-//   the persistent launch for the remaining steps.  The host never waits.
+// - Step loop: one workgroup with the run's state in LDS (small graphs; several
+//   sources, one workgroup each), one persistent launch with a grid barrier per
+//   step, or a fixed number of launches of one step each (last-block bookkeeping)
+//   followed by the persistent launch for the remaining steps.  The host never
+//   waits.
 #include <stdio.h>
 
 #include <algorithm>
