@@ -158,16 +158,53 @@ __device__ float nf_floor(int64_t n, int64_t m, const int32_t* rowptr, const uin
 // ---------------------------------------------------------------------------
 // init
 // ---------------------------------------------------------------------------
+// Step 0's counts and long rows: a seed's row in the queue of its tier.  (A
+// short row is found by its bit.)  ALONE: the only seed, right after the same
+// workgroup has cleared the control words with plain stores: no atomics.
+template <bool ALONE>
+__device__ __forceinline__ void ss_queue_seed(const SsArgs& A, int64_t s) {
+  SsCtl* C = A.ctl;
+  const int32_t start = A.rowptr[s], deg = A.rowptr[s + 1] - start;
+  if (deg == 0) return;
+  const bool wave = deg > A.t_lane && deg <= A.t_wave, wg = deg > A.t_lane && !wave;
+  const uint32_t nch = wg ? (uint32_t)((deg + A.t_chunk - 1) / A.t_chunk) : 0u;
+  uint32_t p = 0u;
+  if (ALONE) {
+    C->ctr.fedges[0] = (unsigned long long)deg;
+    C->ctr.frows[0] = 1ull;
+    if (wave) C->cnt[0][1].v = 1u;
+    if (wg) C->cnt[0][2].v = nch;
+  } else {
+    atomicAdd(&C->ctr.fedges[0], (unsigned long long)deg);
+    atomicAdd(&C->ctr.frows[0], 1ull);
+    if (wave) p = atomicAdd(&C->cnt[0][1].v, 1u);
+    if (wg) p = atomicAdd(&C->cnt[0][2].v, nch);
+  }
+  if (wave) A.qwave[0][p] = (int32_t)s;
+  for (uint32_t c = 0; c < nch; c++) {
+    const int32_t off = (int32_t)c * A.t_chunk;
+    if (p + c < A.cap_wg)
+      A.qwg[0][p + c] = make_int4((int32_t)s, start + off, min(A.t_chunk, deg - off), c == 0);
+  }
+}
+
 // hv (may be null): bit v set when row v has more than t_lane edges, the rows
 // that steps take from the wave and workgroup queues rather than from the bitmap.
+// seed (or -1): the run's only source, placed here, which saves the launch that
+// places several (with the run's report in its last launch: ER n = 40,000 272 ->
+// 254 us, R-MAT scale 16 376 -> 366, scale 20 802 -> 789).
 template <int WT>
 __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_t* bm1,
                                int64_t nwords, SsCtl* ctl, const int32_t* rowptr, uint32_t* hv,
-                               int32_t t_lane, const uint32_t* w, int64_t m, int32_t n1) {
+                               int32_t t_lane, const uint32_t* w, int64_t m, int32_t n1,
+                               int64_t seed, SsArgs A) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = tid; i < n; i += stride) dist[i] = inf_key<WT>();
-  for (int64_t i = tid; i < nwords; i += stride) { bm0[i] = 0; bm1[i] = 0; }
+  for (int64_t i = tid; i < n; i += stride) dist[i] = i == seed ? zero_key<WT>() : inf_key<WT>();
+  for (int64_t i = tid; i < nwords; i += stride) {
+    bm0[i] = seed >= 0 && i == seed >> 5 ? 1u << (seed & 31) : 0u;
+    bm1[i] = 0;
+  }
   if (hv) {
     // a wavefront per 64 vertices: the ballot's halves are two bitmap words
     // (blockDim and the grid's thread count are multiples of 64)
@@ -190,7 +227,10 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
     __syncthreads();
     if (threadIdx.x < kRot) ctl->minp[threadIdx.x].v = kNoKey;
     const float floor = nf_floor<WT>(n1, m, rowptr, w, kNfSamples);
-    if (threadIdx.x == 0) ctl->nf = NfState{kNoKey, floor, floor, 0u};
+    if (threadIdx.x == 0) {
+      ctl->nf = NfState{kNoKey, floor, floor, 0u};
+      if (seed >= 0) ss_queue_seed<true>(A, seed);
+    }
   }
 }
 
@@ -229,24 +269,7 @@ __global__ void ss_seed_kernel(SsArgs A, const int32_t* sources, const int64_t* 
     const uint32_t bit = 1u << (s & 31);
     const uint32_t old = atomicOr(&A.bm[0][s >> 5], bit);
     if (old & bit) continue;  // duplicate seed
-    const int32_t start = A.rowptr[s], deg = A.rowptr[s + 1] - start;
-    if (deg == 0) continue;
-    atomicAdd(&C->ctr.fedges[0], (unsigned long long)deg);
-    atomicAdd(&C->ctr.frows[0], 1ull);
-    if (deg <= A.t_lane) {
-      // short row: step 0 finds it by its bit
-    } else if (deg <= A.t_wave) {
-      const uint32_t p = atomicAdd(&C->cnt[0][1].v, 1u);
-      A.qwave[0][p] = (int32_t)s;
-    } else {
-      const uint32_t nch = (deg + A.t_chunk - 1) / A.t_chunk;
-      const uint32_t p = atomicAdd(&C->cnt[0][2].v, nch);
-      for (uint32_t c = 0; c < nch; c++) {
-        const int32_t off = (int32_t)c * A.t_chunk;
-        if (p + c < A.cap_wg)
-          A.qwg[0][p + c] = make_int4((int32_t)s, start + off, min(A.t_chunk, deg - off), c == 0);
-      }
-    }
+    ss_queue_seed<false>(A, s);
   }
 }
 
@@ -279,12 +302,6 @@ __device__ void ss_report(SsCtl* C, dawn_run_info* info, uint32_t* latch) {
   info->improvements = (int64_t)im;
   info->union_rows = (int64_t)fe;
   info->union_edges = (int64_t)es;
-}
-
-template <int WT>
-__global__ void ss_finalize_kernel(SsCtl* C, dawn_run_info* info, uint32_t* latch) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  ss_report<WT>(C, info, latch);
 }
 
 // ---------------------------------------------------------------------------
@@ -936,10 +953,13 @@ __device__ __forceinline__ bool ss_grid_sync(SsCtl* C, uint32_t nblocks, uint32_
 // kernel's compiled resources (residency_of); should a barrier wait still give
 // up, the run ends with status -2, reported to the caller.
 template <int WT, bool COPIES>
-__global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A) {
+__global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_info* info) {
   __shared__ SsShared sh;
   SsCtl* C = A.ctl;
-  if (ld_agent(&C->done)) return;
+  if (ld_agent(&C->done)) {  // ended by an earlier launch, or given up by workgroup 0
+    if (last_block_arrive(&C->arrive, gridDim.x) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
+    return;
+  }
   Acc acc;
   uint32_t epoch = 0;
   const uint32_t bar_base = ld_agent(&C->bar_base);
@@ -980,6 +1000,8 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A) {
     st_agent(&C->done, 1u);
     st_agent(&C->bar_base, bar_base + epoch);
   }
+  // the last workgroup to leave has every counter: it reports the run
+  if (last_block_arrive(&C->arrive, gridDim.x) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
 }
 
 // One step per launch; the last block to finish advances the step.
@@ -1680,7 +1702,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     if (T.validate) {
       hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                          (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, nullptr, nullptr, 0, nullptr, 0,
-                         A.n1);
+                         A.n1, (int64_t)-1, A);
       const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
       hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
                          A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
@@ -1693,16 +1715,19 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     ktimer_end(tk, stream, 1);
     return hip_check(hipGetLastError(), "small-graph launch");
   }
+  // (a validation that fails leaves every distance INF: it comes before the seed)
+  const bool placed = !seeds.sources_dev && !T.validate;
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, rowptr, A.hv, A.t_lane, A.w,
-                     (int64_t)A.m, A.n1);
+                     (int64_t)A.m, A.n1, placed ? (int64_t)seeds.source : (int64_t)-1, A);
   if (T.validate) {
     const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
     hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
                        A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
   }
-  hipLaunchKernelGGL(ss_seed_kernel<WT>, dim3(1), dim3(256), 0, stream, A, seeds.sources_dev,
-                     seeds.voff_dev, seeds.count, seeds.source);
+  if (!placed)
+    hipLaunchKernelGGL(ss_seed_kernel<WT>, dim3(1), dim3(256), 0, stream, A, seeds.sources_dev,
+                       seeds.voff_dev, seeds.count, seeds.source);
   if ((st = hip_check(hipGetLastError(), "init launch")) != DAWN_OK) return st;
 
   // Mode 1: `step_launches` step launches, then one persistent launch for
@@ -1728,7 +1753,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     a.counted = mode == 1 && A.pull_min >= 0;
     ss_persistent_tiers(a);
     a.pull_min = -1;  // pull steps need step launches (the last workgroup clears the bitmap)
-    void* args[] = {&a};
+    void* args[] = {&a, &info};
     hipError_t e;
     const PersistentGate gate(stream, grid);
     void* tk = capture ? nullptr : ktimer_begin(stream);
@@ -1736,14 +1761,12 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
       e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&ss_persistent_kernel<WT, false>),
                                      dim3(grid), dim3(threads), args, 0, stream);
     } else {
-      hipLaunchKernelGGL((ss_persistent_kernel<WT, false>), dim3(grid), dim3(threads), 0, stream, a);
+      hipLaunchKernelGGL((ss_persistent_kernel<WT, false>), dim3(grid), dim3(threads), 0, stream, a, info);
       e = hipGetLastError();
     }
     ktimer_end(tk, stream, 1);
     if ((st = hip_check(e, "persistent launch")) != DAWN_OK) return st;
   }
-  hipLaunchKernelGGL(ss_finalize_kernel<WT>, dim3(1), dim3(64), 0, stream, A.ctl, info, A.latch);
-  if ((st = hip_check(hipGetLastError(), "finalize launch")) != DAWN_OK) return st;
   if constexpr (WT == kWI32) {
     hipLaunchKernelGGL(ss_decode_i32_kernel, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                        (int64_t)A.n);
@@ -1843,7 +1866,7 @@ static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int
   const int fill_blocks = (int)std::min<int64_t>(4096, ((int64_t)A.n + 255) / 256 + 1);
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, A.rowptr, A.hv, A.t_lane, A.w,
-                     (int64_t)A.m, A.n1);
+                     (int64_t)A.m, A.n1, (int64_t)-1, A);
   hipLaunchKernelGGL(ss_copy_seed_kernel<WT>, dim3(1), dim3(64), 0, stream, A, sources, k);
   const Residency r = residency_of(ss_persistent_kernel<WT, true>, threads);
   int grid = std::min(std::min(r.grid, kMaxGrid),
@@ -1851,9 +1874,8 @@ static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int
   if (T.grid > 0 && T.grid < grid) grid = T.grid;
   const PersistentGate gate(stream, grid);
   void* tk = ktimer_begin(stream);
-  hipLaunchKernelGGL((ss_persistent_kernel<WT, true>), dim3(grid), dim3(threads), 0, stream, A);
+  hipLaunchKernelGGL((ss_persistent_kernel<WT, true>), dim3(grid), dim3(threads), 0, stream, A, info);
   ktimer_end(tk, stream, 1);
-  hipLaunchKernelGGL(ss_finalize_kernel<WT>, dim3(1), dim3(64), 0, stream, A.ctl, info, A.latch);
   return hip_check(hipGetLastError(), "copies launch");
 }
 
