@@ -833,8 +833,11 @@ __global__ void __launch_bounds__(1024) tile_compact_kernel(TileArgs A) {
   flush_acc(acc, &S.fe, &S.es, &S.im, &S.sa, &S.se, &S.fedges[step % kRot], &S.fpairs[step % kRot]);
 }
 
-// Whether a step pulls.  The counts come from the compaction, before the step's
-// relaxation, so every workgroup takes the same decision.  A pull step reads
+// Whether a step pulls.  The counts come from the step's compaction, an earlier
+// launch, so every workgroup that has a part in the step takes the same decision.
+// (A workgroup with none may start so late that the step has been advanced and
+// ask about the next one, which has no compaction yet: its counts are zero, and a
+// step without frontier edges never pulls, whatever the bounds.)  A pull step reads
 // whole segment rows of the frontier's in-neighbours whatever is active there; a
 // push step reads active segments and pays for each improvement (about 50 ps: an
 // atomic at the memory side).  How many there will be shows in whether the
@@ -856,7 +859,7 @@ __device__ __forceinline__ bool tile_is_pull_step(const TileArgs& A, uint32_t st
   if (A.T.hdr == nullptr || A.pull_min < 0) return false;
   const size_t off = offsetof(CtrStripe, fedges) + (step % kRot) * sizeof(unsigned long long);
   const unsigned long long fe = ctr_sum(A.ctl->ctr, off);
-  if (fe < (unsigned long long)(HOPS ? A.pull_min / 4 * 3 : A.pull_min)) return false;
+  if (fe == 0 || fe < (unsigned long long)(HOPS ? A.pull_min / 4 * 3 : A.pull_min)) return false;
   if (A.pull_src <= 0) return true;
   const size_t offp = offsetof(CtrStripe, fpairs);
   const unsigned long long now = ctr_sum(A.ctl->ctr, offp + (step % kRot) * sizeof(unsigned long long));
@@ -1054,6 +1057,10 @@ __device__ __forceinline__ void tile_pull_step(const TileArgs& A, uint32_t step,
 // The relaxation of a step: a pull step on all workgroups, or a push step on the
 // first `push_wgs` of them (the others leave at once).  One launch for either: a
 // launch that finds the step is not its own costs 4.5 us, on a call of 30 or more.
+// Invariant: the workgroups that count towards the step's end (nb) read `step`
+// before it advances, since it advances when all of them have arrived.  A workgroup
+// past push_wgs of a push step may read the advanced step; it must leave then too,
+// which tile_is_pull_step sees to.
 template <bool F32, bool PULL>
 __global__ void __launch_bounds__(1024) tile_step_kernel(TileArgs A, uint32_t push_wgs,
                                                          int32_t cap_n) {
