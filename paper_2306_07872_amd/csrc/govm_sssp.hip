@@ -956,7 +956,10 @@ template <int WT, bool COPIES>
 __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_info* info) {
   __shared__ SsShared sh;
   SsCtl* C = A.ctl;
-  if (ld_agent(&C->done)) {  // ended by an earlier launch, or given up by workgroup 0
+  // Ended by an earlier launch, or given up by workgroup 0, which may happen while
+  // this workgroup starts: one read for all of its threads, which would else part
+  // here and miss each other at the barriers of the steps.
+  if (ld_agent_block(&C->done)) {
     if (last_block_arrive(&C->arrive, gridDim.x) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
     return;
   }

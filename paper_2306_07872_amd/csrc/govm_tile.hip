@@ -776,7 +776,8 @@ __global__ void __launch_bounds__(1024) tile_persistent_kernel(TileArgs A, int32
   __shared__ unsigned long long sh_colact[kSegMax];
   __shared__ CompactShared csh;
   TileCtl* C = A.ctl;
-  if (ld_agent(&C->done)) return;
+  // one read for the workgroup: workgroup 0 may give up and set it meanwhile
+  if (ld_agent_block(&C->done)) return;
   Acc acc;  // every counter is taken by the compaction
   uint32_t epoch = 0;
   const uint32_t bar_base = ld_agent(&C->bar_base);
@@ -1243,7 +1244,7 @@ __global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A) {
   __shared__ unsigned long long sh_colact[kSegMax];
   __shared__ CompactShared csh;
   TileCtl* C = A.ctl;
-  if (ld_agent(&C->done)) return;
+  if (ld_agent_block(&C->done)) return;  // as tile_persistent_kernel
   Acc acc;
   uint32_t epoch = 0;
   const uint32_t bar_base = ld_agent(&C->bar_base);
