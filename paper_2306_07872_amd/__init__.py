@@ -366,7 +366,7 @@ def sssp_noalloc(csr: Csr, source: int, out, stream=None, check: bool = True):
     """``dawn_sssp_noalloc``: distances from `source` into the caller's `out`
     (length n, the graph's distance type), with the library's fixed per-device
     scratch array as workspace, so the call allocates no device memory.  Graphs
-    needing more than NOALLOC_SCRATCH_BYTES of workspace raise DawnError
+    whose queues and bitmaps need more than NOALLOC_SCRATCH_BYTES raise DawnError
     (workspace too small).  Calls on one device share the array: order them on
     one stream.  check=True synchronises and raises if the run did not
     converge (``dawn_run_status``)."""

@@ -52,8 +52,13 @@ __device__ __align__(256) uint32_t g_run_latch[64];
 // object until the process ends.  Host code never names the array in a launch
 // or copy; it uses the device address that hipGetSymbolAddress returned with
 // that device current (DevInfo::noalloc).
-// The grid barrier's slots come on top of the documented bytes.
-constexpr size_t kNoallocBytes = DAWN_NOALLOC_SCRATCH_BYTES + sizeof(GridBar::slot);
+// The control block comes on top of the documented bytes, which the arrays that
+// grow with the graph may fill.
+constexpr size_t kNoallocBytes = DAWN_NOALLOC_SCRATCH_BYTES + sizeof(SsCtl);
+// What the control block counts for when a graph is held against the documented
+// bytes: a fixed figure, so that a larger block does not narrow what is accepted.
+constexpr size_t kNoallocCtl = 2816;
+static_assert(sizeof(SsCtl) >= kNoallocCtl, "graphs that pass the check fit the array");
 static __device__ __align__(256) unsigned char g_noalloc_scratch[kNoallocBytes];
 
 const DevInfo& dev_info() {
@@ -496,8 +501,8 @@ extern "C" dawn_status dawn_sssp_noalloc(const int32_t* rowptr, const int32_t* c
   if (st != DAWN_OK) return st;
   if (source < 0 || source >= n) return set_error(DAWN_E_INVALID, "source %d out of range", source);
   if (!dist_out) return set_error(DAWN_E_INVALID, "dist_out is null");
-  const size_t bytes = ss_layout(n, m).total;
-  if (bytes > kNoallocBytes)
+  const size_t bytes = ss_layout(n, m).total - sizeof(SsCtl) + kNoallocCtl;
+  if (bytes > (size_t)DAWN_NOALLOC_SCRATCH_BYTES)
     return set_error(DAWN_E_WORKSPACE,
                      "graph needs %zu bytes of scratch; dawn_sssp_noalloc holds %zu (use dawn_sssp_ws)",
                      bytes, (size_t)DAWN_NOALLOC_SCRATCH_BYTES);
