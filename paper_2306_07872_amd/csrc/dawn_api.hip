@@ -52,9 +52,11 @@ __device__ __align__(256) uint32_t g_run_latch[64];
 // object until the process ends.  Host code never names the array in a launch
 // or copy; it uses the device address that hipGetSymbolAddress returned with
 // that device current (DevInfo::noalloc).
-// The control block comes on top of the documented bytes, which the arrays that
-// grow with the graph may fill.
-constexpr size_t kNoallocBytes = DAWN_NOALLOC_SCRATCH_BYTES + sizeof(SsCtl);
+// On top of the documented bytes, which the queues and three bitmaps may fill,
+// come the control block and the fourth bitmap (SsLayout::df, the layout's last
+// part: a bit per vertex, whose queue entries alone take 64).
+constexpr size_t kNoallocBytes =
+    DAWN_NOALLOC_SCRATCH_BYTES + sizeof(SsCtl) + DAWN_NOALLOC_SCRATCH_BYTES / 64 + 256;
 // What the control block counts for when a graph is held against the documented
 // bytes: a fixed figure, so that a larger block does not narrow what is accepted.
 constexpr size_t kNoallocCtl = 2816;
@@ -501,7 +503,7 @@ extern "C" dawn_status dawn_sssp_noalloc(const int32_t* rowptr, const int32_t* c
   if (st != DAWN_OK) return st;
   if (source < 0 || source >= n) return set_error(DAWN_E_INVALID, "source %d out of range", source);
   if (!dist_out) return set_error(DAWN_E_INVALID, "dist_out is null");
-  const size_t bytes = ss_layout(n, m).total - sizeof(SsCtl) + kNoallocCtl;
+  const size_t bytes = ss_layout(n, m).df - sizeof(SsCtl) + kNoallocCtl;
   if (bytes > (size_t)DAWN_NOALLOC_SCRATCH_BYTES)
     return set_error(DAWN_E_WORKSPACE,
                      "graph needs %zu bytes of scratch; dawn_sssp_noalloc holds %zu (use dawn_sssp_ws)",

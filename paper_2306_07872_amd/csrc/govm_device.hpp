@@ -583,6 +583,7 @@ struct SsArgs {
   int4* qwg[2];           // delta, workgroup tier: {row, first edge, edges, first chunk?}
   uint32_t* bm[2];        // beta dedup bitmaps [step % 2]
   uint32_t* hv;           // rows with more than t_lane edges (queued; shorter rows are scanned)
+  uint32_t* df;           // short rows that the last step left in the frontier (deferral)
   uint32_t cap_v, cap_wg;
   SsCtl* ctl;
   unsigned long long bar_ticks;  // grid-barrier wait bound (persistent launches)

@@ -129,7 +129,7 @@ struct Carver {
 
 // ----- single source ---------------------------------------------------------
 struct SsLayout {
-  size_t ctl, qwave[2], qwg[2], bm[2], hv, total;
+  size_t ctl, qwave[2], qwg[2], bm[2], hv, df, total;
   uint32_t cap_v, cap_wg;
   int64_t nwords;
 };

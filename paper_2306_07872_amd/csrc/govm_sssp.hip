@@ -49,7 +49,11 @@ namespace dawn {
 // a 2048 x 2048 grid with fp32 weights every vertex used to be expanded 72
 // times, on an ER graph 2.8 times.  So a step expands the frontier rows up to
 // thr = M + delta (M: the smallest distance in the frontier) and leaves the
-// others in the frontier.  The fixed point does not depend on the order
+// others in the frontier: their bits go to a bitmap of their own (df), read and
+// written by the lane that scans the word, so that the next step's bitmap holds
+// the vertices that the step lowered and nothing else, and is counted as such.
+// (Rows of the queued tiers are never left: a queue entry lasts one step.)  The
+// fixed point does not depend on the order
 // (distances are unique), and a row at M is always expanded.  With weights >= 0
 // no later path can lower it, so every step settles a vertex and at most n
 // steps are taken, as without deferral.  At unit weights all frontier rows have
@@ -204,6 +208,7 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
   for (int64_t i = tid; i < nwords; i += stride) {
     bm0[i] = seed >= 0 && i == seed >> 5 ? 1u << (seed & 31) : 0u;
     bm1[i] = 0;
+    A.df[i] = 0;
   }
   if (hv) {
     // a wavefront per 64 vertices: the ballot's halves are two bitmap words
@@ -365,7 +370,7 @@ __device__ __forceinline__ void scan_rows(ScanRows& st, uint32_t bits, F&& f) {
 struct SsShared {
   DealRows<4096, true> rows[kMaxWavesPerBlock];  // lane-tier batch
   ScanRows scan[kMaxWavesPerBlock];        // bitmap block
-  uint32_t def[kMaxWavesPerBlock][kWave];  // deferred rows, by word of the block
+  uint32_t def[kMaxWavesPerBlock][kWave];  // rows left for later, by word of the block
   int32_t qw[kLdsQWave];
   uint32_t nqw, upd, gbase_w;
   uint32_t minp, work, heavy;  // smallest key left in the frontier, edges expanded, rows queued
@@ -607,25 +612,6 @@ __device__ __forceinline__ bool ss_skip_row(const SsArgs& A, int nxt, int32_t u)
   return A.skip && ((ld_agent(&A.bm[nxt][u >> 5]) >> (u & 31)) & 1u);
 }
 
-// Leave row u (one of the queued tiers) in the frontier: its next bit, and for
-// its first setter the next queue.  Reached by the whole wavefront.
-__device__ __forceinline__ void ss_defer_row(const SsArgs& A, bool lead, int32_t u, int32_t off,
-                                             uint32_t du, int nxt, int rn, Acc& acc, SsShared& sh,
-                                             StepSeen& seen) {
-  bool first = false;
-  int32_t start = 0, deg = 0;
-  if (lead) {
-    const uint32_t bit = 1u << (u & 31);
-    first = (atomicOr(&A.bm[nxt][u >> 5], bit) & bit) == 0u;
-    seen.minp = min(seen.minp, du);
-    sh.upd = 1u;
-    acc.im -= first ? 1ull : 0ull;  // counted again by the next scan
-    start = A.rowptr[u - off];
-    deg = A.rowptr[u - off + 1] - start;
-  }
-  ss_queue_row(A, first, u, start, deg, nxt, rn, sh);
-}
-
 // What the copy of vertex u adds to vertex ids (0 without copies).
 template <bool COPIES>
 __device__ __forceinline__ int32_t copy_off(const SsArgs& A, int32_t u) {
@@ -637,8 +623,8 @@ __device__ __forceinline__ int32_t copy_off(const SsArgs& A, int32_t u) {
 }
 
 // Returns true when the step was a pull step.
-// thr: rows above it are left in the frontier (not kAll).  count: the scan counts the frontier's vertices as lowered by
-// the previous step (rows left in the frontier are taken off again).
+// thr: short rows above it are left in the frontier (not kAll).  count: the scan
+// counts the vertices that the previous step lowered.
 // PULL: pull steps may run (step launches with a reverse graph); the push-only
 // instance keeps none of their code.
 // The step's queue counts (lane, wave, workgroup-chunk tiers); read at the
@@ -694,13 +680,6 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
       // one value per wavefront (another wavefront may read a lower one; then
       // the row has been lowered in this step and is queued for the next)
       const uint32_t du = (uint32_t)__builtin_amdgcn_readfirstlane((int)dul);
-      if (NF && du > thr) {
-        // left in the frontier: whichever chunk of the row sets the next bit
-        // queues the whole row again (a chunk that is expanded meanwhile, with a
-        // value lowered in this step, is expanded once more then)
-        if (wave == 0) ss_defer_row(A, lane == 0, u, uoff, du, nxt, rn, acc, sh, seen);
-        continue;
-      }
       const int32_t len = skipped ? 0 : r.z;
       if (threadIdx.x == 0) {
         acc.es += (unsigned long long)len;
@@ -732,10 +711,6 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
       const int32_t start = A.rowptr[u - uoff], last = A.rowptr[u - uoff + 1];
       const bool skipped = ss_skip_row(A, nxt, u);
       const uint32_t du = (uint32_t)__builtin_amdgcn_readfirstlane((int)dul);
-      if (NF && du > thr) {
-        ss_defer_row(A, lane == 0, u, uoff, du, nxt, rn, acc, sh, seen);
-        continue;
-      }
       const int32_t end = skipped ? start : last;
       if (lane == 0) {
         acc.fe += 1;
@@ -777,14 +752,15 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
       const int64_t wi = w0 + lo + (lane >> gs) * span;
       // (a group's first word; words of later groups lie further on)
       if (w0 + ((int64_t)gw << gs) >= nwords) break;
-      uint32_t bits = 0u;
+      uint32_t bits = 0u, left = 0u;
       if (wi < nwords) {
         const uint32_t word = ld_agent(&A.bm[cur][wi]), hv = A.hv[wi];
+        if (NF) left = ld_agent(&A.df[wi]);
         if (word) {
           st_agent(&A.bm[cur][wi], 0u);
-          bits = word & ~hv;
           if (count) acc.im += (unsigned long long)__popc(word);
         }
+        bits = (word & ~hv) | left;
       }
       uint32_t* def = sh.def[wave];
       if (NF) def[lane] = 0u;
@@ -825,11 +801,8 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
       if (NF) {
         wave_lds_sync();
         const uint32_t x = def[lane];
-        if (x) {
-          acc.im -= (unsigned long long)__popc(x);  // counted again by the next scan
-          atomicOr(&A.bm[nxt][wi], x);
-          sh.upd = 1u;
-        }
+        if (x != left) st_agent(&A.df[wi], x);
+        if (x) sh.upd = 1u;
       }
     }
 
@@ -1017,14 +990,18 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
   if (blockIdx.x == 0 && threadIdx.x == 0) ss_zero_rotation(C, step);
   Acc acc;
   const uint32_t gb = blockIdx.x, nb = gridDim.x;
-  const bool near = nf_weights<WT>() && C->nf.floor != 0.f;  // (written by an earlier launch)
-  bool pulled;
-  if (near)
-    pulled = ss_step<WT, PULL, kNear, false>(A, step, gb, nb, acc, sh, ss_counts(A, step), C->nf.thr,
-                                      !PULL && step > 0);
-  else
+  // (written by an earlier launch; with pull steps no row waits: they take the
+  // frontier from one bitmap, and their rule needs all of its out-edges counted)
+  const bool near = !PULL && nf_weights<WT>() && C->nf.floor != 0.f;
+  bool pulled = false;
+  if constexpr (!PULL) {
+    if (near)
+      ss_step<WT, false, kNear, false>(A, step, gb, nb, acc, sh, ss_counts(A, step), C->nf.thr,
+                                       step > 0);
+  }
+  if (!near)
     pulled = ss_step<WT, PULL, kAll, false>(A, step, gb, nb, acc, sh, ss_counts(A, step), kNoKey,
-                                     !PULL && step > 0);
+                                            !PULL && step > 0);
   if (near && threadIdx.x == 0 && sh.minp != kNoKey)
     atomicMin(&C->minp[(step + 1) % kRot].v, sh.minp);
   // counters, and the next frontier's out-edges and rows (its pull decision)
@@ -1575,6 +1552,7 @@ SsLayout ss_layout(int64_t n, int64_t m) {
   for (int i = 0; i < 2; i++) L.qwg[i] = c.take((size_t)L.cap_wg * 16);
   for (int i = 0; i < 2; i++) L.bm[i] = c.take((size_t)L.nwords * 4);
   L.hv = c.take((size_t)L.nwords * 4);
+  L.df = c.take((size_t)L.nwords * 4);
   L.total = c.off;
   return L;
 }
@@ -1834,6 +1812,7 @@ static SsLayout ss_copies_layout(int64_t n, int64_t m, int64_t k) {
   for (int i = 0; i < 2; i++) L.qwg[i] = c.take((size_t)L.cap_wg * 16);
   for (int i = 0; i < 2; i++) L.bm[i] = c.take((size_t)L.nwords * 4);
   L.hv = c.take((size_t)L.nwords * 4);
+  L.df = c.take((size_t)L.nwords * 4);
   L.total = c.off;
   return L;
 }
@@ -1909,6 +1888,7 @@ dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const vo
     A.bm[i] = reinterpret_cast<uint32_t*>(base + L.bm[i]);
   }
   A.hv = reinterpret_cast<uint32_t*>(base + L.hv);
+  A.df = reinterpret_cast<uint32_t*>(base + L.df);
   A.cap_v = L.cap_v;
   A.cap_wg = L.cap_wg;
   A.ctl = reinterpret_cast<SsCtl*>(base + L.ctl);
@@ -1952,6 +1932,7 @@ dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, 
     A.bm[i] = reinterpret_cast<uint32_t*>(base + L.bm[i]);
   }
   A.hv = reinterpret_cast<uint32_t*>(base + L.hv);
+  A.df = reinterpret_cast<uint32_t*>(base + L.df);
   A.cap_v = L.cap_v;
   A.cap_wg = L.cap_wg;
   A.ctl = reinterpret_cast<SsCtl*>(base + L.ctl);
