@@ -49,9 +49,12 @@ namespace dawn {
 // a 2048 x 2048 grid with fp32 weights every vertex used to be expanded 72
 // times, on an ER graph 2.8 times.  So a step expands the frontier rows up to
 // thr = M + delta (M: the smallest distance in the frontier) and leaves the
-// others in the frontier: their bits go to a bitmap of their own (df), read and
-// written by the lane that scans the word, so that the next step's bitmap holds
-// the vertices that the step lowered and nothing else, and is counted as such.
+// others in the frontier: their bits go to a bitmap of their own, read and written
+// by the lane that scans the word alone, so that the next step's bitmap holds the
+// vertices that the step lowered and nothing else, and is counted as such.  A
+// persistent launch keeps the words of a wavefront's first block in a register and
+// the others in df (2048 x 2048 grid: 40.4 ms; 42.2 with all of them in df; 39.4 with
+// the bits in the next step's bitmap, where they could not be told apart).
 // (Rows of the queued tiers are never left: a queue entry lasts one step.)  The
 // fixed point does not depend on the order
 // (distances are unique), and a row at M is always expanded.  With weights >= 0
@@ -643,9 +646,33 @@ __device__ __forceinline__ SsCounts ss_counts(const SsArgs& A, uint32_t step) {
   return SsCounts{min(ld_agent(&C->cnt[rc][1].v), A.cap_v), min(ld_agent(&C->cnt[rc][2].v), A.cap_wg)};
 }
 
+// How the scan's blocks fall on the wavefronts.  Groups of 1 << gs neighbouring
+// words go to the wavefronts in turn (four words, 128 vertices, or fewer when that
+// leaves wavefronts without a group; up to 64 words a wavefront at a time), so a
+// run of frontier rows is shared by many of them.  With blocks of 32 words per
+// wavefront the slowest workgroup took 13 us of a 15 us step on a 2048 x 2048
+// grid, against 5 on average.
+struct ScanSplit {
+  int64_t nwords, span, first;  // words; between a lane's neighbours' groups; of the wavefront's first group
+  int gs;
+  __device__ __forceinline__ ScanSplit(int32_t n, uint32_t gw, uint32_t nwv)
+      : nwords(((int64_t)n + 31) / 32), gs(2) {
+    while (gs > 0 && (nwords >> gs) < (int64_t)nwv) gs--;
+    span = (int64_t)nwv << gs;
+    first = (int64_t)gw << gs;
+  }
+  // the word of lane l in the block that starts at w0
+  __device__ __forceinline__ int64_t word(int64_t w0, int l) const {
+    return w0 + first + (l & ((1 << gs) - 1)) + (l >> gs) * span;
+  }
+  __device__ __forceinline__ int64_t block() const { return span << (6 - gs); }
+};
+
+// left0: the rows left for later of this lane's word in the wavefront's first block
+// (those of the other blocks are in df).
 template <int WT, bool PULL, int MODE, bool COPIES>
 __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb, Acc& acc,
-                        SsShared& sh, SsCounts counts, uint32_t thr, bool count) {
+                        SsShared& sh, SsCounts counts, uint32_t thr, bool count, uint32_t& left0) {
   constexpr bool NF = MODE != kAll;
   StepSeen seen;
   const int cur = step & 1, nxt = cur ^ 1;
@@ -735,41 +762,30 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
 
     // lane tier: rows of at most t_lane edges are not queued.  The wavefronts
     // scan the step's bitmap, clear it and take its short rows 64 at a time; the
-    // rows' edges are dealt out to the lanes.  Groups of 1 << gs neighbouring
-    // words go to the wavefronts in turn (four words, 128 vertices, or fewer when
-    // that leaves wavefronts without a group; up to 64 words a wavefront at a
-    // time), so a run of frontier rows is shared by many of them.  With blocks of
-    // 32 words per wavefront the slowest workgroup took 13 us of a 15 us step on
-    // a 2048 x 2048 grid, against 5 on average.  The scan clears every word,
+    // rows' edges are dealt out to the lanes.  The scan clears every word,
     // heavy rows' bits included: nothing else reads this bitmap during a push
     // step.
-    const int64_t nwords = ((int64_t)A.n + 31) / 32;
-    int gs = 2;
-    while (gs > 0 && (nwords >> gs) < (int64_t)nwv) gs--;
-    const int64_t span = (int64_t)nwv << gs;  // words that lie between a lane's neighbours' groups
-    const int64_t lo = ((int64_t)gw << gs) + (lane & ((1 << gs) - 1));
-    for (int64_t w0 = 0; w0 < nwords; w0 += span << (6 - gs)) {
-      const int64_t wi = w0 + lo + (lane >> gs) * span;
-      // (a group's first word; words of later groups lie further on)
-      if (w0 + ((int64_t)gw << gs) >= nwords) break;
+    const ScanSplit split(A.n, gw, nwv);
+    for (int64_t w0 = 0; w0 + split.first < split.nwords; w0 += split.block()) {
+      const int64_t wi = split.word(w0, lane);
+      uint32_t* def = sh.def[wave];
       uint32_t bits = 0u, left = 0u;
-      if (wi < nwords) {
+      if (wi < split.nwords) {
         const uint32_t word = ld_agent(&A.bm[cur][wi]), hv = A.hv[wi];
-        if (NF) left = ld_agent(&A.df[wi]);
+        if (NF) left = w0 == 0 ? left0 : ld_agent(&A.df[wi]);
         if (word) {
           st_agent(&A.bm[cur][wi], 0u);
           if (count) acc.im += (unsigned long long)__popc(word);
         }
-        bits = (word & ~hv) | left;
+        if (word) bits = word & ~hv;
+        bits |= left;
       }
-      uint32_t* def = sh.def[wave];
       if (NF) def[lane] = 0u;
       scan_rows(sh.scan[wave], bits, [&](bool has, int o, int bit) {
         int32_t start = 0, deg = 0, uoff = 0;
         uint32_t du = 0;
         if (has) {
-          const int64_t wo = w0 + ((int64_t)gw << gs) + (o & ((1 << gs) - 1)) + (o >> gs) * span;
-          const int32_t u = (int32_t)(wo * 32 + bit);
+          const int32_t u = (int32_t)(split.word(w0, o) * 32 + bit);
           uoff = copy_off<COPIES>(A, u);
           start = A.rowptr[u - uoff];
           deg = A.rowptr[u - uoff + 1] - start;
@@ -801,7 +817,8 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
       if (NF) {
         wave_lds_sync();
         const uint32_t x = def[lane];
-        if (x != left) st_agent(&A.df[wi], x);
+        if (w0 == 0) left0 = x;
+        else if (x != left) st_agent(&A.df[wi], x);
         if (x) sh.upd = 1u;
       }
     }
@@ -947,16 +964,23 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_
   // launches that count as they enqueue came before
   bool count = step > 0 && !A.counted;
   int32_t status = 1;
+  const uint32_t gb = blockIdx.x, nb = gridDim.x;
+  const uint32_t wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+  uint32_t left0 = 0u;
+  if (nf_weights<WT>()) {
+    const ScanSplit split(A.n, wave * nb + gb, nb * W);  // (as in ss_step)
+    const int64_t wi = split.word(0, lane_id());
+    if (wi < split.nwords) left0 = A.df[wi];  // (written by an earlier launch)
+  }
   for (;;) {
     if (blockIdx.x == 0 && threadIdx.x == 0) ss_zero_rotation(C, step);
-    const uint32_t gb = blockIdx.x, nb = gridDim.x;
     if (nf_weights<WT>() && nf.floor != 0.f) {
       if (next.fresh)
-        ss_step<WT, false, kFresh, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count);
+        ss_step<WT, false, kFresh, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count, left0);
       else
-        ss_step<WT, false, kNear, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count);
+        ss_step<WT, false, kNear, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count, left0);
     } else {
-      ss_step<WT, false, kAll, COPIES>(A, step, gb, nb, acc, sh, counts, kNoKey, count);
+      ss_step<WT, false, kAll, COPIES>(A, step, gb, nb, acc, sh, counts, kNoKey, count, left0);
     }
     count = true;
     if (!ss_grid_sync<WT>(C, gridDim.x, bar_base, epoch, A.bar_ticks, sh, nf, A.nf_work, next)) {
@@ -994,14 +1018,22 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
   // frontier from one bitmap, and their rule needs all of its out-edges counted)
   const bool near = !PULL && nf_weights<WT>() && C->nf.floor != 0.f;
   bool pulled = false;
+  uint32_t left0 = 0u;
   if constexpr (!PULL) {
-    if (near)
+    if (near) {
+      const uint32_t wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+      const ScanSplit split(A.n, wave * nb + gb, nb * W);  // (as in ss_step)
+      const int64_t wi = split.word(0, lane_id());
+      if (wi < split.nwords) left0 = A.df[wi];
+      const uint32_t was = left0;
       ss_step<WT, false, kNear, false>(A, step, gb, nb, acc, sh, ss_counts(A, step), C->nf.thr,
-                                       step > 0);
+                                       step > 0, left0);
+      if (left0 != was) A.df[wi] = left0;
+    }
   }
   if (!near)
     pulled = ss_step<WT, PULL, kAll, false>(A, step, gb, nb, acc, sh, ss_counts(A, step), kNoKey,
-                                            !PULL && step > 0);
+                                            !PULL && step > 0, left0);
   if (near && threadIdx.x == 0 && sh.minp != kNoKey)
     atomicMin(&C->minp[(step + 1) % kRot].v, sh.minp);
   // counters, and the next frontier's out-edges and rows (its pull decision)
