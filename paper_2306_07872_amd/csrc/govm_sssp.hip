@@ -1246,7 +1246,10 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
     const float floor =
         A.m >= kNfMinCu ? nf_floor<WT>(n, A.m, A.rowptr, A.w, 1024) : 0.f;
     NfState nf{kNoKey, floor, floor, 0u};
-    const bool near = nf_weights<WT>() && floor != 0.f;
+    // (the words of the rows left for later stay in a register of the lane that scans
+    // them, one word a lane, as all do at 1024 threads)
+    const bool near = nf_weights<WT>() && floor != 0.f && nwords <= kWave * W;
+    uint32_t left = 0u;
     __syncthreads();
     if constexpr (MULTI) {
       if (threadIdx.x == 0) {
@@ -1276,7 +1279,11 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
         uint32_t bits = 0u;
         if (wi < nwords) {
           bits = bc[wi];
-          if (bits) bc[wi] = 0u;
+          if (bits) {
+            bc[wi] = 0u;
+            if (step > 0) acc.im += (unsigned long long)__popc(bits);  // lowered by the last step
+          }
+          bits |= left;
         }
         scan_rows(st.scan, bits, [&](bool has, int o, int bit) {
           int32_t start = 0, deg = 0;
@@ -1292,7 +1299,7 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
             }
             du = sh.dist[u];
             if (near && du > nf.thr) {
-              atomicOr(&bn[u >> 5], 1u << (u & 31));
+              atomicOr(&bc[u >> 5], 1u << (u & 31));  // (the wavefront's own word, just cleared)
               seen.minp = min(seen.minp, du);
               deg = 0;
             }
@@ -1325,7 +1332,6 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
             for (int j = 0; j < kUnrollCu; j++) {
               if (ok[j] && cand[j] < dv[j] && v[j] != src &&
                   cand[j] < atomicMin(&sh.dist[v[j]], cand[j])) {
-                acc.im += 1;
                 upd = true;
                 seen.minp = min(seen.minp, cand[j]);
                 __hip_atomic_fetch_or(&bn[v[j] >> 5], 1u << (v[j] & 31), __ATOMIC_RELAXED,
@@ -1334,6 +1340,11 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
             }
           });
         });
+        if (near) {
+          wave_lds_sync();
+          left = wi < nwords ? bc[wi] : 0u;
+          if (left) bc[wi] = 0u;
+        }
       }
       // three flags rotate: step t sets (t+1) mod 3, read after the barrier,
       // and clears (t+2) mod 3, which nothing else touches before step t+1 ends
@@ -1362,6 +1373,9 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
       if (!more) { status = 1; break; }
       if (step >= (uint32_t)n) { status = 0; break; }
     }
+    if (status == 0)  // lowered by the last step
+      for (int i = threadIdx.x; i < nwords; i += blockDim.x)
+        acc.im += (unsigned long long)__popc(sh.bm[step & 1][i]);
     for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = key_value<WT>(sh.dist[i]);
   }
   ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part);  // (after the last step's barrier)
@@ -1547,14 +1561,16 @@ __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int
         for (int i = 0; i < kLdsHalf; i++) {
           const uint32_t v = uv[h + i] >> 16;
           if (((need >> i) & 1u) && cand[i] < old[i]) {
-            acc.im += 1;
             upd = true;
             __hip_atomic_fetch_or(&bn[v >> 5], 1u << (v & 31), __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_WORKGROUP);
           }
         }
       }
-      for (int i = t; i < nwords; i += kLdsThreads) sh.bm[(step + 2) % 3][i] = 0u;
+      for (int i = t; i < nwords; i += kLdsThreads) {
+        if (step > 0) acc.im += (unsigned long long)__popc(bc[i]);  // lowered by the last step
+        sh.bm[(step + 2) % 3][i] = 0u;
+      }
       if (t == 0) sh.upd[(step + 2) % 3] = 0u;
       if (upd) sh.upd[(step + 1) % 3] = 1u;
       __syncthreads();
@@ -1563,6 +1579,9 @@ __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int
       if (!more) { status = 1; break; }
       if (step >= (uint32_t)n) { status = 0; break; }
     }
+    if (status == 0)  // lowered by the last step
+      for (int i = t; i < nwords; i += kLdsThreads)
+        acc.im += (unsigned long long)__popc(sh.bm[step % 3][i]);
     for (int i = t; i < n; i += kLdsThreads) out[i] = key_value<WT>(sh.dist[i]);
   }
   ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part);

@@ -101,3 +101,47 @@ def test_never_below_the_reached_vertices(dawn):
             finally:
                 dawn.set_tuning(**prev)
             assert dawn.read_info(info)["improvements"] >= int(np.isfinite(d).sum()) - 1
+
+
+@pytest.mark.parametrize("threads", [0, 256])
+@pytest.mark.parametrize("wk", ["u32", "f32"])
+def test_lowered_while_waiting_in_one_workgroup(dawn, wk, threads):
+    g = _far_targets(wk)
+    csr = dawn.Csr.from_graph(g)
+    prev = dawn.set_tuning(small_m=1 << 20, wg_threads=threads)
+    try:
+        announce("improvements, one workgroup", wk, threads)
+        info = dawn.info_tensor()
+        assert_sssp_matches(g, 0, to_np(dawn.sssp(csr, 0, info=info)), tag="one workgroup")
+        assert dawn.read_info(info)["improvements"] == L + T * (L + 1)
+        info = dawn.info_tensor()
+        D = to_np(dawn.msssp(csr, np.array([0, L + 1, 0], np.int32), info=info))
+        assert_sssp_matches(g, 0, D[2], tag="workgroup per source")
+        assert dawn.read_info(info)["improvements"] == 2 * (L + T * (L + 1))
+    finally:
+        dawn.set_tuning(**prev)
+
+
+@pytest.mark.parametrize("mids", [700, 8000])
+def test_lowered_many_times_in_one_step(dawn, mids):
+    """A source, `mids` vertices at descending distances, and two targets that each
+    of them lowers, all in one step: the targets count once.  The edge-parallel and
+    the bitmap-scan kernel, alone and per source, against the tile."""
+    a = np.arange(1, mids + 1)
+    src = np.concatenate([np.zeros(mids, np.int64), a, a])
+    dst = np.concatenate([a, np.full(mids, mids + 1), np.full(mids, mids + 2)])
+    w = np.concatenate([2 * mids - a, np.full(2 * mids, 5)]).astype(np.uint32)
+    g = graphgen.from_edges(mids + 3, src, dst, w, "u32")
+    csr = dawn.Csr.from_graph(g)
+    announce("improvements, many decreases", mids)
+    info = dawn.info_tensor()
+    dawn.sssp(csr, 0, info=info)
+    assert dawn.read_info(info)["improvements"] == mids + 2
+    for tune in (dict(), dict(mode=1)):
+        prev = dawn.set_tuning(**tune)
+        try:
+            info = dawn.info_tensor()
+            dawn.msssp(csr, np.array([0, 3, 0], np.int32), info=info)
+        finally:
+            dawn.set_tuning(**prev)
+        assert dawn.read_info(info)["improvements"] == 2 * (mids + 2) + 2, tune
