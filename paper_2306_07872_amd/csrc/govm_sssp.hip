@@ -992,6 +992,11 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_
     if (step >= (uint32_t)A.n) { status = 0; break; }
     counts = next.queued ? ss_counts(A, step) : SsCounts{0u, 0u};
   }
+  if (status == 0) {  // no scan follows that would count what the last step lowered
+    const int64_t nwords = ((int64_t)A.n + 31) / 32;
+    for (int64_t i = (int64_t)gb * blockDim.x + threadIdx.x; i < nwords; i += (int64_t)nb * blockDim.x)
+      acc.im += (unsigned long long)__popc(ld_agent(&A.bm[step & 1][i]));
+  }
   SsCounters& S = C->ctr;
   flush_acc(acc, &S.fe, &S.es, &S.im, nullptr, nullptr);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1045,9 +1050,15 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
     if (pulled)
       for (int64_t i = threadIdx.x; i < ((int64_t)A.n + 31) / 32; i += blockDim.x)
         A.bm[step & 1][i] = 0u;
-    if (threadIdx.x != 0) return;
     const uint32_t upd = ld_agent(&C->upd[(step + 1) % kRot]);
     const uint32_t ns = step + 1;
+    if (!PULL && upd && ns >= (uint32_t)A.n) {  // as in the persistent launch
+      unsigned long long im = 0;
+      for (int64_t i = threadIdx.x; i < ((int64_t)A.n + 31) / 32; i += blockDim.x)
+        im += (unsigned long long)__popc(ld_agent(&A.bm[ns & 1][i]));
+      if (im) atomicAdd(&S.im, im);
+    }
+    if (threadIdx.x != 0) return;
     st_agent(&C->step, ns);
     if (near && upd) {
       NfState nf = C->nf;  // (only a launch's last workgroup writes it)

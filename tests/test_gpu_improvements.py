@@ -145,3 +145,34 @@ def test_lowered_many_times_in_one_step(dawn, mids):
         finally:
             dawn.set_tuning(**prev)
         assert dawn.read_info(info)["improvements"] == 2 * (mids + 2) + 2, tune
+def test_counted_up_to_the_step_limit(dawn):
+    """A negative cycle in one workgroup: n steps, each lowering one vertex of the
+    ring that the source leads into."""
+
+
+STEP_LIMIT_TUNINGS = [dict(), dict(small_m=0), dict(small_m=0, mode=1, step_launches=10),
+                      dict(small_m=0, mode=1, step_launches=4096),
+                      dict(small_m=0, mode=1, step_launches=4096, ss_pull=0)]
+
+
+@pytest.mark.parametrize("ti", range(len(STEP_LIMIT_TUNINGS)))
+def test_counted_up_to_the_step_limit(dawn, ti):
+    """A negative cycle: n steps, each lowering one vertex of the ring that the
+    source leads into, the last one among them."""
+    tune = STEP_LIMIT_TUNINGS[ti]
+    ring = 70
+    src = np.concatenate([[0], np.arange(1, ring + 1)])
+    dst = np.concatenate([[1], np.arange(1, ring + 1) % ring + 1])
+    g = graphgen.from_edges(ring + 1, src, dst, np.full(ring + 1, -1, np.int32), "i32")
+    csr = dawn.Csr.from_graph(g)
+    tg = dawn.tgraph(csr) if "ss_pull" in tune else None
+    announce("improvements, step limit", tune)
+    prev = dawn.set_tuning(**tune)
+    try:
+        info = dawn.info_tensor()
+        dawn.sssp(csr, 0, info=info, tgraph=tg, check=False)
+        i = dawn.read_info(info)
+    finally:
+        dawn.set_tuning(**prev)
+    assert i["converged"] == 0 and i["steps"] == g.n
+    assert i["improvements"] == g.n
