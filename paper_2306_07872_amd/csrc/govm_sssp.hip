@@ -1727,15 +1727,19 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   // scale 22 2.21 / 2.55 ms, scale 20 0.81 / 0.99 ms, 64 ER graphs (118M edges)
   // 5.74 / 6.10 ms, the 2048^2 grid 43.4 / 47.2 ms.
   int mode = T.mode;
-  // (Pull steps need step launches: large graphs with a reverse graph keep them.
-  // So do captured runs, whose replays on several streams would else be
-  // persistent launches that nothing orders.)
-  // One workgroup only where its LDS holds the run: past that, a kernel with the
-  // state in global memory took 1606 us on an ER graph of 60,000 vertices and
-  // 120,000 edges, the persistent launch 404 us.
-  if (mode == 0) mode = (int64_t)A.m <= (int64_t)T.small_m && A.n <= kCuMaxN ? 3
+  // (Pull steps need step launches: large graphs with a reverse graph keep them,
+  // and so do captured runs of that size.)
+  // One workgroup's LDS where it holds the run; past that, a kernel with the state
+  // in global memory took 1606 us on an ER graph of 60,000 vertices and 120,000
+  // edges, the persistent launch 404 us.  A captured run of so few edges takes the
+  // persistent launch with one workgroup (1135 us): its replays are ordered by
+  // nothing, and on several streams at once they would wait for each other's
+  // workgroups at grid barriers.
+  const bool capturing = stream_capturing(stream), small = (int64_t)A.m <= (int64_t)T.small_m;
+  const bool lone = mode == 0 && small && capturing;
+  if (mode == 0) mode = small && A.n <= kCuMaxN ? 3
                         : (int64_t)A.m >= (int64_t)T.step_min_m ||
-                          ((A.pull_min >= 0 || stream_capturing(stream)) && A.m >= 1 << 25)
+                          ((A.pull_min >= 0 || capturing) && A.m >= 1 << 25)
                             ? 1 : 2;
   const int threads = T.wg_threads > 0 ? T.wg_threads : mode == 1 ? 512 : 1024;
   const int fill_blocks = (int)std::min<int64_t>(4096, (A.n + 255) / 256 + 1);
@@ -1792,6 +1796,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     int grid = std::min(std::min(r.grid, kMaxGrid), ss_persistent_wgs(A.n, A.m, r.grid));
     if (T.grid > 0 && T.grid < grid) grid = T.grid;
     if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
+    if (lone) grid = 1;
     SsArgs a = A;
     a.counted = mode == 1 && A.pull_min >= 0;
     ss_persistent_tiers(a);
