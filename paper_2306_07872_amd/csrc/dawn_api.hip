@@ -80,6 +80,11 @@ const DevInfo& dev_info() {
     // The array's name is a host-side stand-in: kernels get this address.
     void* q = nullptr;
     di.noalloc = hipGetSymbolAddress(&q, HIP_SYMBOL(g_noalloc_scratch)) == hipSuccess ? q : nullptr;
+    // made here, not by the first launch that needs it: dawn_sssp_noalloc makes no events
+    if (hipEventCreateWithFlags(&di.gate, hipEventDisableTiming) != hipSuccess) {
+      di.gate = nullptr;
+      (void)hipGetLastError();
+    }
     di.device = d;
   }
   return di;
@@ -92,29 +97,22 @@ bool stream_capturing(hipStream_t stream) {
   return true;
 }
 
-// One event per device, created by its first gated launch and kept until the
-// process ends.
 static std::mutex g_gate_mu[64];
-static hipEvent_t g_gate[64];
 
 PersistentGate::PersistentGate(hipStream_t s, int grid)
     : stream(s), on(grid > 1 && !stream_capturing(s)) {
   if (!on) return;
-  const int d = dev_info().device;
-  g_gate_mu[d].lock();
-  if (g_gate[d]) {
-    hipStreamWaitEvent(stream, g_gate[d], 0);
-  } else if (hipEventCreateWithFlags(&g_gate[d], hipEventDisableTiming) != hipSuccess) {
-    g_gate[d] = nullptr;
-    (void)hipGetLastError();
-  }
+  const DevInfo& di = dev_info();
+  g_gate_mu[di.device].lock();
+  // (an event that has not been recorded yet is not waited for)
+  if (di.gate) hipStreamWaitEvent(stream, di.gate, 0);
 }
 
 PersistentGate::~PersistentGate() {
   if (!on) return;
-  const int d = dev_info().device;
-  if (g_gate[d]) hipEventRecord(g_gate[d], stream);
-  g_gate_mu[d].unlock();
+  const DevInfo& di = dev_info();
+  if (di.gate) hipEventRecord(di.gate, stream);
+  g_gate_mu[di.device].unlock();
 }
 
 // Residency rule of a gfx950 compute unit: 4 SIMDs, each with 512 VGPRs per

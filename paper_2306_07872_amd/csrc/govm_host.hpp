@@ -45,6 +45,7 @@ struct DevInfo {
   bool coop = false;
   uint32_t* latch = nullptr;  // this device's run-status latch (device address)
   void* noalloc = nullptr;    // this device's copy of the no-allocation scratch array
+  hipEvent_t gate = nullptr;  // the last gated launch on any stream (PersistentGate); kept until the process ends
 };
 const DevInfo& dev_info();
 
