@@ -159,6 +159,11 @@ typedef struct {
  * A persistent launch's grid is what the compute units hold at once, by the
  * kernel's compiled VGPR and LDS use (dawn_device_query); a grid barrier that
  * waits longer than barrier_ms ends the run with converged = -2, never a hang.
+ * Two persistent launches that each hold part of the device would wait for each
+ * other, so those of one device are ordered, whatever their streams, and so are
+ * dawn_batch_replay's.  Replays of a graph that a caller captured are not: order
+ * them, unless the captured call runs in one workgroup (single source and batches
+ * with at most small_m edges do, whatever n) or in one workgroup per source.
  * Tile sessions always take step launches.
  * wg_threads: 256, 512 or 1024, or 0 = auto (single source: 512 for step launches,
  * 1024 for persistent launches; tiles: 256 for step launches, 1024 for

@@ -756,6 +756,7 @@ struct dawn_batch {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipStream_t cap_stream = nullptr;
+  int cap_wgs = 1;  // workgroups of the captured run's persistent launch (1: no grid barrier)
 };
 
 __global__ void batch_rows_kernel(const int32_t* rp, int32_t n, int64_t voff, int64_t eoff,
@@ -867,7 +868,8 @@ extern "C" int64_t dawn_batch_vertex_offset(const dawn_batch* b, int32_t i) {
 }
 
 static dawn_status batch_enqueue(dawn_batch* b, const int32_t* sources, void* dist_out,
-                                 dawn_run_info* info, hipStream_t stream, bool capture) {
+                                 dawn_run_info* info, hipStream_t stream, bool capture,
+                                 int* wgs = nullptr) {
   if (!tuning_ok(g_tuning)) return set_error(DAWN_E_INVALID, "tuning out of range");
   SsSeeds seeds;
   seeds.sources_dev = sources;
@@ -875,7 +877,8 @@ static dawn_status batch_enqueue(dawn_batch* b, const int32_t* sources, void* di
   seeds.count = b->count;
   seeds.source = 0;
   return ss_run(b->rowptr, b->colidx, b->w, (int)b->wt, (int32_t)b->total_n,
-                (int32_t)b->total_m, seeds, false, dist_out, b->ws, info, stream, capture);
+                (int32_t)b->total_m, seeds, false, dist_out, b->ws, info, stream, capture, nullptr,
+                wgs);
 }
 
 extern "C" dawn_status dawn_batch_run(dawn_batch* b, const int32_t* sources, void* dist_out,
@@ -911,7 +914,7 @@ extern "C" dawn_status dawn_batch_capture(dawn_batch* b, const int32_t* sources,
   if ((st = hip_check(hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal),
                       "begin capture")) != DAWN_OK)
     return st;
-  dawn_status rs = batch_enqueue(b, sources, dist_out, info, b->cap_stream, true);
+  dawn_status rs = batch_enqueue(b, sources, dist_out, info, b->cap_stream, true, &b->cap_wgs);
   hipGraph_t g = nullptr;
   st = hip_check(hipStreamEndCapture(b->cap_stream, &g), "end capture");
   if (rs != DAWN_OK) {
@@ -925,6 +928,7 @@ extern "C" dawn_status dawn_batch_capture(dawn_batch* b, const int32_t* sources,
 
 extern "C" dawn_status dawn_batch_replay(dawn_batch* b, hipStream_t stream) {
   if (!b || !b->exec) return set_error(DAWN_E_INVALID, "batch has no captured graph");
+  const PersistentGate gate(stream, b->cap_wgs);
   return hip_check(hipGraphLaunch(b->exec, stream), "graph launch");
 }
 

@@ -55,7 +55,8 @@ const DevInfo& dev_info();
 // barriers give up.  Held around a launch, the gate makes the stream wait for
 // the last persistent launch on any stream and records the new one.  A stream
 // that is being captured is left alone (events from outside would end the
-// capture).
+// capture): replays of graphs that the library holds pass the gate themselves,
+// those of a caller's graph are the caller's to order.
 struct PersistentGate {
   hipStream_t stream;
   bool on;
@@ -148,10 +149,11 @@ struct SsSeeds {
 // Enqueue a full single-source (or many-seed) GOVM run on `stream`; nothing
 // waits on the host.  capture=true: never use a cooperative launch (HIP graph
 // capture).  Without `info` the run's status goes to the run-status latch.
+// *wgs: workgroups that wait for each other at grid barriers (1: none).
 dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
                    int32_t n, int32_t m, const SsSeeds& seeds, bool guard_source, void* dist,
                    void* ws, dawn_run_info* info, hipStream_t stream, bool capture,
-                   const void* tgraph = nullptr);
+                   const void* tgraph = nullptr, int* wgs = nullptr);
 
 // Multi-source calls on graphs whose run state fits one workgroup's LDS: one
 // workgroup per source, dist[j * n + v].  Takes no workspace.  wt: kWU32,

@@ -1718,7 +1718,7 @@ static void ss_persistent_tiers(SsArgs& A) {
 template <int WT>
 static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_t* colidx,
                             const SsSeeds& seeds, const SsLayout& L, dawn_run_info* info,
-                            hipStream_t stream, bool capture) {
+                            hipStream_t stream, bool capture, int* wgs) {
   const Tuning& T = tuning();
   const DevInfo& di = dev_info();
   // mode 0 picks: one workgroup when m <= small_m; step launches first when
@@ -1797,6 +1797,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     if (T.grid > 0 && T.grid < grid) grid = T.grid;
     if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
     if (lone) grid = 1;
+    if (wgs) *wgs = grid;
     SsArgs a = A;
     a.counted = mode == 1 && A.pull_min >= 0;
     ss_persistent_tiers(a);
@@ -1969,7 +1970,8 @@ dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const vo
 dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
                    int32_t n, int32_t m, const SsSeeds& seeds, bool guard_source, void* dist,
                    void* ws, dawn_run_info* info, hipStream_t stream, bool capture,
-                   const void* tgraph) {
+                   const void* tgraph, int* wgs) {
+  if (wgs) *wgs = 1;
   const Tuning& T = tuning();
   const SsLayout L = ss_layout(n, m);
   char* base = static_cast<char*>(ws);
@@ -2008,10 +2010,10 @@ dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, 
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
     capture = true;
-  if (wt == kWF32) return ss_run_t<kWF32>(A, rowptr, colidx, seeds, L, info, stream, capture);
-  if (wt == kWUNIT) return ss_run_t<kWUNIT>(A, rowptr, colidx, seeds, L, info, stream, capture);
-  if (wt == kWI32) return ss_run_t<kWI32>(A, rowptr, colidx, seeds, L, info, stream, capture);
-  return ss_run_t<kWU32>(A, rowptr, colidx, seeds, L, info, stream, capture);
+  if (wt == kWF32) return ss_run_t<kWF32>(A, rowptr, colidx, seeds, L, info, stream, capture, wgs);
+  if (wt == kWUNIT) return ss_run_t<kWUNIT>(A, rowptr, colidx, seeds, L, info, stream, capture, wgs);
+  if (wt == kWI32) return ss_run_t<kWI32>(A, rowptr, colidx, seeds, L, info, stream, capture, wgs);
+  return ss_run_t<kWU32>(A, rowptr, colidx, seeds, L, info, stream, capture, wgs);
 }
 
 }  // namespace dawn

@@ -63,3 +63,41 @@ def test_small_captured_batches_wait_for_no_other_workgroup(dawn):
         for g, s, d in zip(gs, srcs, b.split(out)):
             assert_sssp_matches(g, s, to_np(d), tag=f"replay {rep}", check_invariants=False)
     b.close()
+
+
+@pytest.mark.parametrize("small", [False, True])
+def test_batch_replays_on_two_streams(dawn, small):
+    """A replay whose run holds a grid barrier waits for the one before it on
+    another stream (held up here by a spin kernel); a one-workgroup run does not."""
+    import torch
+    n, m = (900, 4000) if small else (60000, 480000)
+    g = graphgen.er(n, m, 9, weights="u32")
+    csr = dawn.Csr.from_graph(g)
+    s = int(graphgen.pick_sources(g, 1, 2)[0])
+    src = torch.tensor([s], dtype=torch.int32, device="cuda")
+    batches = [dawn.Batch([csr]) for _ in range(2)]
+    outs = [torch.empty(n, dtype=torch.uint32, device="cuda") for _ in range(2)]
+    for b, o in zip(batches, outs):
+        b.capture(src, o)
+        b.replay()
+    torch.cuda.synchronize()
+    for o in outs:
+        o.fill_(7)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    ends = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    torch.cuda.synchronize()
+    announce("batch replays on two streams", "small" if small else "large")
+    with torch.cuda.stream(streams[0]):
+        torch.cuda._sleep(200_000_000)
+        batches[0].replay(stream=streams[0])
+        ends[0].record()
+    with torch.cuda.stream(streams[1]):
+        batches[1].replay(stream=streams[1])
+        ends[1].record()
+    torch.cuda.synchronize()
+    first = ends[0].elapsed_time(ends[1])   # ms from the first replay's end to the second's
+    assert first < 0 if small else first > 0, first
+    for b, o in zip(batches, outs):
+        assert_sssp_matches(g, s, to_np(o), tag="two streams", check_invariants=False)
+        b.close()
+    dawn.check_runs()
