@@ -1098,10 +1098,11 @@ constexpr int kTinyN = 6144;
 // End of a one-workgroup run, reached by every thread: the counters are summed
 // over the workgroup (`part`: LDS scratch).  A single run stores them and its
 // state in the control words and reports as ss_report does; a run of a
-// multi-source call adds them to `info` (zeroed by an earlier launch).
+// multi-source call adds them to `info` (zeroed by an earlier launch).  tile: the
+// sources of a tile (multi-source calls).
 template <int WT, bool MULTI>
 __device__ void ss_wg_report(const SsArgs& A, dawn_run_info* info, int32_t status, uint32_t step,
-                             const Acc& acc, unsigned long long (*part)[3]) {
+                             const Acc& acc, unsigned long long (*part)[3], uint32_t tile) {
   SsCtl* C = A.ctl;
   const unsigned long long v0 = wave_sum64(acc.fe), v1 = wave_sum64(acc.es),
                            v2 = wave_sum64(acc.im);
@@ -1123,7 +1124,8 @@ __device__ void ss_wg_report(const SsArgs& A, dawn_run_info* info, int32_t statu
   }
   if constexpr (MULTI) {
     if (!info) {
-      latch_status(A.latch, status);
+      // a bad source counts as one run that failed, as its tile's would
+      if (status != -1 || blockIdx.x % tile == 0) latch_status(A.latch, status);
       return;
     }
     atomicMax(&info->steps, (int32_t)step);
@@ -1167,6 +1169,18 @@ __device__ void ss_wg_report(const SsArgs& A, dawn_run_info* info, int32_t statu
     info->union_rows = (int64_t)fe;
     info->union_edges = (int64_t)es;
   }
+}
+
+// Whether the tile that source blockIdx.x would be in (of `tile` sources) holds a
+// source outside [0, n): such a tile's run ends before its first step.  Every
+// thread calls it and gets the result.
+__device__ __forceinline__ bool ss_multi_bad(const int32_t* sources, int32_t k, int32_t tile,
+                                             int32_t n) {
+  const int32_t j0 = (int32_t)blockIdx.x / tile * tile;
+  bool bad = false;
+  for (int32_t j = j0 + (int32_t)threadIdx.x; j < min(k - j0, tile) + j0; j += blockDim.x)
+    bad |= sources[j] < 0 || sources[j] >= n;
+  return __syncthreads_or(bad) != 0;
 }
 
 // A distance key as the caller sees it (int32: the sign bit flipped back).
@@ -1226,13 +1240,14 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
   if constexpr (MULTI) {
     out += (size_t)blockIdx.x * n;
     src = sources[blockIdx.x];
-    if (src < 0 || src >= n) status = -1;
+    if (ss_multi_bad(sources, count, single, n)) status = -1;
   } else {
     if (check_valid && ld_agent(&C->done)) status = -1;
   }
   if (status == -1) {
-    // nothing is run: every distance INF
-    for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = key_value<WT>(inf_key<WT>());
+    // nothing is run: every distance INF (but a source's own, as a tile leaves it)
+    for (int i = threadIdx.x; i < n; i += blockDim.x)
+      out[i] = key_value<WT>(MULTI && WT != kWUNIT && i == src ? zero_key<WT>() : inf_key<WT>());
   } else {
     for (int i = threadIdx.x; i < n; i += blockDim.x) sh.dist[i] = inf_key<WT>();
     for (int i = threadIdx.x; i < nwords; i += blockDim.x) {
@@ -1389,7 +1404,7 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
         acc.im += (unsigned long long)__popc(sh.bm[step & 1][i]);
     for (int i = threadIdx.x; i < n; i += blockDim.x) out[i] = key_value<WT>(sh.dist[i]);
   }
-  ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part);  // (after the last step's barrier)
+  ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part, (uint32_t)single);  // (after the last step's barrier)
 }
 
 // ---------------------------------------------------------------------------
@@ -1438,13 +1453,14 @@ __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int
   if constexpr (MULTI) {
     out += (size_t)blockIdx.x * n;
     src = sources[blockIdx.x];
-    if (src < 0 || src >= n) status = -1;
+    if (ss_multi_bad(sources, count, single, n)) status = -1;
   } else {
     if (check_valid && ld_agent(&C->done)) status = -1;
   }
   if (status == -1) {
-    // nothing is run: every distance INF
-    for (int i = t; i < n; i += kLdsThreads) out[i] = key_value<WT>(inf_key<WT>());
+    // nothing is run: every distance INF (but a source's own, as a tile leaves it)
+    for (int i = t; i < n; i += kLdsThreads)
+      out[i] = key_value<WT>(MULTI && WT != kWUNIT && i == src ? zero_key<WT>() : inf_key<WT>());
   } else {
     if (!MULTI && t == 0) {
       // the status words the report reads: the workspace may hold an earlier
@@ -1595,7 +1611,7 @@ __global__ void __launch_bounds__(kLdsThreads) ss_lds_kernel(SsArgs A, const int
         acc.im += (unsigned long long)__popc(sh.bm[step % 3][i]);
     for (int i = t; i < n; i += kLdsThreads) out[i] = key_value<WT>(sh.dist[i]);
   }
-  ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part);
+  ss_wg_report<WT, MULTI>(A, info, status, step, acc, sh.part, (uint32_t)single);
 }
 
 // ---------------------------------------------------------------------------
@@ -1674,8 +1690,8 @@ dawn_status ss_multi_run(const int32_t* rowptr, const int32_t* colidx, const voi
                                          : ss_wg_kernel<kWU32, true>(n, m);
   if (info) hipLaunchKernelGGL(ss_multi_info_kernel, dim3(1), dim3(64), 0, stream, info);
   void* tk = ktimer_begin(stream);
-  hipLaunchKernelGGL(kern, dim3((unsigned)k), dim3(1024), 0, stream, A, sources, nullptr, k, 0, 0,
-                     info);
+  hipLaunchKernelGGL(kern, dim3((unsigned)k), dim3(1024), 0, stream, A, sources, nullptr, k,
+                     std::min(k, tuning().tile_k), 0, info);
   ktimer_end(tk, stream, 1);
   return hip_check(hipGetLastError(), "one workgroup per source");
 }
@@ -1834,19 +1850,24 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
 // single-source run, and there is no tile to fill, scan or transpose.
 // ---------------------------------------------------------------------------
 // A source outside [0, n) ends the run before its first step (converged = -1),
-// as in a tile.
+// as in a tile, whose distances then hold the sources' zeros, of hop counts nothing.
 template <int WT>
 __global__ void ss_copy_seed_kernel(SsArgs A, const int32_t* sources, int32_t count) {
   SsCtl* C = A.ctl;
+  bool bad = false;
+  for (int j = threadIdx.x; j < count; j += blockDim.x) bad |= sources[j] < 0 || sources[j] >= A.n1;
+  bad = __syncthreads_or(bad) != 0;
+  if (bad && threadIdx.x == 0) {
+    st_agent_i(&C->converged, -1);
+    st_agent(&C->done, 1u);
+  }
+  if (bad && WT == kWUNIT) return;
   for (int j = threadIdx.x; j < count; j += blockDim.x) {
     const int32_t s = sources[j];
-    if (s < 0 || s >= A.n1) {
-      st_agent_i(&C->converged, -1);
-      st_agent(&C->done, 1u);
-      continue;
-    }
+    if (s < 0 || s >= A.n1) continue;
     const int32_t x = j * A.n1 + s;
     A.dist[x] = zero_key<WT>();
+    if (bad) continue;
     atomicOr(&A.bm[0][x >> 5], 1u << (x & 31));
     const int32_t start = A.rowptr[s], deg = A.rowptr[s + 1] - start;
     if (deg <= A.t_lane) continue;
