@@ -1689,10 +1689,19 @@ dawn_status ss_multi_run(const int32_t* rowptr, const int32_t* colidx, const voi
                           : wt == kWUNIT ? ss_wg_kernel<kWUNIT, true>(n, m)
                                          : ss_wg_kernel<kWU32, true>(n, m);
   if (info) hipLaunchKernelGGL(ss_multi_info_kernel, dim3(1), dim3(64), 0, stream, info);
+  // A launch holds fewer than 2^32 threads: whole tiles of sources, 2^21 workgroups
+  // at most.
+  const int32_t tile = std::min(k, tuning().tile_k), most = (1 << 21) / tile * tile;
   void* tk = ktimer_begin(stream);
-  hipLaunchKernelGGL(kern, dim3((unsigned)k), dim3(1024), 0, stream, A, sources, nullptr, k,
-                     std::min(k, tuning().tile_k), 0, info);
-  ktimer_end(tk, stream, 1);
+  int32_t launches = 0;
+  for (int32_t j0 = 0; j0 < k; j0 += std::min(most, k - j0)) {
+    const int32_t cnt = std::min(most, k - j0);
+    hipLaunchKernelGGL(kern, dim3((unsigned)cnt), dim3(1024), 0, stream, A, sources + j0, nullptr,
+                       cnt, tile, 0, info);
+    A.dist += (size_t)cnt * (size_t)n;
+    launches++;
+  }
+  ktimer_end(tk, stream, launches);
   return hip_check(hipGetLastError(), "one workgroup per source");
 }
 
