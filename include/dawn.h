@@ -156,8 +156,9 @@ typedef struct {
  *   1 `step_launches` (tiles: `tile_step_launches`) launches of one step
  *     each, then one persistent launch for the steps that remain;
  *   2 one persistent launch for all steps, with a grid barrier between steps.
- * A persistent launch's grid is what the compute units hold at once, by the
- * kernel's compiled VGPR and LDS use (dawn_device_query); a grid barrier that
+ * A persistent launch's grid is at most what the compute units hold at once, by
+ * the kernel's compiled VGPR and LDS use (dawn_device_query): tiles take that many
+ * workgroups, single-source runs fewer on sparse or small graphs.  A grid barrier that
  * waits longer than barrier_ms ends the run with converged = -2, never a hang.
  * Two persistent launches that each hold part of the device would wait for each
  * other, so those of one device are ordered, whatever their streams, and so are
@@ -170,8 +171,9 @@ typedef struct {
  * persistent launches).  One-workgroup single-source runs
  * of graphs held whole in LDS (n <= 6144 and m <= 16384) always take 1024
  * threads: each thread keeps its share of the edges in registers.
- * grid: workgroups per launch, 0 = auto (persistent: what the device holds at
- * once; tile step launches: 4 per compute unit for the push relaxation (the
+ * grid: workgroups per launch, 0 = auto (persistent: see above, a larger figure is
+ * cut to what the device holds at once; tile step launches: 4 per compute unit for
+ * the push relaxation (the
  * pull relaxation always takes 16); single-source step launches:
  * 4 per compute unit).
  * tile_k: sources per tile for dawn_msssp / dawn_apsp, a multiple of 64,
@@ -237,7 +239,7 @@ typedef struct {
                            gives up and ends the run with converged = -2; 0..600000,
                            default 4000 (0: give up at the first wait, for tests) */
   int32_t ss_tail_grid; /* single-source and batch runs: at most this many workgroups in the
-                           persistent launch (0 = what the device holds at once).  A persistent
+                           persistent launch (0 = no such limit).  A persistent
                            launch waits at grid barriers for all of its workgroups; when kernels
                            of other streams may hold compute units meanwhile, 1 keeps it from
                            waiting on workgroups that cannot start (a server's lone queries run

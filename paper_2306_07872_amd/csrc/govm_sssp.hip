@@ -1740,6 +1740,34 @@ static void ss_persistent_tiers(SsArgs& A) {
   A.t_chunk = std::max(256, T.t_chunk / 4);
 }
 
+// The grid of a persistent launch: tuning field `grid` where it is set, else the
+// rule's, and what the device holds at once.
+template <int WT, bool COPIES>
+static int ss_persistent_grid(int64_t n, int64_t m, int threads) {
+  const int most = std::min(residency_of(ss_persistent_kernel<WT, COPIES>, threads).grid, kMaxGrid);
+  return tuning().grid > 0 ? std::min(tuning().grid, most) : ss_persistent_wgs(n, m, most);
+}
+
+template <int WT, bool COPIES>
+static dawn_status ss_launch_persistent(const SsArgs& a, int grid, int threads, dawn_run_info* info,
+                                        hipStream_t stream, bool capture) {
+  SsArgs args = a;
+  void* ptrs[] = {&args, &info};
+  hipError_t e;
+  const PersistentGate gate(stream, grid);
+  void* tk = capture ? nullptr : ktimer_begin(stream);
+  if (!capture && dev_info().coop && tuning().coop) {
+    e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&ss_persistent_kernel<WT, COPIES>),
+                                   dim3(grid), dim3(threads), ptrs, 0, stream);
+  } else {
+    hipLaunchKernelGGL((ss_persistent_kernel<WT, COPIES>), dim3(grid), dim3(threads), 0, stream, args,
+                       info);
+    e = hipGetLastError();
+  }
+  ktimer_end(tk, stream, 1);
+  return hip_check(e, "persistent launch");
+}
+
 template <int WT>
 static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_t* colidx,
                             const SsSeeds& seeds, const SsLayout& L, dawn_run_info* info,
@@ -1816,31 +1844,16 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     ktimer_end(tk, stream, chunk);
     if ((st = hip_check(hipGetLastError(), "step launches")) != DAWN_OK) return st;
   }
-  {
-    const Residency r = residency_of(ss_persistent_kernel<WT, false>, threads);
-    int grid = std::min(std::min(r.grid, kMaxGrid), ss_persistent_wgs(A.n, A.m, r.grid));
-    if (T.grid > 0 && T.grid < grid) grid = T.grid;
-    if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
-    if (lone) grid = 1;
-    if (wgs) *wgs = grid;
-    SsArgs a = A;
-    a.counted = mode == 1 && A.pull_min >= 0;
-    ss_persistent_tiers(a);
-    a.pull_min = -1;  // pull steps need step launches (the last workgroup clears the bitmap)
-    void* args[] = {&a, &info};
-    hipError_t e;
-    const PersistentGate gate(stream, grid);
-    void* tk = capture ? nullptr : ktimer_begin(stream);
-    if (!capture && di.coop && T.coop) {
-      e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&ss_persistent_kernel<WT, false>),
-                                     dim3(grid), dim3(threads), args, 0, stream);
-    } else {
-      hipLaunchKernelGGL((ss_persistent_kernel<WT, false>), dim3(grid), dim3(threads), 0, stream, a, info);
-      e = hipGetLastError();
-    }
-    ktimer_end(tk, stream, 1);
-    if ((st = hip_check(e, "persistent launch")) != DAWN_OK) return st;
-  }
+  SsArgs a = A;
+  a.counted = mode == 1 && A.pull_min >= 0;
+  ss_persistent_tiers(a);
+  a.pull_min = -1;  // pull steps need step launches (the last workgroup clears the bitmap)
+  int grid = ss_persistent_grid<WT, false>(A.n, A.m, threads);
+  if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
+  if (lone) grid = 1;
+  if (wgs) *wgs = grid;
+  if ((st = ss_launch_persistent<WT, false>(a, grid, threads, info, stream, capture)) != DAWN_OK)
+    return st;
   if constexpr (WT == kWI32) {
     hipLaunchKernelGGL(ss_decode_i32_kernel, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                        (int64_t)A.n);
@@ -1948,15 +1961,8 @@ static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, A.rowptr, A.hv, A.t_lane, A.w,
                      (int64_t)A.m, A.n1, (int64_t)-1, A);
   hipLaunchKernelGGL(ss_copy_seed_kernel<WT>, dim3(1), dim3(64), 0, stream, A, sources, k);
-  const Residency r = residency_of(ss_persistent_kernel<WT, true>, threads);
-  int grid = std::min(std::min(r.grid, kMaxGrid),
-                      ss_persistent_wgs(A.n, (int64_t)k * A.m, r.grid));
-  if (T.grid > 0 && T.grid < grid) grid = T.grid;
-  const PersistentGate gate(stream, grid);
-  void* tk = ktimer_begin(stream);
-  hipLaunchKernelGGL((ss_persistent_kernel<WT, true>), dim3(grid), dim3(threads), 0, stream, A, info);
-  ktimer_end(tk, stream, 1);
-  return hip_check(hipGetLastError(), "copies launch");
+  return ss_launch_persistent<WT, true>(A, ss_persistent_grid<WT, true>(A.n, (int64_t)k * A.m, threads),
+                                        threads, info, stream, false);
 }
 
 dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
