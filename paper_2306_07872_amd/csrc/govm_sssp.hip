@@ -116,20 +116,38 @@ __device__ __forceinline__ void nf_advance(NfState& s, uint32_t M, float work, f
 
 // The run's smallest delta, or 0 for no deferral: from samples of the weights
 // (their mean) and of the row lengths (deferral only where the mean length of an
-// edge's row is at most four times the mean length of a row).  Every thread of
-// the workgroup calls it and gets the result.
+// edge's row is at most four times the mean length of a row).  batch: and only
+// where the weights are of one scale throughout, by the mean of their logarithms
+// over runs of 64 samples (within a factor of 8): with one threshold for all, the
+// graphs of larger weights would wait for the others to end, and the steps add up.
+// 16 ER graphs of 240,000 edges, one with weights 100 times the others': 35 steps,
+// 1077 us with deferral, 19 and 870 without.  Every thread of the workgroup (whole
+// wavefronts) calls it and gets the result.
 template <int WT>
 __device__ float nf_floor(int64_t n, int64_t m, const int32_t* rowptr, const uint32_t* w,
-                          int samples) {
+                          int samples, bool batch) {
   if (!nf_weights<WT>() || !rowptr || !w || m < 1) return 0.f;
-  __shared__ float part[3][kMaxWavesPerBlock];
+  __shared__ float part[5][kMaxWavesPerBlock];
   __shared__ float s_floor;
-  float sw = 0.f, sd = 0.f, sd2 = 0.f;
+  float sw = 0.f, sd = 0.f, sd2 = 0.f, lo = 1e9f, hi = -1e9f;
   const int64_t ew = m > samples ? m / samples : 1, rw = n > samples ? n / samples : 1;
   const int ne = (int)(m < samples ? m : samples), nr = (int)(n < samples ? n : samples);
 #pragma unroll 4
   for (int i = threadIdx.x; i < ne; i += blockDim.x)
     sw += WT == kWF32 ? __uint_as_float(w[i * ew]) : (float)w[i * ew];
+  if (batch) {
+    const int ne64 = ne & ~63;
+    for (int i = threadIdx.x; i < ne64; i += blockDim.x) {
+      const uint32_t x = w[i * ew];
+      float lg = x == 0u ? 0.f : WT == kWF32 ? (float)(x >> 23) : (float)(31 - __clz((int)x));
+      const int cnt = __popcll(__ballot(x != 0u));
+      for (int off = kWave / 2; off > 0; off >>= 1) lg += __shfl_xor(lg, off, kWave);
+      if (cnt >= 16) {
+        lo = fminf(lo, lg / (float)cnt);
+        hi = fmaxf(hi, lg / (float)cnt);
+      }
+    }
+  }
 #pragma unroll 4
   for (int i = threadIdx.x; i < nr; i += blockDim.x) {
     const float d = (float)(rowptr[i * rw + 1] - rowptr[i * rw]);
@@ -146,6 +164,8 @@ __device__ float nf_floor(int64_t n, int64_t m, const int32_t* rowptr, const uin
     part[0][wv] = sw;
     part[1][wv] = sd;
     part[2][wv] = sd2;
+    part[3][wv] = lo;
+    part[4][wv] = hi;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -154,9 +174,11 @@ __device__ float nf_floor(int64_t n, int64_t m, const int32_t* rowptr, const uin
       sw += part[0][i];
       sd += part[1][i];
       sd2 += part[2][i];
+      lo = fminf(lo, part[3][i]);
+      hi = fmaxf(hi, part[4][i]);
     }
     // sd2 / sd <= 4 * sd / nr
-    s_floor = sd2 * nr <= 4.f * sd * sd ? fmaxf(kNfDelta * (sw / ne), 1e-30f) : 0.f;
+    s_floor = sd2 * nr <= 4.f * sd * sd && hi - lo <= 3.f ? fmaxf(kNfDelta * (sw / ne), 1e-30f) : 0.f;
   }
   __syncthreads();
   return s_floor;
@@ -200,11 +222,12 @@ __device__ __forceinline__ void ss_queue_seed(const SsArgs& A, int64_t s) {
 // seed (or -1): the run's only source, placed here, which saves the launch that
 // places several (with the run's report in its last launch: ER n = 40,000 272 ->
 // 254 us, R-MAT scale 16 376 -> 366, scale 20 802 -> 789).
+// batch: the run is a batch's.
 template <int WT>
 __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_t* bm1,
                                int64_t nwords, SsCtl* ctl, const int32_t* rowptr, uint32_t* hv,
                                int32_t t_lane, const uint32_t* w, int64_t m, int32_t n1,
-                               int64_t seed, SsArgs A) {
+                               int64_t seed, bool batch, SsArgs A) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = tid; i < n; i += stride) dist[i] = i == seed ? zero_key<WT>() : inf_key<WT>();
@@ -234,7 +257,7 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
     for (int i = threadIdx.x; i < (int)(offsetof(SsCtl, bar.slot) / 4); i += blockDim.x) c[i] = 0;
     __syncthreads();
     if (threadIdx.x < kRot) ctl->minp[threadIdx.x].v = kNoKey;
-    const float floor = nf_floor<WT>(n1, m, rowptr, w, kNfSamples);
+    const float floor = nf_floor<WT>(n1, m, rowptr, w, kNfSamples, batch);
     if (threadIdx.x == 0) {
       ctl->nf = NfState{kNoKey, floor, floor, 0u};
       if (seed >= 0) ss_queue_seed<true>(A, seed);
@@ -992,7 +1015,7 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_
     if (step >= (uint32_t)A.n) { status = 0; break; }
     counts = next.queued ? ss_counts(A, step) : SsCounts{0u, 0u};
   }
-  if (status == 0) {  // no scan follows that would count what the last step lowered
+  if (WT == kWI32 && status == 0) {  // no scan follows that would count what the last step lowered
     const int64_t nwords = ((int64_t)A.n + 31) / 32;
     for (int64_t i = (int64_t)gb * blockDim.x + threadIdx.x; i < nwords; i += (int64_t)nb * blockDim.x)
       acc.im += (unsigned long long)__popc(ld_agent(&A.bm[step & 1][i]));
@@ -1052,7 +1075,7 @@ __global__ void __launch_bounds__(1024) ss_step_kernel(SsArgs A) {
         A.bm[step & 1][i] = 0u;
     const uint32_t upd = ld_agent(&C->upd[(step + 1) % kRot]);
     const uint32_t ns = step + 1;
-    if (!PULL && upd && ns >= (uint32_t)A.n) {  // as in the persistent launch
+    if (WT == kWI32 && !PULL && upd && ns >= (uint32_t)A.n) {  // as in the persistent launch
       unsigned long long im = 0;
       for (int64_t i = threadIdx.x; i < ((int64_t)A.n + 31) / 32; i += blockDim.x)
         im += (unsigned long long)__popc(ld_agent(&A.bm[ns & 1][i]));
@@ -1270,7 +1293,7 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
     }
     // far rows wait, as in the multi-workgroup runs
     const float floor =
-        A.m >= kNfMinCu ? nf_floor<WT>(n, A.m, A.rowptr, A.w, 1024) : 0.f;
+        A.m >= kNfMinCu ? nf_floor<WT>(n, A.m, A.rowptr, A.w, 1024, !MULTI && voff) : 0.f;
     NfState nf{kNoKey, floor, floor, 0u};
     // (the words of the rows left for later stay in a register of the lane that scans
     // them, one word a lane, as all do at 1024 threads)
@@ -1802,7 +1825,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     if (T.validate) {
       hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                          (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, nullptr, nullptr, 0, nullptr, 0,
-                         A.n1, (int64_t)-1, A);
+                         A.n1, (int64_t)-1, false, A);
       const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
       hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
                          A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
@@ -1819,7 +1842,8 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   const bool placed = !seeds.sources_dev && !T.validate;
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, rowptr, A.hv, A.t_lane, A.w,
-                     (int64_t)A.m, A.n1, placed ? (int64_t)seeds.source : (int64_t)-1, A);
+                     (int64_t)A.m, A.n1, placed ? (int64_t)seeds.source : (int64_t)-1,
+                     seeds.voff_dev != nullptr, A);
   if (T.validate) {
     const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
     hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
@@ -1959,7 +1983,7 @@ static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int
   const int fill_blocks = (int)std::min<int64_t>(4096, ((int64_t)A.n + 255) / 256 + 1);
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, A.rowptr, A.hv, A.t_lane, A.w,
-                     (int64_t)A.m, A.n1, (int64_t)-1, A);
+                     (int64_t)A.m, A.n1, (int64_t)-1, false, A);
   hipLaunchKernelGGL(ss_copy_seed_kernel<WT>, dim3(1), dim3(64), 0, stream, A, sources, k);
   return ss_launch_persistent<WT, true>(A, ss_persistent_grid<WT, true>(A.n, (int64_t)k * A.m, threads),
                                         threads, info, stream, false);
