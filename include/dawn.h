@@ -152,7 +152,7 @@ typedef struct {
  *     (dawn_msssp, dawn_apsp, dawn_umsssp_ws) as mode 1, unless the
  *     call runs in one workgroup per source (see small_m) or, with few
  *     sources and not under graph capture, as one single-source run on
- *     copies of the graph;
+ *     copies of the graph, from the start or once the tile's steps are small;
  *   1 `step_launches` (tiles: `tile_step_launches`) launches of one step
  *     each, then one persistent launch for the steps that remain;
  *   2 one persistent launch for all steps, with a grid barrier between steps.
@@ -234,7 +234,10 @@ typedef struct {
   int32_t tile_step_launches; /* tiles, mode 0 or 1: step launches (each one step, with pull
                            steps on dense frontiers) before the persistent launch that
                            finishes the run, 0..4096, default 16 (R-MAT scale 20 with 256
-                           sources takes 15 steps) */
+                           sources takes 15 steps).  In mode 0 at most 8 where a run of few
+                           sources may go on on copies of the graph (without a reverse
+                           graph), and at most 10 for hop counts with 12 edges per vertex
+                           or more */
   int32_t barrier_ms;   /* persistent launches: a grid barrier that waits longer than this
                            gives up and ends the run with converged = -2; 0..600000,
                            default 4000 (0: give up at the first wait, for tests) */

@@ -544,7 +544,8 @@ __global__ void dawn_info_add_kernel(dawn_run_info* acc, const dawn_run_info* pa
 }
 
 // A multi-source run: one workgroup per source on small graphs, copies of the
-// graph for a few sources, else tile by tile.  Each tile: reset, seeding,
+// graph for a few sources, else tile by tile (with few sources the steps that the
+// step launches leave run on copies).  Each tile: reset, seeding,
 // `tile_step_launches` step launches (a step launch returns at once once the
 // tile's run has ended), then one persistent launch for whatever steps remain
 // (tuning mode 2: the persistent launch alone), the transposed store and the
@@ -581,6 +582,15 @@ static dawn_status msssp_impl(const int32_t* rowptr, const int32_t* colidx, cons
   // hop counts on graphs of many edges per vertex: the dense steps are over by
   // then, and a spare step costs two launches (9 us)
   if (unweighted && g_tuning.mode == 0 && m >= 12 * (int64_t)n) launches = std::min(launches, 10);
+  // few sources (one tile): once the steps are small after the step launches, the run
+  // goes on on copies, laid out over the distances, which have been stored by then
+  const size_t over = unweighted ? L.planes : L.D;
+  const size_t room = unweighted ? L.total - L.planes : (size_t)n * L.K * 4;
+  const bool hand = ss_handover_fits(n, m, k, unweighted, room) && !stream_capturing(stream);
+  const uint32_t few = hand ? ss_handover_rows(n) : 0u;
+  // (eight step launches then: what is left of the dense steps is as fast in the
+  // persistent launch, unless they pull)
+  if (hand && !A.T.hdr) launches = std::min(launches, 8);
   for (int32_t j0 = 0; j0 < k; j0 += kt) {
     const int32_t cnt = std::min(kt, k - j0);
     if ((st = tile_reset(A, f32, stream)) != DAWN_OK) return st;
@@ -590,12 +600,19 @@ static dawn_status msssp_impl(const int32_t* rowptr, const int32_t* colidx, cons
       st = unweighted ? utile_steps(A, launches, stream) : tile_steps(A, f32, false, launches, stream);
       if (st != DAWN_OK) return st;
     }
-    st = unweighted ? utile_persistent(A, stream) : tile_steps(A, f32, true, INT32_MAX, stream);
+    st = unweighted ? utile_persistent(A, few, stream)
+                    : tile_steps(A, f32, true, INT32_MAX, stream, few);
     if (st != DAWN_OK) return st;
     char* out = static_cast<char*>(dist_out) + (size_t)j0 * (size_t)n * 4;
     st = unweighted ? utile_store(A, 0, cnt, reinterpret_cast<uint32_t*>(out), n, stream)
                     : tile_store(A, 0, cnt, out, n, stream);
     if (st != DAWN_OK) return st;
+    if (hand) {
+      if ((st = ss_handover(A, unweighted ? kWUNIT : f32 ? kWF32 : kWU32, k, out,
+                            static_cast<char*>(ws) + over, info, stream)) != DAWN_OK)
+        return st;
+      return tile_info(A, info, stream);
+    }
     // with run info: this tile's summary, summed into the caller's; without:
     // the tile's status into the run-status latch
     if ((st = tile_info(A, info ? part : nullptr, stream)) != DAWN_OK) return st;

@@ -170,6 +170,16 @@ dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const vo
                           int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
                           void* ws, dawn_run_info* info, hipStream_t stream);
 
+// A tile's run of few sources goes on as a run on copies: once the tile's steps are
+// small (ss_handover_rows) and it has been stored, the remaining steps of a tile that
+// is not done, in ws_bytes at ws (the tile's distances are not needed any more; its
+// control block and masks are).  Reports the run if it takes it.
+struct TileArgs;
+bool ss_handover_fits(int64_t n, int64_t m, int32_t k, bool unit, size_t ws_bytes);
+uint32_t ss_handover_rows(int64_t n);
+dawn_status ss_handover(const TileArgs& tile, int wt, int32_t k, void* dist, void* ws,
+                        dawn_run_info* info, hipStream_t stream);
+
 // ----- distance tile ---------------------------------------------------------
 struct TileLayout {
   size_t ctl, info, D, mk[3], qgrp[3], qwave[3], qwg[3], fbm[2], vis, planes, total;
@@ -193,9 +203,10 @@ dawn_status tile_seed_all(const TileArgs& a, const int32_t* sources_dev, int32_t
 dawn_status tile_admit(const TileArgs& a, bool f32, int32_t col, int32_t source, bool clean,
                        hipStream_t stream);
 dawn_status tile_evict(const TileArgs& a, bool f32, int32_t col, hipStream_t stream);
-// Run steps: persistent (all until done) or `max_steps` step launches.
+// Run steps: persistent (all until done, or with few > 0 until a step of at most so
+// many frontier records) or `max_steps` step launches.
 dawn_status tile_steps(const TileArgs& a, bool f32, bool persistent, int32_t max_steps,
-                       hipStream_t stream);
+                       hipStream_t stream, uint32_t few = 0);
 dawn_status tile_done_bits(const TileArgs& a, int32_t k, uint32_t* done_bits, hipStream_t stream);
 dawn_status tile_store(const TileArgs& a, int32_t col0, int32_t count, void* out, int64_t ld,
                        hipStream_t stream);
@@ -216,8 +227,9 @@ Residency ss_persistent_residency(int threads);
 Residency tile_persistent_residency(int threads);
 Residency utile_persistent_residency(int threads);
 // Hop-count tiles: the rest of the run (until no column is active, at most n
-// steps) in one persistent launch (returns at once when the run has ended).
-dawn_status utile_persistent(const TileArgs& a, hipStream_t stream);
+// steps) in one persistent launch (returns at once when the run has ended; few as
+// in tile_steps).
+dawn_status utile_persistent(const TileArgs& a, uint32_t few, hipStream_t stream);
 
 // ----- measurement -------------------------------------------------------------
 // Bracket a main launch with events when the kernel timer is on.

@@ -73,6 +73,9 @@ namespace dawn {
 // 2048 x 2048 grid 73.8 -> 38 ms (1187M -> 66M edges expanded), 64 ER graphs in
 // one launch 11.8 -> 6.0 ms, together with the scan's order and kFresh below.
 // ---------------------------------------------------------------------------
+// SsCtl::converged of a run on copies that is not needed: the tile's is done.
+constexpr int32_t kNoRun = 2;
+
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;  // above every distance that a row can have
 constexpr float kNfDelta = 1.2f;
 constexpr float kNfWork = 30000.f;
@@ -222,15 +225,24 @@ __device__ __forceinline__ void ss_queue_seed(const SsArgs& A, int64_t s) {
 // seed (or -1): the run's only source, placed here, which saves the launch that
 // places several (with the run's report in its last launch: ER n = 40,000 272 ->
 // 254 us, R-MAT scale 16 376 -> 366, scale 20 802 -> 789).
-// batch: the run is a batch's.
+// batch: the run is a batch's.  dist: null when the distances are there already.
+// over (or null): a word that says whether nothing is left to run.
 template <int WT>
 __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_t* bm1,
                                int64_t nwords, SsCtl* ctl, const int32_t* rowptr, uint32_t* hv,
                                int32_t t_lane, const uint32_t* w, int64_t m, int32_t n1,
-                               int64_t seed, bool batch, SsArgs A) {
+                               int64_t seed, bool batch, const uint32_t* over, SsArgs A) {
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (over && *over) {  // (written by an earlier launch)
+    if (tid == 0) {
+      ctl->converged = kNoRun;
+      ctl->done = 1u;
+    }
+    return;
+  }
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = tid; i < n; i += stride) dist[i] = i == seed ? zero_key<WT>() : inf_key<WT>();
+  if (dist)
+    for (int64_t i = tid; i < n; i += stride) dist[i] = i == seed ? zero_key<WT>() : inf_key<WT>();
   for (int64_t i = tid; i < nwords; i += stride) {
     bm0[i] = seed >= 0 && i == seed >> 5 ? 1u << (seed & 31) : 0u;
     bm1[i] = 0;
@@ -331,8 +343,8 @@ __device__ void ss_report(SsCtl* C, dawn_run_info* info, uint32_t* latch) {
   info->frontier_entries = (int64_t)fe;
   info->edges_scanned = (int64_t)es;
   info->improvements = (int64_t)im;
-  info->union_rows = (int64_t)fe;
-  info->union_edges = (int64_t)es;
+  info->union_rows = (int64_t)(fe + C->u_rows);  // (written by an earlier launch)
+  info->union_edges = (int64_t)(es + C->u_edges);
 }
 
 // ---------------------------------------------------------------------------
@@ -691,11 +703,13 @@ struct ScanSplit {
   __device__ __forceinline__ int64_t block() const { return span << (6 - gs); }
 };
 
-// left0: the rows left for later of this lane's word in the wavefront's first block
-// (those of the other blocks are in df).
+// left0: the rows left for later of this lane's word in the wavefront's first block;
+// those of the other blocks are in df, with COPIES of the first nheld of them in
+// `held` (LDS).
 template <int WT, bool PULL, int MODE, bool COPIES>
 __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t gb, uint32_t nb, Acc& acc,
-                        SsShared& sh, SsCounts counts, uint32_t thr, bool count, uint32_t& left0) {
+                        SsShared& sh, SsCounts counts, uint32_t thr, bool count, uint32_t& left0,
+                        uint32_t* held = nullptr, int nheld = 0) {
   constexpr bool NF = MODE != kAll;
   StepSeen seen;
   const int cur = step & 1, nxt = cur ^ 1;
@@ -789,13 +803,17 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
     // heavy rows' bits included: nothing else reads this bitmap during a push
     // step.
     const ScanSplit split(A.n, gw, nwv);
-    for (int64_t w0 = 0; w0 + split.first < split.nwords; w0 += split.block()) {
+    int block = 0;  // of this wavefront's
+    for (int64_t w0 = 0; w0 + split.first < split.nwords; w0 += split.block(), block++) {
       const int64_t wi = split.word(w0, lane);
       uint32_t* def = sh.def[wave];
       uint32_t bits = 0u, left = 0u;
       if (wi < split.nwords) {
         const uint32_t word = ld_agent(&A.bm[cur][wi]), hv = A.hv[wi];
-        if (NF) left = w0 == 0 ? left0 : ld_agent(&A.df[wi]);
+        if (NF)
+          left = w0 == 0 ? left0
+                 : COPIES && block <= nheld ? held[((block - 1) * W + wave) * kWave + lane]
+                                            : ld_agent(&A.df[wi]);
         if (word) {
           st_agent(&A.bm[cur][wi], 0u);
           if (count) acc.im += (unsigned long long)__popc(word);
@@ -841,6 +859,7 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
         wave_lds_sync();
         const uint32_t x = def[lane];
         if (w0 == 0) left0 = x;
+        else if (COPIES && block <= nheld) held[((block - 1) * W + wave) * kWave + lane] = x;
         else if (x != left) st_agent(&A.df[wi], x);
         if (x) sh.upd = 1u;
       }
@@ -966,13 +985,16 @@ __device__ __forceinline__ bool ss_grid_sync(SsCtl* C, uint32_t nblocks, uint32_
 // kernel's compiled resources (residency_of); should a barrier wait still give
 // up, the run ends with status -2, reported to the caller.
 template <int WT, bool COPIES>
-__global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_info* info) {
+__global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_info* info,
+                                                             int32_t nheld) {
   __shared__ SsShared sh;
+  extern __shared__ uint32_t held[];  // copies: rows left for later, see ss_step
   SsCtl* C = A.ctl;
   // Ended by an earlier launch, or given up by workgroup 0, which may happen while
   // this workgroup starts: one read for all of its threads, which would else part
   // here and miss each other at the barriers of the steps.
   if (ld_agent_block(&C->done)) {
+    if (COPIES && ld_agent_i(&C->converged) == kNoRun) return;  // (an earlier launch's word)
     if (last_block_arrive(&C->arrive, gridDim.x) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
     return;
   }
@@ -995,15 +1017,18 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_
     const int64_t wi = split.word(0, lane_id());
     if (wi < split.nwords) left0 = A.df[wi];  // (written by an earlier launch)
   }
+  if (COPIES)  // (no step launches came before: nothing is left yet)
+    for (int i = lane_id(); i < nheld * kWave; i += kWave)
+      held[((i / kWave) * W + wave) * kWave + i % kWave] = 0u;
   for (;;) {
     if (blockIdx.x == 0 && threadIdx.x == 0) ss_zero_rotation(C, step);
     if (nf_weights<WT>() && nf.floor != 0.f) {
       if (next.fresh)
-        ss_step<WT, false, kFresh, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count, left0);
+        ss_step<WT, false, kFresh, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count, left0, held, nheld);
       else
-        ss_step<WT, false, kNear, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count, left0);
+        ss_step<WT, false, kNear, COPIES>(A, step, gb, nb, acc, sh, counts, next.thr, count, left0, held, nheld);
     } else {
-      ss_step<WT, false, kAll, COPIES>(A, step, gb, nb, acc, sh, counts, kNoKey, count, left0);
+      ss_step<WT, false, kAll, COPIES>(A, step, gb, nb, acc, sh, counts, kNoKey, count, left0, held, nheld);
     }
     count = true;
     if (!ss_grid_sync<WT>(C, gridDim.x, bar_base, epoch, A.bar_ticks, sh, nf, A.nf_work, next)) {
@@ -1775,16 +1800,29 @@ template <int WT, bool COPIES>
 static dawn_status ss_launch_persistent(const SsArgs& a, int grid, int threads, dawn_run_info* info,
                                         hipStream_t stream, bool capture) {
   SsArgs args = a;
-  void* ptrs[] = {&args, &info};
+  // Copies: LDS for the rows left for later in the blocks after each wavefront's
+  // first (1000 x 1021 grid, 32 sources: 64 ms; 69 with them in memory), as far as
+  // the resident workgroups' LDS (with 2 KiB of each for its allocation's rounding)
+  // and 64 KiB a workgroup go.
+  int32_t nheld = 0;
+  if (COPIES) {
+    const Residency r = residency_of(ss_persistent_kernel<WT, COPIES>, threads);
+    const int64_t W = threads / kWave, block = (int64_t)grid * W * kWave * 32;
+    const int64_t room = std::min<int64_t>(65536, 163840 / std::max(r.per_cu, 1) - 2048) - r.lds;
+    nheld = (int32_t)std::max<int64_t>(
+        0, std::min<int64_t>((a.n + block - 1) / block - 1, room / (W * kWave * 4)));
+  }
+  const unsigned dyn = (unsigned)nheld * (unsigned)threads * 4u;
+  void* ptrs[] = {&args, &info, &nheld};
   hipError_t e;
   const PersistentGate gate(stream, grid);
   void* tk = capture ? nullptr : ktimer_begin(stream);
   if (!capture && dev_info().coop && tuning().coop) {
     e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&ss_persistent_kernel<WT, COPIES>),
-                                   dim3(grid), dim3(threads), ptrs, 0, stream);
+                                   dim3(grid), dim3(threads), ptrs, dyn, stream);
   } else {
-    hipLaunchKernelGGL((ss_persistent_kernel<WT, COPIES>), dim3(grid), dim3(threads), 0, stream, args,
-                       info);
+    hipLaunchKernelGGL((ss_persistent_kernel<WT, COPIES>), dim3(grid), dim3(threads), dyn, stream, args,
+                       info, nheld);
     e = hipGetLastError();
   }
   ktimer_end(tk, stream, 1);
@@ -1825,7 +1863,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
     if (T.validate) {
       hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                          (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, nullptr, nullptr, 0, nullptr, 0,
-                         A.n1, (int64_t)-1, false, A);
+                         A.n1, (int64_t)-1, false, nullptr, A);
       const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
       hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
                          A.n, A.m, (int32_t)(WT == kWF32), &A.ctl->done, &A.ctl->converged);
@@ -1843,7 +1881,7 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, rowptr, A.hv, A.t_lane, A.w,
                      (int64_t)A.m, A.n1, placed ? (int64_t)seeds.source : (int64_t)-1,
-                     seeds.voff_dev != nullptr, A);
+                     seeds.voff_dev != nullptr, nullptr, A);
   if (T.validate) {
     const int vb = (int)std::min<int64_t>(4096, ((int64_t)A.m + 255) / 256 + 1);
     hipLaunchKernelGGL(ss_validate_kernel, dim3(vb), dim3(256), 0, stream, rowptr, colidx, A.w,
@@ -1954,46 +1992,56 @@ static SsLayout ss_copies_layout(int64_t n, int64_t m, int64_t k) {
 
 // The work of a run on copies grows with k; a tile reads each row once for all
 // its sources, but pays for whole 64-column rows and scans every vertex each
-// step.  Measured (copies / tile): grid 1000 x 1021 (4 edges per vertex), k = 8
-// 37.4 / 77.7 ms, k = 32 60.0 / 157.4 ms; ER n = 100,000 (8 per vertex), k = 8
-// 642 / 990 us, k = 32 1378 / 1416, k = 64 2265 / 1842; ER n = 1,000,000, k = 32
-// 10.0 / 11.4 ms (9.5 with a reverse graph); R-MAT (16 per vertex) scale 16,
-// k = 8 678 / 672 us, k = 16 948 / 751; scale 18, k = 8 1435 / 1541, k = 16 2441
-// / 1596.  Hop counts, whose tiles keep no distances: grid 500 x 500, k = 12
-// 12.9 / 25.9 ms; ER n = 300,000, k = 8 579 / 673 us, k = 32 1738 / 811; R-MAT
-// scale 18, k = 2 332 / 471, k = 8 656 / 523.
+// step.  So copies win where a call is short of work: with few sources, and in
+// long runs of small steps (grids) at any of the k here.  Long runs show when the
+// tile's step launches are over: what is left of a run then goes on on copies.
+// Measured (us, copies / tile; weighted): k = 8: ER of 6 to 12 edges per vertex, n =
+// 100,000 and 600,000, 0.75 to 0.9 of the tile's time; R-MAT scales 18 and 20, 8 to
+// 30 edges per vertex, 0.94 to 1.09; k = 2: ER 0.59 to 0.87, R-MAT 0.69 to 0.97.  k
+// = 16: ER 0.88 to 1.08, R-MAT 1.35 to 1.87; k = 24: ER 1.02 to 1.23, R-MAT 1.62 to
+// 2.37.  Fewer edges per vertex: R-MAT scale 20 with 3, k = 2 1116 / 767, k = 32 4191
+// / 1827; ER n = 100,000 with 3, k = 8 1001 / 878, k = 24 2432 / 1121.  Hop counts:
+// R-MAT scale 20 with 8, k = 4 651 / 745, k = 8 1160 / 793; with 16, k = 2 558 / 840,
+// k = 4 1014 / 869; with 5, k = 32 3452 / 850; ER n = 1,000,000 with 8, k = 4 758 /
+// 1053, k = 8 1375 / 1255.  Grids, tile / copies / tile first: 1000 x 1021, k = 8
+// 77.7 / 38.2 / 39.2 ms, k = 32 157.4 / 58.7 / 64.2 ms; 200 x 221, k = 8 - / 4.06 /
+// 4.59 ms.  Tile first where copies alone lose: R-MAT scale 20 with 3, k = 32 1.81
+// ms, ER n = 100,000 with 3, k = 8 837 us.
 static int ss_copies_most(int64_t n, int64_t m, bool unit) {
+  if (m < 6 * n) return 0;
+  if (m < 12 * n) return unit ? 4 : 8;
+  return unit ? 3 : 8;
+}
+// The most sources whose runs go on on copies (hop counts of many edges per vertex
+// are over by then).
+static int ss_handover_most(int64_t n, int64_t m, bool unit) {
   if (m < 6 * n) return 32;
   if (m < 12 * n) return unit ? 8 : 24;
-  return unit ? 4 : 8;
+  return 0;
+}
+
+// The frontier records of a step after which a run goes on on copies: a tile shares
+// the rows of a dense step among its sources.
+uint32_t ss_handover_rows(int64_t n) { return (uint32_t)std::max<int64_t>(n / 16, 16384); }
+
+static bool ss_copies_sizes(int64_t n, int64_t m, int32_t k, size_t ws_bytes) {
+  const Tuning& T = tuning();
+  return T.mode == 0 && T.tile_step_launches > 0 && T.validate == 0 && k >= 2 && n >= 1024 &&
+         k * n <= (int64_t)1 << 30 && ss_copies_layout(n, m, k).total <= ws_bytes;
 }
 
 bool ss_copies_fit(int64_t n, int64_t m, int32_t k, bool unit, size_t ws_bytes) {
-  const Tuning& T = tuning();
-  return T.mode == 0 && T.tile_step_launches > 0 && T.validate == 0 && k >= 2 &&
-         k <= ss_copies_most(n, m, unit) && n >= 1024 && k * n <= (int64_t)1 << 30 &&
-         ss_copies_layout(n, m, k).total <= ws_bytes;
+  return k <= ss_copies_most(n, m, unit) && ss_copies_sizes(n, m, k, ws_bytes);
 }
 
-template <int WT>
-static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int32_t* sources,
-                                   int32_t k, dawn_run_info* info, hipStream_t stream) {
-  const Tuning& T = tuning();
-  const int threads = T.wg_threads > 0 ? T.wg_threads : 1024;
-  const int fill_blocks = (int)std::min<int64_t>(4096, ((int64_t)A.n + 255) / 256 + 1);
-  hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
-                     (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, A.rowptr, A.hv, A.t_lane, A.w,
-                     (int64_t)A.m, A.n1, (int64_t)-1, false, A);
-  hipLaunchKernelGGL(ss_copy_seed_kernel<WT>, dim3(1), dim3(64), 0, stream, A, sources, k);
-  return ss_launch_persistent<WT, true>(A, ss_persistent_grid<WT, true>(A.n, (int64_t)k * A.m, threads),
-                                        threads, info, stream, false);
+bool ss_handover_fits(int64_t n, int64_t m, int32_t k, bool unit, size_t ws_bytes) {
+  return k <= ss_handover_most(n, m, unit) && ss_copies_sizes(n, m, k, ws_bytes);
 }
 
-dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
-                          int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
-                          void* ws, dawn_run_info* info, hipStream_t stream) {
+// The arguments of a run on copies, laid out at ws.
+static SsArgs ss_copies_args(const int32_t* rowptr, const int32_t* colidx, const void* w, int32_t n,
+                             int32_t m, int32_t k, const SsLayout& L, void* dist, void* ws) {
   const Tuning& T = tuning();
-  const SsLayout L = ss_copies_layout(n, m, k);
   char* base = static_cast<char*>(ws);
   SsArgs A{};
   A.rowptr = rowptr;
@@ -2022,9 +2070,135 @@ dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const vo
   A.ctl = reinterpret_cast<SsCtl*>(base + L.ctl);
   A.bar_ticks = (unsigned long long)T.barrier_ms * kTicksPerMs;
   A.latch = dev_info().latch;
+  return A;
+}
+
+// The launches of a run on copies: `start` (placing its frontier) between the fill
+// and the persistent launch.
+template <int WT, typename F>
+static dawn_status ss_copies_launch(const SsArgs& A, const SsLayout& L, uint32_t* dist, int32_t k,
+                                    const uint32_t* over, dawn_run_info* info, hipStream_t stream,
+                                    F&& start) {
+  const int threads = tuning().wg_threads > 0 ? tuning().wg_threads : 1024;
+  const int fill_blocks = (int)std::min<int64_t>(4096, ((int64_t)A.n + 255) / 256 + 1);
+  hipLaunchKernelGGL(ss_fill_kernel<WT>, dim3(fill_blocks), dim3(256), 0, stream, dist,
+                     (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, A.rowptr, A.hv, A.t_lane, A.w,
+                     (int64_t)A.m, A.n1, (int64_t)-1, false, over, A);
+  start();
+  return ss_launch_persistent<WT, true>(A, ss_persistent_grid<WT, true>(A.n, (int64_t)k * A.m, threads),
+                                        threads, info, stream, false);
+}
+
+template <int WT>
+static dawn_status ss_copies_run_t(const SsArgs& A, const SsLayout& L, const int32_t* sources,
+                                   int32_t k, dawn_run_info* info, hipStream_t stream) {
+  return ss_copies_launch<WT>(A, L, A.dist, k, nullptr, info, stream, [&] {
+    hipLaunchKernelGGL(ss_copy_seed_kernel<WT>, dim3(1), dim3(64), 0, stream, A, sources, k);
+  });
+}
+
+dawn_status ss_copies_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,
+                          int32_t n, int32_t m, const int32_t* sources, int32_t k, void* dist,
+                          void* ws, dawn_run_info* info, hipStream_t stream) {
+  const SsLayout L = ss_copies_layout(n, m, k);
+  const SsArgs A = ss_copies_args(rowptr, colidx, w, n, m, k, L, dist, ws);
   if (wt == kWF32) return ss_copies_run_t<kWF32>(A, L, sources, k, info, stream);
   if (wt == kWUNIT) return ss_copies_run_t<kWUNIT>(A, L, sources, k, info, stream);
   return ss_copies_run_t<kWU32>(A, L, sources, k, info, stream);
+}
+
+// From a tile (one segment) that is not done to a run on copies: the frontier's
+// masks become bits, rows longer than t_lane are queued, and the counters and the
+// step go on.  The tile's distances have been stored; of hop counts those of the
+// frontier, which a tile takes down in its next compaction, are stored here.
+template <int WT>
+__global__ void __launch_bounds__(256) ss_handover_kernel(SsArgs A, TileArgs t, int32_t k) {
+  SsCtl* C = A.ctl;
+  const TileCtl* T = t.ctl;
+  if (T->done) return;  // (every read here is of an earlier launch's words)
+  const uint32_t step = T->step;
+  const int cur = step & 1, rc = step % kRot;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    unsigned long long fe = 0, es = 0, im = 0, sa = 0, se = 0;
+    for (int i = 0; i < kCtrStripes; i++) {
+      fe += T->ctr[i].fe;
+      es += T->ctr[i].es;
+      im += T->ctr[i].im;
+      sa += T->ctr[i].sa;
+      se += T->ctr[i].se;
+    }
+    C->step = step;
+    C->ctr.fe = sa;
+    C->ctr.es = se;
+    C->ctr.im = im;
+    C->u_rows = fe - sa;
+    C->u_edges = es - se;
+    if (T->overflow) atomicOr(&C->overflow, 1u);
+  }
+  const unsigned long long* mk = t.mk[step % 3];
+  const int lane = lane_id();
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t v0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x - lane; v0 < A.n1; v0 += stride) {
+    const int64_t v = v0 + lane;
+    const unsigned long long m = v < A.n1 ? mk[v] : 0ull;
+    if (__ballot(m != 0ull) == 0ull) continue;
+    int32_t start = 0, deg = 0;
+    if (m) {
+      start = A.rowptr[v];
+      deg = A.rowptr[v + 1] - start;
+    }
+    for (int j = 0; j < k; j++) {
+      const bool on = (m >> j) & 1ull;
+      const unsigned long long b = __ballot(on);
+      if (b == 0ull) continue;
+      // 64 bits from bit j * n1 + v0 on: parts of up to three words
+      const int64_t bit0 = (int64_t)j * A.n1 + v0;
+      const int sh = (int)(bit0 & 31);
+      const uint32_t part = lane == 0   ? (uint32_t)(b << sh)
+                            : lane == 1 ? (uint32_t)(b >> (32 - sh))
+                            : lane == 2 && sh ? (uint32_t)(b >> (64 - sh))
+                                              : 0u;
+      if (part) atomicOr(&A.bm[cur][(bit0 >> 5) + lane], part);
+      if (!on) continue;
+      const int32_t x = j * A.n1 + (int32_t)v;
+      if (WT == kWUNIT) A.dist[x] = step;
+      if (deg <= A.t_lane) continue;
+      if (deg <= A.t_wave) {
+        const uint32_t p = atomicAdd(&C->cnt[rc][1].v, 1u);
+        if (p < A.cap_v) A.qwave[cur][p] = x;
+        else atomicOr(&C->overflow, 1u);
+      } else {
+        const uint32_t nch = (uint32_t)((deg + A.t_chunk - 1) / A.t_chunk);
+        const uint32_t p = atomicAdd(&C->cnt[rc][2].v, nch);
+        for (uint32_t c = 0; c < nch; c++) {
+          const int32_t off = (int32_t)c * A.t_chunk;
+          if (p + c < A.cap_wg)
+            A.qwg[cur][p + c] = make_int4(x, start + off, min(A.t_chunk, deg - off), c == 0);
+          else
+            atomicOr(&C->overflow, 1u);
+        }
+      }
+    }
+  }
+}
+
+template <int WT>
+static dawn_status ss_handover_t(const SsArgs& A, const SsLayout& L, const TileArgs& tile, int32_t k,
+                                 dawn_run_info* info, hipStream_t stream) {
+  return ss_copies_launch<WT>(A, L, nullptr, k, &tile.ctl->done, info, stream, [&] {
+    const int blocks = (int)std::min<int64_t>(2048, ((int64_t)A.n1 + 255) / 256);
+    hipLaunchKernelGGL(ss_handover_kernel<WT>, dim3(blocks), dim3(256), 0, stream, A, tile, k);
+  });
+}
+
+dawn_status ss_handover(const TileArgs& tile, int wt, int32_t k, void* dist, void* ws,
+                        dawn_run_info* info, hipStream_t stream) {
+  const SsLayout L = ss_copies_layout(tile.n, tile.m, k);
+  const SsArgs A =
+      ss_copies_args(tile.rowptr, tile.colidx, tile.w, tile.n, tile.m, k, L, dist, ws);
+  if (wt == kWF32) return ss_handover_t<kWF32>(A, L, tile, k, info, stream);
+  if (wt == kWUNIT) return ss_handover_t<kWUNIT>(A, L, tile, k, info, stream);
+  return ss_handover_t<kWU32>(A, L, tile, k, info, stream);
 }
 
 dawn_status ss_run(const int32_t* rowptr, const int32_t* colidx, const void* w, int wt,

@@ -768,11 +768,26 @@ __device__ __forceinline__ bool any_active(const TileCtl* C, int rn, int nseg) {
   return a != 0ull;
 }
 
+// Whether the step's frontier held at most `few` queue records (rows, and chunks of
+// long rows), and hardly more than the step's before: a frontier that multiplies
+// (ER, R-MAT) is on its way to the dense steps.  The counts stand until the second
+// compaction after the step's.
+__device__ __forceinline__ bool tile_few_rows(const TileCtl* C, uint32_t step, uint32_t few) {
+  const int rc = step % kRot, rp = (step + kRot - 1) % kRot;
+  uint32_t now = 0, before = 0;
+  for (int t = 0; t < 3; t++) {
+    now += ld_agent(&C->cnt[rc][t].v);
+    before += ld_agent(&C->cnt[rp][t].v);
+  }
+  return now <= few && now <= before + before / 4u;
+}
+
 // All steps (up to max_steps, and at most n when cap_n) in one launch with a
-// grid barrier after each compaction and each relaxation.
+// grid barrier after each compaction and each relaxation.  few > 0: the launch also
+// ends, its run not done, after a step of at most so many frontier records.
 template <bool F32>
 __global__ void __launch_bounds__(1024) tile_persistent_kernel(TileArgs A, int32_t max_steps,
-                                                               int32_t cap_n) {
+                                                               int32_t cap_n, uint32_t few) {
   __shared__ unsigned long long sh_colact[kSegMax];
   __shared__ CompactShared csh;
   TileCtl* C = A.ctl;
@@ -803,7 +818,7 @@ __global__ void __launch_bounds__(1024) tile_persistent_kernel(TileArgs A, int32
     step++;
     if (!act) { status = 1; finished = true; break; }
     if (cap_n && step >= (uint32_t)A.n) { status = 0; finished = true; break; }
-    if (step == stop) break;
+    if (step == stop || (few && tile_few_rows(C, step - 1, few))) break;
   }
   // (the frontier's out-edges per step decide pull steps of step launches only)
   CtrStripe& S = C->ctr[blockIdx.x % kCtrStripes];
@@ -1240,7 +1255,7 @@ __device__ void utile_push_step(const TileArgs& A, uint32_t step, uint32_t gb, u
 // with a grid barrier after each compaction and each push step; at most n
 // steps in all.  As tile_persistent_kernel.
 template <int S>
-__global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A) {
+__global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A, uint32_t few) {
   __shared__ unsigned long long sh_colact[kSegMax];
   __shared__ CompactShared csh;
   TileCtl* C = A.ctl;
@@ -1250,6 +1265,7 @@ __global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A) {
   const uint32_t bar_base = ld_agent(&C->bar_base);
   uint32_t step = ld_agent(&C->step);
   int32_t status = 1;
+  bool finished = true;
   for (;;) {
     if (blockIdx.x == 0) tile_prologue(C, step, A.K);
     tile_compact<true>(A, step, blockIdx.x, gridDim.x, acc, csh);
@@ -1266,14 +1282,17 @@ __global__ void __launch_bounds__(1024) utile_persistent_kernel(TileArgs A) {
     step++;
     if (!act) break;
     if (step >= (uint32_t)A.n) { status = 0; break; }
+    if (few && tile_few_rows(C, step - 1, few)) { finished = false; break; }
   }
   CtrStripe& Sx = C->ctr[blockIdx.x % kCtrStripes];
   flush_acc(acc, &Sx.fe, &Sx.es, &Sx.im, &Sx.sa, &Sx.se);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st_agent(&C->step, step);
     st_agent(&C->bar_base, bar_base + epoch);
-    st_agent_i(&C->converged, status);
-    st_agent(&C->done, 1u);
+    if (finished) {
+      st_agent_i(&C->converged, status);
+      st_agent(&C->done, 1u);
+    }
   }
 }
 
@@ -1534,7 +1553,8 @@ __global__ void tile_info_kernel(const TileCtl* C, int32_t K, dawn_run_info* inf
   for (int j = threadIdx.x; j < K; j += blockDim.x) mx = max(mx, ld_agent_i(&C->colsteps[j]));
   atomicMax(&s_max, mx);
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  // (a run that is not done has been handed over to copies, which report it)
+  if (threadIdx.x != 0 || !ld_agent(&C->done)) return;
   const int32_t conv = run_status(ld_agent_i(&C->converged), ld_agent(&C->abort),
                                   ld_agent(&C->overflow));
   if (!info) {
@@ -1712,7 +1732,7 @@ static hipError_t launch_persistent(K kernel, int grid, int threads, hipStream_t
   return hipGetLastError();
 }
 
-dawn_status utile_persistent(const TileArgs& a, hipStream_t stream) {
+dawn_status utile_persistent(const TileArgs& a, uint32_t few, hipStream_t stream) {
   const Tuning& T = tuning();
   const int threads = T.wg_threads > 0 ? T.wg_threads : kTilePersistentThreads;
   auto k = a.nseg <= 1 ? utile_persistent_kernel<1> : a.nseg <= 2 ? utile_persistent_kernel<2>
@@ -1720,14 +1740,14 @@ dawn_status utile_persistent(const TileArgs& a, hipStream_t stream) {
   int grid = std::min(residency_of(k, threads).grid, kMaxGrid);
   if (T.grid > 0 && T.grid < grid) grid = T.grid;
   void* tk = ktimer_begin(stream);
-  const hipError_t e = launch_persistent(k, grid, threads, stream, a);
+  const hipError_t e = launch_persistent(k, grid, threads, stream, a, few);
   ktimer_end(tk, stream, 1);
   return hip_check(e, "hop-count tile persistent launch");
 }
 
 template <bool F32>
 static dawn_status tile_steps_t(const TileArgs& a, bool persistent, int32_t max_steps,
-                                hipStream_t stream) {
+                                hipStream_t stream, uint32_t few) {
   const Tuning& T = tuning();
   const int threads = T.wg_threads > 0 ? T.wg_threads : 256;
   const int32_t cap_n = persistent ? 1 : 0;
@@ -1739,7 +1759,8 @@ static dawn_status tile_steps_t(const TileArgs& a, bool persistent, int32_t max_
     aa.pull_min = -1;  // pull steps need the step-launch path
     void* tk = ktimer_begin(stream);
     const hipError_t e =
-        launch_persistent(tile_persistent_kernel<F32>, grid, pthreads, stream, aa, max_steps, cap_n);
+        launch_persistent(tile_persistent_kernel<F32>, grid, pthreads, stream, aa, max_steps, cap_n,
+                          few);
     ktimer_end(tk, stream, 1);
     return hip_check(e, "tile persistent launch");
   }
@@ -1794,9 +1815,9 @@ dawn_status utile_steps(const TileArgs& a, int32_t max_steps, hipStream_t stream
 }
 
 dawn_status tile_steps(const TileArgs& a, bool f32, bool persistent, int32_t max_steps,
-                       hipStream_t stream) {
-  return f32 ? tile_steps_t<true>(a, persistent, max_steps, stream)
-             : tile_steps_t<false>(a, persistent, max_steps, stream);
+                       hipStream_t stream, uint32_t few) {
+  return f32 ? tile_steps_t<true>(a, persistent, max_steps, stream, few)
+             : tile_steps_t<false>(a, persistent, max_steps, stream, few);
 }
 
 dawn_status tile_done_bits(const TileArgs& a, int32_t k, uint32_t* done_bits, hipStream_t stream) {
