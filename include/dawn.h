@@ -158,7 +158,8 @@ typedef struct {
  *   2 one persistent launch for all steps, with a grid barrier between steps.
  * A persistent launch's grid is at most what the compute units hold at once, by
  * the kernel's compiled VGPR and LDS use (dawn_device_query): tiles take that many
- * workgroups, single-source runs fewer on sparse or small graphs.  A grid barrier that
+ * workgroups, single-source runs fewer on small graphs and on sparse graphs of even
+ * degrees (grids, ER; told on the device).  A grid barrier that
  * waits longer than barrier_ms ends the run with converged = -2, never a hang.
  * Two persistent launches that each hold part of the device would wait for each
  * other, so those of one device are ordered, whatever their streams, and so are

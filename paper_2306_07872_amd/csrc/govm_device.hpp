@@ -75,6 +75,7 @@ struct alignas(256) SsCtl {
   uint32_t bar_base;          // the last barrier epoch of earlier persistent launches
   uint32_t negfloor;          // int32 weights: a path sum fell to or below INT32_MIN
   NfState nf;                 // of the next step
+  uint32_t even;              // rows are of even length: the persistent launch takes fewer workgroups
   unsigned long long es_seen; // ctr.es before the step (step launches)
   unsigned long long u_rows, u_edges;  // union_rows / union_edges less ctr.fe / ctr.es (a tile's steps before)
   alignas(128) uint32_t upd[kRot];  // [step % 4]: any improvement during the previous step

@@ -124,21 +124,24 @@ __device__ __forceinline__ void nf_advance(NfState& s, uint32_t M, float work, f
 // over runs of 64 samples (within a factor of 8): with one threshold for all, the
 // graphs of larger weights would wait for the others to end, and the steps add up.
 // 16 ER graphs of 240,000 edges, one with weights 100 times the others': 35 steps,
-// 1077 us with deferral, 19 and 870 without.  Every thread of the workgroup (whole
-// wavefronts) calls it and gets the result.
+// 1077 us with deferral, 19 and 870 without.  even: whether those rules hold (also
+// for weights that are never deferred).  Every thread of the workgroup (whole
+// wavefronts) calls it and gets the results.
 template <int WT>
 __device__ float nf_floor(int64_t n, int64_t m, const int32_t* rowptr, const uint32_t* w,
-                          int samples, bool batch) {
-  if (!nf_weights<WT>() || !rowptr || !w || m < 1) return 0.f;
+                          int samples, bool batch, bool& even) {
+  even = false;
+  if (!rowptr || m < 1 || (nf_weights<WT>() && !w)) return 0.f;
   __shared__ float part[5][kMaxWavesPerBlock];
   __shared__ float s_floor;
+  __shared__ bool s_even;
   float sw = 0.f, sd = 0.f, sd2 = 0.f, lo = 1e9f, hi = -1e9f;
   const int64_t ew = m > samples ? m / samples : 1, rw = n > samples ? n / samples : 1;
   const int ne = (int)(m < samples ? m : samples), nr = (int)(n < samples ? n : samples);
 #pragma unroll 4
-  for (int i = threadIdx.x; i < ne; i += blockDim.x)
+  for (int i = threadIdx.x; i < (nf_weights<WT>() ? ne : 0); i += blockDim.x)
     sw += WT == kWF32 ? __uint_as_float(w[i * ew]) : (float)w[i * ew];
-  if (batch) {
+  if (nf_weights<WT>() && batch) {
     const int ne64 = ne & ~63;
     for (int i = threadIdx.x; i < ne64; i += blockDim.x) {
       const uint32_t x = w[i * ew];
@@ -181,9 +184,11 @@ __device__ float nf_floor(int64_t n, int64_t m, const int32_t* rowptr, const uin
       hi = fmaxf(hi, part[4][i]);
     }
     // sd2 / sd <= 4 * sd / nr
-    s_floor = sd2 * nr <= 4.f * sd * sd && hi - lo <= 3.f ? fmaxf(kNfDelta * (sw / ne), 1e-30f) : 0.f;
+    s_even = sd2 * nr <= 4.f * sd * sd && hi - lo <= 3.f;
+    s_floor = nf_weights<WT>() && s_even ? fmaxf(kNfDelta * (sw / ne), 1e-30f) : 0.f;
   }
   __syncthreads();
+  even = s_even;
   return s_floor;
 }
 
@@ -269,8 +274,10 @@ __global__ void ss_fill_kernel(uint32_t* dist, int64_t n, uint32_t* bm0, uint32_
     for (int i = threadIdx.x; i < (int)(offsetof(SsCtl, bar.slot) / 4); i += blockDim.x) c[i] = 0;
     __syncthreads();
     if (threadIdx.x < kRot) ctl->minp[threadIdx.x].v = kNoKey;
-    const float floor = nf_floor<WT>(n1, m, rowptr, w, kNfSamples, batch);
+    bool even;
+    const float floor = nf_floor<WT>(n1, m, rowptr, w, kNfSamples, batch, even);
     if (threadIdx.x == 0) {
+      ctl->even = even;
       ctl->nf = NfState{kNoKey, floor, floor, 0u};
       if (seed >= 0) ss_queue_seed<true>(A, seed);
     }
@@ -986,16 +993,20 @@ __device__ __forceinline__ bool ss_grid_sync(SsCtl* C, uint32_t nblocks, uint32_
 // up, the run ends with status -2, reported to the caller.
 template <int WT, bool COPIES>
 __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_info* info,
-                                                             int32_t nheld) {
+                                                             int32_t nheld, uint32_t even_wgs,
+                                                             uint32_t wide_wgs) {
   __shared__ SsShared sh;
   extern __shared__ uint32_t held[];  // copies: rows left for later, see ss_step
   SsCtl* C = A.ctl;
+  // the workgroups that take part (`even` is of an earlier launch)
+  const uint32_t gb = blockIdx.x, nb = C->even ? even_wgs : wide_wgs;
+  if (gb >= nb) return;
   // Ended by an earlier launch, or given up by workgroup 0, which may happen while
   // this workgroup starts: one read for all of its threads, which would else part
   // here and miss each other at the barriers of the steps.
   if (ld_agent_block(&C->done)) {
     if (COPIES && ld_agent_i(&C->converged) == kNoRun) return;  // (an earlier launch's word)
-    if (last_block_arrive(&C->arrive, gridDim.x) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
+    if (last_block_arrive(&C->arrive, nb) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
     return;
   }
   Acc acc;
@@ -1009,7 +1020,6 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_
   // launches that count as they enqueue came before
   bool count = step > 0 && !A.counted;
   int32_t status = 1;
-  const uint32_t gb = blockIdx.x, nb = gridDim.x;
   const uint32_t wave = threadIdx.x >> 6, W = blockDim.x >> 6;
   uint32_t left0 = 0u;
   if (nf_weights<WT>()) {
@@ -1031,7 +1041,7 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_
       ss_step<WT, false, kAll, COPIES>(A, step, gb, nb, acc, sh, counts, kNoKey, count, left0, held, nheld);
     }
     count = true;
-    if (!ss_grid_sync<WT>(C, gridDim.x, bar_base, epoch, A.bar_ticks, sh, nf, A.nf_work, next)) {
+    if (!ss_grid_sync<WT>(C, nb, bar_base, epoch, A.bar_ticks, sh, nf, A.nf_work, next)) {
       status = -2;
       break;
     }
@@ -1054,7 +1064,7 @@ __global__ void __launch_bounds__(1024) ss_persistent_kernel(SsArgs A, dawn_run_
     st_agent(&C->bar_base, bar_base + epoch);
   }
   // the last workgroup to leave has every counter: it reports the run
-  if (last_block_arrive(&C->arrive, gridDim.x) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
+  if (last_block_arrive(&C->arrive, nb) && threadIdx.x == 0) ss_report<WT>(C, info, A.latch);
 }
 
 // One step per launch; the last block to finish advances the step.
@@ -1317,8 +1327,10 @@ __global__ void __launch_bounds__(1024) ss_cu_kernel(SsArgs A, const int32_t* so
       atomicExch(&C->overflow, 0u);
     }
     // far rows wait, as in the multi-workgroup runs
+    bool even;
     const float floor =
-        A.m >= kNfMinCu ? nf_floor<WT>(n, A.m, A.rowptr, A.w, 1024, !MULTI && voff) : 0.f;
+        nf_weights<WT>() && A.m >= kNfMinCu
+            ? nf_floor<WT>(n, A.m, A.rowptr, A.w, 1024, !MULTI && voff, even) : 0.f;
     NfState nf{kNoKey, floor, floor, 0u};
     // (the words of the rows left for later stay in a register of the lane that scans
     // them, one word a lane, as all do at 1024 threads)
@@ -1758,21 +1770,33 @@ Residency ss_persistent_residency(int threads) {
   return residency_of(ss_persistent_kernel<kWU32, false>, threads);
 }
 
-// Workgroups of a persistent launch.  A barrier costs 1.9 us with 64 and 3.3 us
-// with 256, and the steps of sparse or small graphs are bound by it and by one
-// chain of loads; steps with many edges need the whole chip.  m * (m / n) tells
-// the two apart.  Measured at 256 / 128 / 64 / 32 workgroups: grid 2048 x 2048
+// Workgroups of a persistent launch on a graph of even degrees.  A barrier costs 1.9
+// us with 64 and 3.3 us with 256, and the steps of sparse or small graphs are bound
+// by it and by one chain of loads; steps with many edges need the whole chip.  m *
+// (m / n) tells the two apart.  Measured at 256 / 128 / 64 / 32 workgroups: grid 2048 x 2048
 // 43.5 / 37.9 / 41.2 / 50.1 ms, grid 512 x 512 12.9 / 11.3 / 10.4 / 9.2 ms, ER
 // n = 100,000 420 / 359 / 352 / 366 us, ER n = 1,000,000 910 / 863 / 1053 /
 // 1519 us, R-MAT scale 16 447 / 439 / 444 / 460 us, scale 20 820 / 952 / 1320 /
 // 2129 us.  Powers of two: workgroup b runs on XCD b mod 8, and with 125 or 112
 // workgroups the 2048 x 2048 grid took 43.4 and 40.4 ms, against 37.9 with 128
-// (the rows below each other of a grid then stay on one XCD).
-static int ss_persistent_wgs(int64_t n, int64_t m, int resident) {
+// (the rows below each other of a grid then stay on one XCD).  With 2 to 5 edges per
+// vertex, at 32 / 64 / 128 / 256: ER n = 300,000 with 2 543 / 572 / 625 / 751 us, n =
+// 1,000,000 with 2 1074 / 937 / 933 / 1088, with 3 1168 / 927 / 835 / 946, grid 1024 x
+// 1024 17.3 / 17.7 / 18.4 / 21.3 ms.
+static int ss_even_wgs(int64_t n, int64_t m, int resident) {
   const double grow = (double)m * ((double)m / (double)n) / (double)(1 << 26);
-  int wgs = m < 6 * n ? 32 : 64;
+  int wgs = m < 6 * n && n < 1 << 19 ? 32 : 64;
   while (wgs < resident && grow * 128 > wgs * 1.42) wgs *= 2;
   return std::min(wgs, resident);
+}
+
+// And on others, whose frontiers are wide after a few steps however few edges a
+// vertex has.  At 32 / 64 / 128 / 256: R-MAT scale 18 with 2 edges per vertex 238 /
+// 216 / 212 / 229 us, scale 20 with 4 1005 / 706 / 570 / 564, scale 21 with 4 1504 /
+// 930 / 679 / 588, scale 22 with 4 2319 / 1348 / 902 / 762; a star of 50,000 leaves
+// 128 / 129 / 129 / 132, of 2,000,000 882 / 553 / 374 / 240.
+static int ss_wide_wgs(int64_t m, int resident) {
+  return std::min(m < 3 << 17 ? 64 : m < 1 << 20 ? 128 : resident, resident);
 }
 
 // Tier bounds of persistent launches, relative to the tuning's (which are those of
@@ -1788,17 +1812,30 @@ static void ss_persistent_tiers(SsArgs& A) {
   A.t_chunk = std::max(256, T.t_chunk / 4);
 }
 
-// The grid of a persistent launch: tuning field `grid` where it is set, else the
-// rule's, and what the device holds at once.
+// The workgroups of a persistent launch, which the kernel chooses from by the rows'
+// lengths: tuning field `grid` where it is set, else the rules', and what the device
+// holds at once.
+struct SsWgs {
+  uint32_t even, wide;
+  void limit(int most) {
+    even = std::min(even, (uint32_t)most);
+    wide = std::min(wide, (uint32_t)most);
+  }
+};
 template <int WT, bool COPIES>
-static int ss_persistent_grid(int64_t n, int64_t m, int threads) {
+static SsWgs ss_persistent_wgs(int64_t n, int64_t m, int threads) {
   const int most = std::min(residency_of(ss_persistent_kernel<WT, COPIES>, threads).grid, kMaxGrid);
-  return tuning().grid > 0 ? std::min(tuning().grid, most) : ss_persistent_wgs(n, m, most);
+  if (tuning().grid > 0) {
+    const uint32_t g = (uint32_t)std::min(tuning().grid, most);
+    return SsWgs{g, g};
+  }
+  return SsWgs{(uint32_t)ss_even_wgs(n, m, most), (uint32_t)ss_wide_wgs(m, most)};
 }
 
 template <int WT, bool COPIES>
-static dawn_status ss_launch_persistent(const SsArgs& a, int grid, int threads, dawn_run_info* info,
+static dawn_status ss_launch_persistent(const SsArgs& a, SsWgs wgs, int threads, dawn_run_info* info,
                                         hipStream_t stream, bool capture) {
+  const int grid = (int)std::max(wgs.even, wgs.wide);
   SsArgs args = a;
   // Copies: LDS for the rows left for later in the blocks after each wavefront's
   // first (1000 x 1021 grid, 32 sources: 64 ms; 69 with them in memory), as far as
@@ -1807,13 +1844,13 @@ static dawn_status ss_launch_persistent(const SsArgs& a, int grid, int threads, 
   int32_t nheld = 0;
   if (COPIES) {
     const Residency r = residency_of(ss_persistent_kernel<WT, COPIES>, threads);
-    const int64_t W = threads / kWave, block = (int64_t)grid * W * kWave * 32;
+    const int64_t W = threads / kWave, block = (int64_t)std::min(wgs.even, wgs.wide) * W * kWave * 32;
     const int64_t room = std::min<int64_t>(65536, 163840 / std::max(r.per_cu, 1) - 2048) - r.lds;
     nheld = (int32_t)std::max<int64_t>(
         0, std::min<int64_t>((a.n + block - 1) / block - 1, room / (W * kWave * 4)));
   }
   const unsigned dyn = (unsigned)nheld * (unsigned)threads * 4u;
-  void* ptrs[] = {&args, &info, &nheld};
+  void* ptrs[] = {&args, &info, &nheld, &wgs.even, &wgs.wide};
   hipError_t e;
   const PersistentGate gate(stream, grid);
   void* tk = capture ? nullptr : ktimer_begin(stream);
@@ -1822,7 +1859,7 @@ static dawn_status ss_launch_persistent(const SsArgs& a, int grid, int threads, 
                                    dim3(grid), dim3(threads), ptrs, dyn, stream);
   } else {
     hipLaunchKernelGGL((ss_persistent_kernel<WT, COPIES>), dim3(grid), dim3(threads), dyn, stream, args,
-                       info, nheld);
+                       info, nheld, wgs.even, wgs.wide);
     e = hipGetLastError();
   }
   ktimer_end(tk, stream, 1);
@@ -1910,11 +1947,11 @@ static dawn_status ss_run_t(const SsArgs& A, const int32_t* rowptr, const int32_
   a.counted = mode == 1 && A.pull_min >= 0;
   ss_persistent_tiers(a);
   a.pull_min = -1;  // pull steps need step launches (the last workgroup clears the bitmap)
-  int grid = ss_persistent_grid<WT, false>(A.n, A.m, threads);
-  if (T.ss_tail_grid > 0 && T.ss_tail_grid < grid) grid = T.ss_tail_grid;
-  if (lone) grid = 1;
-  if (wgs) *wgs = grid;
-  if ((st = ss_launch_persistent<WT, false>(a, grid, threads, info, stream, capture)) != DAWN_OK)
+  SsWgs pw = ss_persistent_wgs<WT, false>(A.n, A.m, threads);
+  if (T.ss_tail_grid > 0) pw.limit(T.ss_tail_grid);
+  if (lone) pw.limit(1);
+  if (wgs) *wgs = (int)std::max(pw.even, pw.wide);
+  if ((st = ss_launch_persistent<WT, false>(a, pw, threads, info, stream, capture)) != DAWN_OK)
     return st;
   if constexpr (WT == kWI32) {
     hipLaunchKernelGGL(ss_decode_i32_kernel, dim3(fill_blocks), dim3(256), 0, stream, A.dist,
@@ -2085,7 +2122,7 @@ static dawn_status ss_copies_launch(const SsArgs& A, const SsLayout& L, uint32_t
                      (int64_t)A.n, A.bm[0], A.bm[1], L.nwords, A.ctl, A.rowptr, A.hv, A.t_lane, A.w,
                      (int64_t)A.m, A.n1, (int64_t)-1, false, over, A);
   start();
-  return ss_launch_persistent<WT, true>(A, ss_persistent_grid<WT, true>(A.n, (int64_t)k * A.m, threads),
+  return ss_launch_persistent<WT, true>(A, ss_persistent_wgs<WT, true>(A.n, (int64_t)k * A.m, threads),
                                         threads, info, stream, false);
 }
 
