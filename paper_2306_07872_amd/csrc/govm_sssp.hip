@@ -2036,8 +2036,10 @@ static SsLayout ss_copies_layout(int64_t n, int64_t m, int64_t k) {
 // 100,000 and 600,000, 0.75 to 0.9 of the tile's time; R-MAT scales 18 and 20, 8 to
 // 30 edges per vertex, 0.94 to 1.09; k = 2: ER 0.59 to 0.87, R-MAT 0.69 to 0.97.  k
 // = 16: ER 0.88 to 1.08, R-MAT 1.35 to 1.87; k = 24: ER 1.02 to 1.23, R-MAT 1.62 to
-// 2.37.  Fewer edges per vertex: R-MAT scale 20 with 3, k = 2 1116 / 767, k = 32 4191
-// / 1827; ER n = 100,000 with 3, k = 8 1001 / 878, k = 24 2432 / 1121.  Hop counts:
+// 2.37.  Fewer edges per vertex, copies / tile first: R-MAT scale 20 with 3, k = 4 786
+// / 906, k = 8 1257 / 1248, scale 20 with 5, k = 4 1077 / 1107, k = 8 1738 / 1574; ER n
+// = 100,000 with 3, k = 4 666 / 727, n = 600,000, k = 4 1418 / 1469, k = 8 2518 / 2063;
+// hop counts R-MAT scale 20 with 5, k = 4 556 / 720, k = 8 924 / 744.  Hop counts:
 // R-MAT scale 20 with 8, k = 4 651 / 745, k = 8 1160 / 793; with 16, k = 2 558 / 840,
 // k = 4 1014 / 869; with 5, k = 32 3452 / 850; ER n = 1,000,000 with 8, k = 4 758 /
 // 1053, k = 8 1375 / 1255.  Grids, tile / copies / tile first: 1000 x 1021, k = 8
@@ -2045,7 +2047,7 @@ static SsLayout ss_copies_layout(int64_t n, int64_t m, int64_t k) {
 // 4.59 ms.  Tile first where copies alone lose: R-MAT scale 20 with 3, k = 32 1.81
 // ms, ER n = 100,000 with 3, k = 8 837 us.
 static int ss_copies_most(int64_t n, int64_t m, bool unit) {
-  if (m < 6 * n) return 0;
+  if (m < 6 * n) return 4;
   if (m < 12 * n) return unit ? 4 : 8;
   return unit ? 3 : 8;
 }

@@ -53,7 +53,7 @@ def _run(dawn, call, csr, srcs, tg=None, **tune):
 def test_weighted(dawn, name, wk, ti):
     g = GRAPHS[name](wk)
     csr = dawn.Csr.from_graph(g)
-    k = {"er": 20, "hubs": 6}.get(name, (2, 9, 31, 32, 12)[ti])
+    k = {"er": 20, "hubs": 6}.get(name, (5, 9, 31, 32, 12)[ti])
     srcs = np.random.default_rng(ti).integers(0, g.n, k).astype(np.int32)
     srcs[0], srcs[-1] = g.n - 1, srcs[k // 2]
     announce("handover", name, wk, "k", k, TUNINGS[ti])
@@ -69,7 +69,7 @@ def test_weighted(dawn, name, wk, ti):
 def test_hop_counts_and_counters(dawn, name, ti):
     g = GRAPHS[name]("u32")
     csr = dawn.Csr.from_graph(g)
-    k = {"er": 7, "hubs": 6}.get(name, (2, 9, 31, 32, 12)[ti])
+    k = {"er": 7, "hubs": 6}.get(name, (5, 9, 31, 32, 12)[ti])
     srcs = graphgen.pick_sources(g, k, 8)
     lv = [oracle.bfs(g, int(s)) for s in srcs]
     announce("handover, hop counts", name, "k", k, TUNINGS[ti])
@@ -97,7 +97,7 @@ def test_improvements_go_on(dawn):
     csr = dawn.Csr.from_graph(g)
     for tune in (dict(), dict(tile_step_launches=1), dict(t_lane=1, t_wave=64)):
         announce("handover, improvements", tune)
-        D, i = _run(dawn, dawn.msssp, csr, np.array([0, 400, 0], np.int32), **tune)
+        D, i = _run(dawn, dawn.msssp, csr, np.array([0, 400, 0, 401, 402], np.int32), **tune)
         assert i["improvements"] == 2 * (L + T * (L + 1)) and i["steps"] >= L + 1
         assert_sssp_matches(g, 0, D[2], tag="chain")
 
