@@ -107,14 +107,16 @@ typedef enum { DAWN_W_U32 = 0, DAWN_W_F32 = 1, DAWN_W_I32 = 2, DAWN_W_UNIT = 3 }
  *   edges_scanned    sum over steps of the out-degrees of the rows expanded
  *                    (single source with ss_skip: a row lowered again within
  *                    its step is expanded, and counted, in the next step only;
- *                    single-source and batch runs with uint32 or fp32 weights
- *                    may leave rows far above the frontier's smallest distance
- *                    for a later step, which then counts them);
+ *                    single-source and batch runs with uint32 or fp32 weights, and
+ *                    multi-source calls that run as such (see mode), may leave rows
+ *                    far above the frontier's smallest distance for a later step,
+ *                    which then counts them);
  *   improvements     per step, the vertices whose distance the step lowered
  *                    (two decreases of one vertex in one step count once).
  * For a batched call the counters are summed over its sources and `steps` is
  * the largest per-source step count; union_rows / union_edges count the rows
- * and edges the tile actually read (each serving every source active there);
+ * and edges the tile actually read (each serving every source active there; in
+ * steps that run without a tile each serves one source);
  * improvements counts, per step, the (vertex, source) pairs whose distance
  * the step lowered (two decreases of one pair in one step count once).  The
  * row and edge counters are taken from the frontier of each step (the same
@@ -265,8 +267,10 @@ const char* dawn_last_error(void);
  * those streams.  Returns DAWN_OK when each of them converged (status 1), else
  * DAWN_E_INCOMPLETE with *incomplete_runs = how many did not and
  * *last_status = the dawn_run_info.converged code of the last one; the record
- * is cleared by the call.  Either output pointer may be NULL.  Blocking (it
- * copies two words from the device). */
+ * is cleared by the call.  Either output pointer may be NULL.  Blocking: it waits
+ * for the default stream, as a copy from the device would; a host word that the
+ * first call on a device puts in place, and that only a failing run sets, saves the
+ * copies themselves when no run has failed. */
 dawn_status dawn_run_status(int32_t* incomplete_runs, int32_t* last_status);
 
 /* ---------------------------------------------------------------------------

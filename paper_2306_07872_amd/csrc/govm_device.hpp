@@ -45,7 +45,7 @@ struct alignas(128) GridBar {
   unsigned long long slot[kMaxGrid];
 };
 
-// Deferral of far rows in multi-workgroup single-source runs (NearFar below).
+// Deferral of far rows in multi-workgroup single-source runs (nf_advance).
 struct NfState {
   uint32_t thr;    // key: the step expands frontier rows up to it
   float delta;     // thr minus the smallest frontier distance, in distance units

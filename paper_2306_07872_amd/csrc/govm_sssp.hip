@@ -21,7 +21,7 @@
 //   right next-step queue (wavefront ballot + mbcnt prefix, gathered per
 //   workgroup in LDS, one atomicAdd per tier and workgroup).  The scan clears
 //   the bitmap of the current step, n/32 words per step.
-// - Rows far above the frontier's smallest distance may be left in the frontier
+// - Short rows far above the frontier's smallest distance may be left in the frontier
 //   for a later step (see "deferral of far rows").
 // - The relaxation reads alpha[v] with a plain load first (a stale value can
 //   only be higher, so skipping on it is safe) and uses atomicMin only when
@@ -70,7 +70,7 @@ namespace dawn {
 // (R-MAT) the rows that matter are reached in few steps whose distances lie
 // close together, and deferral only adds steps (a CPU model of R-MAT scale 18
 // with lognormal weights: 15 steps instead of 12 for 1 % less work).  Measured:
-// 2048 x 2048 grid 73.8 -> 38 ms (1187M -> 66M edges expanded), 64 ER graphs in
+// 2048 x 2048 grid 73.8 -> 39 ms (1187M -> 66M edges expanded), 64 ER graphs in
 // one launch 11.8 -> 6.0 ms, together with the scan's order and kFresh below.
 // ---------------------------------------------------------------------------
 // SsCtl::converged of a run on copies that is not needed: the tile's is done.
