@@ -52,9 +52,10 @@ namespace dawn {
 // others in the frontier: their bits go to a bitmap of their own, read and written
 // by the lane that scans the word alone, so that the next step's bitmap holds the
 // vertices that the step lowered and nothing else, and is counted as such.  A
-// persistent launch keeps the words of a wavefront's first block in a register and
-// the others in df (2048 x 2048 grid: 40.4 ms; 42.2 with all of them in df; 39.4 with
-// the bits in the next step's bitmap, where they could not be told apart).
+// persistent launch keeps the words of a wavefront's first block in a register, on
+// copies those of its next blocks in LDS, and the others in df (2048 x 2048 grid 38.1
+// ms, 38.2 with the bits in the next step's bitmap, where they could not be told
+// apart; 8 sources 106 ms, 117 with all but the first blocks in df).
 // (Rows of the queued tiers are never left: a queue entry lasts one step.)  The
 // fixed point does not depend on the order
 // (distances are unique), and a row at M is always expanded.  With weights >= 0
@@ -70,7 +71,7 @@ namespace dawn {
 // (R-MAT) the rows that matter are reached in few steps whose distances lie
 // close together, and deferral only adds steps (a CPU model of R-MAT scale 18
 // with lognormal weights: 15 steps instead of 12 for 1 % less work).  Measured:
-// 2048 x 2048 grid 73.8 -> 39 ms (1187M -> 66M edges expanded), 64 ER graphs in
+// 2048 x 2048 grid 73.8 -> 38 ms (1187M -> 66M edges expanded), 64 ER graphs in
 // one launch 11.8 -> 6.0 ms, together with the scan's order and kFresh below.
 // ---------------------------------------------------------------------------
 // SsCtl::converged of a run on copies that is not needed: the tile's is done.
@@ -814,19 +815,21 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
     for (int64_t w0 = 0; w0 + split.first < split.nwords; w0 += split.block(), block++) {
       const int64_t wi = split.word(w0, lane);
       uint32_t* def = sh.def[wave];
-      uint32_t bits = 0u, left = 0u;
+      uint32_t bits = 0u, left = 0u, word = 0u;
       if (wi < split.nwords) {
-        const uint32_t word = ld_agent(&A.bm[cur][wi]), hv = A.hv[wi];
+        word = ld_agent(&A.bm[cur][wi]);
         if (NF)
           left = w0 == 0 ? left0
                  : COPIES && block <= nheld ? held[((block - 1) * W + wave) * kWave + lane]
                                             : ld_agent(&A.df[wi]);
+        bits = left;
         if (word) {
-          st_agent(&A.bm[cur][wi], 0u);
+          // (read only here: 8 sources on that grid, 1M words a step, most of them zero:
+          // 123 ms with the long-row words of all read, 106 so)
+          bits |= word & ~A.hv[wi];
+          if (!NF) st_agent(&A.bm[cur][wi], 0u);
           if (count) acc.im += (unsigned long long)__popc(word);
         }
-        if (word) bits = word & ~hv;
-        bits |= left;
       }
       if (NF) def[lane] = 0u;
       scan_rows(sh.scan[wave], bits, [&](bool has, int o, int bit) {
@@ -863,6 +866,9 @@ __device__ __forceinline__ bool ss_step(const SsArgs& A, uint32_t step, uint32_t
         });
       });
       if (NF) {
+        // (cleared only now: what waits for a load waits for an earlier store too, a
+        // round trip per block: 2048 x 2048 grid 40.3 ms with the store first, 38.2 here)
+        if (word) st_agent(&A.bm[cur][wi], 0u);
         wave_lds_sync();
         const uint32_t x = def[lane];
         if (w0 == 0) left0 = x;
@@ -1838,7 +1844,7 @@ static dawn_status ss_launch_persistent(const SsArgs& a, SsWgs wgs, int threads,
   const int grid = (int)std::max(wgs.even, wgs.wide);
   SsArgs args = a;
   // Copies: LDS for the rows left for later in the blocks after each wavefront's
-  // first (1000 x 1021 grid, 32 sources: 64 ms; 69 with them in memory), as far as
+  // first (1000 x 1021 grid, 32 sources: 58.9 ms; 62.7 with them in memory), as far as
   // the resident workgroups' LDS (with 2 KiB of each for its allocation's rounding)
   // and 64 KiB a workgroup go.
   int32_t nheld = 0;
@@ -2043,8 +2049,8 @@ static SsLayout ss_copies_layout(int64_t n, int64_t m, int64_t k) {
 // R-MAT scale 20 with 8, k = 4 651 / 745, k = 8 1160 / 793; with 16, k = 2 558 / 840,
 // k = 4 1014 / 869; with 5, k = 32 3452 / 850; ER n = 1,000,000 with 8, k = 4 758 /
 // 1053, k = 8 1375 / 1255.  Grids, tile / copies / tile first: 1000 x 1021, k = 8
-// 77.7 / 38.2 / 39.2 ms, k = 32 157.4 / 58.7 / 64.2 ms; 200 x 221, k = 8 - / 4.06 /
-// 4.59 ms.  Tile first where copies alone lose: R-MAT scale 20 with 3, k = 32 1.81
+// 77.7 / 38.2 / 38.3 ms, k = 32 157.4 / 58.7 / 58.9 ms; 200 x 221, k = 8 - / 4.06 /
+// 4.41 ms.  Tile first where copies alone lose: R-MAT scale 20 with 3, k = 32 1.81
 // ms, ER n = 100,000 with 3, k = 8 837 us.
 static int ss_copies_most(int64_t n, int64_t m, bool unit) {
   if (m < 6 * n) return 4;
