@@ -150,7 +150,8 @@ typedef struct {
  * on the host: a run is a fixed launch sequence, and a launch that finds the
  * run already ended returns at once.
  *   0 auto: single source and batches of graphs run in one workgroup when
- *     m <= small_m, as mode 1 when m >= step_min_m, else as mode 2; tiles
+ *     m <= small_m and n <= 32768 (or m <= small_m under graph capture), as
+ *     mode 1 when m >= step_min_m, else as mode 2; tiles
  *     (dawn_msssp, dawn_apsp, dawn_umsssp_ws) as mode 1, unless the
  *     call runs in one workgroup per source (see small_m) or, with few
  *     sources and not under graph capture, as one single-source run on
@@ -209,8 +210,9 @@ typedef struct {
                            multi-source calls on such graphs in one workgroup per source;
                            default 131072, 0 = never */
   int32_t step_min_m;   /* mode 0: graphs with at least this many edges start with step
-                           launches (see mode); default INT32_MAX: none do, except
-                           runs with pull steps from 1 << 25 edges on */
+                           launches (see mode); default INT32_MAX: none do, except,
+                           from 1 << 25 edges on, runs with pull steps and captured
+                           runs */
   int32_t tile_sparse;  /* tile rows (and workgroup chunks) with at most this many active
                            sources are relaxed one edge per lane, 4 bytes per source,
                            instead of 16 lanes per 64-source segment; 0..512, default 8 */
